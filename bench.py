@@ -35,6 +35,7 @@ PMC_GROUPS = {
     "krylov": ("k_krylov.hip", "common.hpp", "batch.hpp"),
     "hessenberg": ("k_hessenberg.hip", "common.hpp", "batch.hpp"),
     "band": ("k_band.hip", "common.hpp", "batch.hpp"),
+    "hier": ("k_hier.hip", "common.hpp", "batch.hpp"),
 }
 PMC_KERNEL_GROUP = {
     "assemble": "factor", "lu_diag": "factor", "lu_panel": "factor", "lu_update": "factor",
@@ -47,6 +48,8 @@ PMC_KERNEL_GROUP = {
     "hess_lsolve": "hessenberg",
     "band_panel": "band", "band_update": "band", "band_init": "band", "band_finish": "band",
     "band_lu_panel": "factor", "band_lu_rows": "factor", "band_lu_step": "factor", "band_lsolve": "factor",
+    "hier_leaf": "hier", "hier_init": "hier", "hier_node": "hier", "hier_cols": "hier", "hier_sub": "hier",
+    "hier_up": "hier",
 }
 # Per measured workload: the source hashes of every kernel group when its counters were taken,
 # and the bytes per launch.  Workload keys: the bench workload, plus a route letter for the
@@ -132,7 +135,8 @@ def measured_mfma_peak(prec):
 
 
 FLOP_KERNELS = ("lu_diag", "lu_panel", "lu_update", "hess_lu", "hess_reduce", "hess_uinv",
-                "band_panel", "band_update", "band_lu_panel", "band_lu_rows", "band_lu_step", "qgemm")
+                "band_panel", "band_update", "band_lu_panel", "band_lu_rows", "band_lu_step", "qgemm",
+                "hier_leaf", "hier_init", "hier_node", "hier_cols")
 
 
 def kernel_table(prof, steps, prec):
@@ -147,7 +151,7 @@ def kernel_table(prof, steps, prec):
             rate = v["work"] / (v["total_ms"] * 1e-3)
             if k in FLOP_KERNELS:
                 fp32 = k in ("lu_diag", "lu_panel", "lu_update", "band_lu_rows", "band_lu_panel", "band_lu_step",
-                             "hess_lu", "hess_uinv")
+                             "hess_lu", "hess_uinv", "hier_leaf", "hier_init", "hier_node", "hier_cols")
                 peak = PEAK_FP32_TFLOPS if (prec == "mixed" and fp32) else PEAK_FP64_TFLOPS
                 row["TFLOPs"] = round(rate / 1e12, 3)
                 row["frac"] = round(rate / 1e12 / peak, 4)
@@ -306,7 +310,8 @@ def timed_steps(S, u0, f, out, prec, steps, warmup, pc=None):
               "time_irfft", "bvm_matvec", "mgs", "cgs", "arnoldi", "normalize", "residual", "update_x", "rhs", "dot",
               "hess_reduce", "hess_formq", "hess_lu", "hess_uinv", "qgemm", "hess_lsolve",
               "band_init", "band_panel", "band_update", "band_finish", "band_lu_panel", "band_lu_rows",
-              "band_lu_step", "band_lsolve"):
+              "band_lu_step", "band_lsolve", "hier_leaf", "hier_init", "hier_node", "hier_cols", "hier_sub",
+              "hier_up"):
         q = S.profile_query(k)
         if q["count"]:
             prof[k] = q
@@ -321,12 +326,12 @@ def roofline(prof, prec, workload_name=None, read_peak=None):
     name, q = max(prof.items(), key=lambda kv: kv[1]["total_ms"])
     avg_ms = q["total_ms"] / q["count"]
     traffic = measured_traffic(workload_name, prec, name)
-    if name.startswith("hess_") or name in ("band_panel", "band_lu_panel"):
-        # the Hessenberg reduction, the shifted LUs and the band panels: flops on the vector ALUs
+    if name.startswith("hess_") or name in ("band_panel", "band_lu_panel", "hier_leaf"):
+        # the Hessenberg reduction, the shifted LUs, the band panels and the leaf inverses: flops on the vector ALUs
         # in chains of dependent steps (latency-bound), priced against the vector peak of the
         # precision they run in (the reductions are FP64 in either form)
         achieved = q["work"] / (q["total_ms"] * 1e-3) / 1e12
-        fp32 = prec == "mixed" and name in ("hess_lu", "hess_uinv", "band_lu_panel")
+        fp32 = prec == "mixed" and name in ("hess_lu", "hess_uinv", "band_lu_panel", "hier_leaf")
         peak = PEAK_FP32_TFLOPS if fp32 else PEAK_FP64_TFLOPS
         return {"kernel": name, "bound": "alu", "achieved": round(achieved, 4),
                 "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 5),
@@ -665,8 +670,14 @@ def main():
     result["changed_rhs"] = {"ms_per_step": round(ms_alt, 4), "value": round(1000.0 / ms_alt, 4),
                              "rhs": f"alternating {p.name} and {q.name}'s u0, f"}
     route_names = {N.FDE_BLOCKS_LU: "lu", N.FDE_BLOCKS_HESSENBERG: "hessenberg", N.FDE_BLOCKS_BAND: "band"}
-    in_use = S.get_option(N.FDE_OPT_BLOCKS_IN_USE)  # the headline form's route (before the mixed form's)
-    result["config"]["blocks"] = route_names.get(in_use, in_use)
+
+    def blocks_in_use():
+        if S.get_option(N.FDE_OPT_COMPRESS_IN_USE):
+            return "hierarchical"
+        return route_names.get(S.get_option(N.FDE_OPT_BLOCKS_IN_USE))
+
+    in_use = blocks_in_use()  # the headline form's (before the mixed form's)
+    result["config"]["blocks"] = in_use
     if not args.no_mixed:
         ms2, _, infos2, prof2 = timed_steps(S, u0, f, out, "mixed", args.steps, args.warmup)
         u_mixed = DEV.get(out)
@@ -677,16 +688,16 @@ def main():
             "t_solve_ms": round(infos2[-1]["t_solve_ms"], 3),
             "rel_diff_vs_fp64": float(np.linalg.norm(u_mixed - u_main) / np.linalg.norm(u_main)),
             "speedup_vs_fp64": round(ms / ms2, 3),
-            "blocks": route_names.get(S.get_option(N.FDE_OPT_BLOCKS_IN_USE)),
+            "blocks": blocks_in_use(),
             "kernels": kernel_table(prof2, args.steps, "mixed"),
             "roofline": roofline(prof2, "mixed", args.workload, read_peak),
         }
     if not args.no_hessenberg:
-        # the same preconditioner S with its blocks solved by the other routes: dense block LU,
+        # the same preconditioner S with its blocks solved by the dense routes: block LU,
         # one Hessenberg form of J (m <= 1024), one band form of J
         for key, route in (("lu", N.FDE_BLOCKS_LU), ("band", N.FDE_BLOCKS_BAND),
                            ("hessenberg", N.FDE_BLOCKS_HESSENBERG)):
-            if route == in_use:
+            if key == in_use:
                 continue
             result[key] = {}
             for form in ("fp64", "mixed"):

@@ -205,7 +205,9 @@ typedef enum {
   FDE_OPT_ORTHO = 8,
   FDE_OPT_BLOCKS_IN_USE = 9,
   FDE_OPT_X0_GATE = 10,
-  FDE_OPT_X0_KEPT = 11
+  FDE_OPT_X0_KEPT = 11,
+  FDE_OPT_COMPRESS = 12,
+  FDE_OPT_COMPRESS_IN_USE = 13
 } fde_option;
 /* FDE_OPT_X0_GATE decides whether an initial guess is used, in millionths: after the scaling by
  * gamma (see fde_solve_opts), a guess with ||b - gamma M x0|| > gate 1e-6 ||b|| is dropped and
@@ -276,6 +278,19 @@ typedef enum { FDE_BLOCKS_LU = 0, FDE_BLOCKS_HESSENBERG = 1, FDE_BLOCKS_BAND = 2
 #define FDE_BAND_MIN_M_FP64_LONG 960
 #define FDE_BAND_LONG_NB 257
 #define FDE_BAND_MIN_M_MIXED 1792
+/* FDE_OPT_COMPRESS: the blocks in hierarchical form.  Away from the diagonal the Toeplitz part of J has
+ * ranges of rows and columns coupled by matrices of rank at most 32 to working precision, the same
+ * for all frequencies; block elimination over that structure applies K_k^{-1} from about
+ * (64 + 25 log2(m / 64)) m numbers per block instead of m^2 or m^2 / 2, in the block's precision and
+ * with the same operator S^{-1} up to rounding.
+ *   0  never;
+ *   1  (default) with FDE_BLOCKS_AUTO, from m = 257 on;
+ *   2  whenever the problem allows it, whatever FDE_OPT_BLOCKS says.
+ * It needs blocks that are diagonally dominant, Re(lambda_k conj mu_k) >= 0 for every frequency (all
+ * built-in formulas); other problems keep the dense route.  FDE_OPT_BLOCKS_IN_USE still names the
+ * dense route that the sizes select, the one whose factors fde_get_factor_block and
+ * fde_get_hessenberg return; with the hierarchical form in use (FDE_OPT_COMPRESS_IN_USE, read-only)
+ * those are computed when first asked for.  Changing the option discards the factorization. */
 /* FDE_OPT_ORTHO selects the Arnoldi orthogonalisation (FP64 either way):
  *   FDE_ORTHO_MGS   (default) modified Gram-Schmidt, j + 2 dependent launches at step j.
  *   FDE_ORTHO_CGS2  classical Gram-Schmidt applied twice: three launches per step whatever j;

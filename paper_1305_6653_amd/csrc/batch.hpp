@@ -8,6 +8,10 @@
 
 namespace fde {
 
+// Hierarchical form of the blocks (k_hier.hip): levels of 64 << l rows a half, ranks up to 32
+static constexpr int HIER_LEVELS = 6, HIER_RMAX = 32;
+static constexpr int HIER_CHUNK = 4;  // panels per workgroup of the apply's first kernel
+
 struct InstDesc {
   // sizes
   int m, s, mp, nb, npan, log2L, log2s, mu1, nu;
@@ -39,6 +43,11 @@ struct InstDesc {
   double2 *hl;
   int *hpiv;
   double2 *Vts;
+  // hierarchical form of the blocks: levels in use (0: one leaf), columns per level, the basis
+  // tables, leaf inverses, W', G and the panel partials of an apply (layouts in k_hier.hip)
+  int nlev, hR[HIER_LEVELS];
+  const double *hx;
+  void *hD, *hW[HIER_LEVELS], *hG[HIER_LEVELS], *ha;
   // vectors (FP64, [s][m] unless noted)
   double *V, *Z;              // (R+1) and R vectors
   double *w, *x, *b, *tmp, *sio;
@@ -50,6 +59,12 @@ struct InstDesc {
   double *h2;                 // [R+2] second Gram-Schmidt pass of the current column
   unsigned *gctr;             // [1] chunks done in the current Gram-Schmidt launch (0 between)
 };
+
+// Nodes of level `lev` over npan panels: pairs of 1 << lev panels whose right half is not empty.
+__host__ __device__ inline int hier_nodes_p(int npan, int lev) {
+  return (npan + (1 << lev) - 1) >> (lev + 1);
+}
+__host__ __device__ inline int hier_nodes(int mp, int lev) { return hier_nodes_p(mp >> 6, lev); }
 
 // vector selectors resolved on the device
 enum VSel : int { VS_V = 0, VS_Z, VS_W, VS_X, VS_B, VS_TMP, VS_SIO, VS_U0, VS_JU0 };

@@ -193,6 +193,24 @@ int qgemm_items(int nb, int mp);
 hipError_t launch_qgemm(const InstDesc *D, const ItemMap &map, int items, int trans, int src2,
                         hipStream_t st);
 
+// ---- the blocks in hierarchical form (k_hier.hip) ----
+// items: leaf and init nb npan per instance; node nb nodes(lev); cols nb nodes(lev) times the
+// 32-column chunks of the higher levels' columns 
+template <typename T>
+hipError_t launch_hier_leaf(const InstDesc *D, const ItemMap &map, int items, int *flag, hipStream_t st);
+template <typename T>
+hipError_t launch_hier_init(const InstDesc *D, const ItemMap &map, int items, hipStream_t st);
+template <typename T>
+hipError_t launch_hier_node(const InstDesc *D, const ItemMap &map, int items, int lev, int *flag, hipStream_t st);
+template <typename T>
+hipError_t launch_hier_cols(const InstDesc *D, const ItemMap &map, int items, int lev, hipStream_t st);
+// Vh <- the block solves, in place: `sub` does the leaves and the levels 0 and 1 in chunks of
+// HIER_CHUNK panels, then `up` the levels from 2 on, one each; items nb ceil(npan / HIER_CHUNK)
+template <typename T>
+hipError_t launch_hier_sub(const InstDesc *D, const ItemMap &map, int items, hipStream_t st);
+template <typename T>
+hipError_t launch_hier_up(const InstDesc *D, const ItemMap &map, int items, int lev, hipStream_t st);
+
 // ---- streaming-read probe: out has `blocks` floats; reads bytes (a multiple of 16) of x ----
 hipError_t launch_read_probe(const void *x, size_t bytes, float *out, int blocks, hipStream_t st);
 // back-to-back 16x16x4 MFMAs (FP64 if fp64, else FP32) in `blocks` workgroups of 256 threads;

@@ -198,6 +198,17 @@ struct fde_bvm {
   // LU [nb][npan][128], the reduction's workspace and error flag
   double *d_bAQ = nullptr, *d_bQt = nullptr, *d_bwork = nullptr;
   int *d_bpiv = nullptr, *d_berr = nullptr;
+  // ---- hierarchical form of the blocks (k_hier.hip): its basis tables (they depend on alpha only;
+  // hx_state 1: built, -1: this problem has none), ranks per level for FP64 and FP32 factors, and
+  // the factor storage (allocated when first factored that way).  hier: the current
+  // factorization is in this form; dense_ok: the dense factors of route blk_route are stored
+  int hx_state = 0, nlev = 0, hrank[2][HIER_LEVELS] = {};
+  int hR[HIER_LEVELS] = {};
+  int hier = 0;
+  bool dense_ok = false;
+  double *d_hx = nullptr;
+  void *d_hD = nullptr, *d_hW = nullptr, *d_hG = nullptr, *d_ha = nullptr;
+  size_t hier_bytes[4] = {}, hier_esz = 16;
   // ---- BCCB preconditioner tables (allocated when a BCCB preconditioner is factored)
   double2 *d_chirp = nullptr, *d_bh = nullptr, *d_lamx = nullptr;
   double lam0s = 0.0;
@@ -210,6 +221,7 @@ struct fde_bvm {
   int opt_side = FDE_SIDE_RIGHT;
   int opt_blocks = FDE_BLOCKS_AUTO;
   int opt_ortho = FDE_ORTHO_MGS;
+  int opt_compress = 1;
   int opt_x0_gate = 10000;  // millionths of ||b||
   int x0_kept = 0;          // the last solve used its initial guess
   // ---- profiling
@@ -350,7 +362,9 @@ struct HostMap {
 
 // Item maps of the solve-phase launches over every instance of a plan.
 struct SolveMaps {
-  ItemMap mv, tfft, trsv, kry, rhs, ju0, blk, qg;
+  ItemMap mv, tfft, trsv, kry, rhs, ju0, blk, qg, hsub, hup[HIER_LEVELS];
+  int n_hsub = 0, n_hup[HIER_LEVELS] = {};  // hierarchical instances (trsv, blk, qg: the others)
+  double hsub_bytes = 0, hup_bytes[HIER_LEVELS] = {};
   int n_mv = 0, n_tfft = 0, n_trsv = 0, n_kry = 0, n_rhs = 0, n_ju0 = 0, n_blk = 0, n_qg = 0;
   int pc = 0, route = FDE_BLOCKS_LU;
   int max_log2L = 1, max_log2s = 1, max_mp = 64;
@@ -365,7 +379,8 @@ struct SolveMaps {
 // The same maps with their items skipped for instances whose gate entry is zero.
 static SolveMaps gated(const SolveMaps &S, const int *gate) {
   SolveMaps G = S;
-  for (ItemMap *m : {&G.mv, &G.tfft, &G.trsv, &G.kry, &G.rhs, &G.ju0, &G.blk, &G.qg}) m->gate = gate;
+  for (ItemMap *m : {&G.mv, &G.tfft, &G.trsv, &G.kry, &G.rhs, &G.ju0, &G.blk, &G.qg, &G.hsub}) m->gate = gate;
+  for (ItemMap &m : G.hup) m.gate = gate;
   return G;
 }
 
@@ -555,6 +570,18 @@ static InstDesc make_desc(fde_bvm *h) {
   }
   d.hl = h->d_hl;
   d.Vts = h->blk_route != FDE_BLOCKS_LU ? h->d_Vh2 : h->d_Vh;
+  d.nlev = h->nlev;
+  d.hx = h->d_hx;
+  d.hD = h->d_hD;
+  size_t hw = 0, hg = 0;
+  for (int l = 0; l < HIER_LEVELS; ++l) {
+    d.hR[l] = h->hR[l];
+    d.hW[l] = (char *)h->d_hW + hw;
+    d.hG[l] = (char *)h->d_hG + hg;
+    hw += (size_t)h->nb * h->hR[l] * h->mp * h->hier_esz;
+    hg += (size_t)h->nb * hier_nodes_p(h->npan, l) * 2 * h->hR[l] * h->hR[l] * h->hier_esz;
+  }
+  d.ha = h->d_ha;
   d.pc = h->pc;
   d.lam0s = h->lam0s;
   d.chirp = h->d_chirp;
@@ -594,7 +621,7 @@ static std::string plan_shape_key(const Plan *P, int prec) {
   if (!P->hs.empty() && P->hs[0]->blk_route == FDE_BLOCKS_BAND) k += "b";
   char buf[32];
   for (const fde_bvm *h : P->hs) {
-    snprintf(buf, sizeof buf, ":%dx%d", h->m, h->s);
+    snprintf(buf, sizeof buf, h->hier ? ":%dx%dc" : ":%dx%d", h->m, h->s);
     k += buf;
   }
   return k;
@@ -622,7 +649,8 @@ static int trsv_capacity(int prec) {
 
 static int trsv_wmax(const Plan *P, const fde_bvm *h, int prec) {
   long total_nb = 0;
-  for (const fde_bvm *q : P->hs) total_nb += q->nb;
+  for (const fde_bvm *q : P->hs) total_nb += q->hier ? 0 : q->nb;
+  total_nb = std::max(total_nb, 1L);
   const int cap = trsv_capacity(prec);
   const long w = (cap > 0 && total_nb <= cap) ? cap / total_nb : 1;
   return (int)std::max(1L, std::min<long>(h->npan, w));
@@ -843,6 +871,92 @@ static void build_tables(fde_bvm *h) {
       h->muk[k] += F.b[i] * w;
     }
   }
+}
+
+// The largest size at which FDE_OPT_COMPRESS = 1 leaves the dense routes in place (see
+// hier_choice), in 64-row panels.
+static constexpr int HIER_MIN_PANELS = 5;
+
+// Basis tables of the hierarchical form: per level the pivoted Cholesky factor X of the positive
+// definite Hankel matrix [g_{p+q+2}] of order h = 64 << l, [h][32] with column 0 = e_0 (the g_0
+// entry beside the diagonal) and X in columns 1.., to a largest residual entry of 1e-17 g_2 (the
+// diagonal of the residual bounds all of it).  The weights are taken in extended precision: the
+// matrix is definite to 1e-19 only there, and the pivots below 1e-16 g_2 would otherwise be
+// rounding.  FP32 factors use the leading columns (the pivots fall), to 1e-11 g_2.
+// Fails (false) if 31 columns do not reach 2e-17 g_2.
+static bool hier_basis(const fde_bvm *h, std::vector<double> &table, int rank[2][HIER_LEVELS]) {
+  const int nlev = h->nlev;
+  const int top = nlev > 0 ? 64 << (nlev - 1) : 0;
+  std::vector<long double> g(2 * (size_t)top + 3);
+  const long double al = h->alpha;
+  g[0] = 1.0L;
+  for (size_t k = 0; k + 1 < g.size(); ++k) g[k + 1] = (1.0L - (al + 1.0L) / (long double)(k + 1)) * g[k];
+  table.assign((size_t)(2 * top) * HIER_RMAX, 0.0);
+  std::vector<long double> X, d;
+  for (int l = 0; l < nlev; ++l) {
+    const int N = 64 << l, rmax = HIER_RMAX - 1;
+    double *out = table.data() + (size_t)(N - 64) * HIER_RMAX;
+    X.assign((size_t)N * rmax, 0.0L);  // column by column
+    d.resize(N);
+    for (int p = 0; p < N; ++p) d[p] = g[2 * p + 2];
+    const long double d0 = d[0];
+    int r = 0, r32 = 0;
+    for (;; ++r) {
+      const int j = (int)(std::max_element(d.begin(), d.end()) - d.begin());
+      if (d[j] > 1e-11L * d0) r32 = r + 1;
+      if (!(d[j] > 1e-17L * d0)) break;
+      if (r == rmax) {
+        if (d[j] > 2e-17L * d0) return false;
+        break;
+      }
+      long double *x = &X[(size_t)r * N];
+      const long double *gj = &g[j + 2];
+      for (int p = 0; p < N; ++p) x[p] = gj[p];
+      for (int c = 0; c < r; ++c) {
+        const long double *xc = &X[(size_t)c * N], f = xc[j];
+        for (int p = 0; p < N; ++p) x[p] -= f * xc[p];
+      }
+      const long double s = 1.0L / sqrtl(d[j]);
+      for (int p = 0; p < N; ++p) {
+        x[p] *= s;
+        d[p] -= x[p] * x[p];
+        out[(size_t)p * HIER_RMAX + 1 + r] = (double)x[p];
+      }
+      d[j] = 0.0L;
+    }
+    out[0] = 1.0;
+    rank[0][l] = (r + 1 + 3) & ~3;
+    rank[1][l] = (std::min(r32, r) + 1 + 3) & ~3;
+  }
+  return true;
+}
+
+// Builds and uploads the tables once per coefficient set; hx_state -1 where the form does not apply:
+// a time formula with Re(lambda_k conj mu_k) < 0 (then the blocks need not be dominant and only
+// the dense routes' arithmetic is known to be safe) or a basis that is too wide.
+static fde_status hier_tables(fde_bvm *h) {
+  if (h->hx_state != 0) return FDE_OK;
+  h->nlev = 0;
+  while ((1 << h->nlev) < h->npan) ++h->nlev;
+  bool ok = true;
+  double sa = 0.0, sb = 0.0;  // the eigenvalues' sums carry rounding of this size (lambda_0 = 0)
+  for (double v : h->F.a) sa += std::fabs(v);
+  for (double v : h->F.b) sb += std::fabs(v);
+  for (int k = 0; k < h->nb; ++k) {
+    const double re = h->lam[k].real() * h->muk[k].real() + h->lam[k].imag() * h->muk[k].imag();
+    if (!(re >= -1e-14 * sa * sb) || !(std::abs(h->lam[k]) + std::abs(h->muk[k]) > 1e-12 * (sa + sb))) ok = false;
+  }
+  std::vector<double> table;
+  if (!ok || !hier_basis(h, table, h->hrank)) {
+    h->hx_state = -1;
+    return FDE_OK;
+  }
+  if (!table.empty()) {
+    if (!h->d_hx) STCHK(dalloc_t(h, &h->d_hx, table.size()));
+    HIPCHK(hipMemcpy(h->d_hx, table.data(), table.size() * sizeof(double), hipMemcpyHostToDevice));
+  }
+  h->hx_state = 1;
+  return FDE_OK;
 }
 
 static std::vector<double2> twiddles(int N) {
@@ -1129,6 +1243,7 @@ extern "C" fde_status fde_bvm_setup(const fde_problem *p, fde_bvm **out) {
     return bail(fail(FDE_EDEVICE, "symbol FFT launch failed: %s", hipGetErrorString(hipGetLastError())));
   if (hipStreamSynchronize(q) != hipSuccess) return bail(fail(FDE_EDEVICE, "setup synchronisation failed"));
   if ((st = plan_create({h}, &h->self)) != FDE_OK) return bail(st);
+  if (h->npan >= HIER_MIN_PANELS && (st = hier_tables(h)) != FDE_OK) return bail(st);
   *out = h;
   return FDE_OK;
 }
@@ -1161,6 +1276,8 @@ extern "C" fde_status fde_bvm_set_coefficients(fde_bvm *h, double alpha, const d
   HIPCHK(hipStreamSynchronize(h->stream));
   h->prec = -1;
   h->self->desc_dirty = true;
+  h->hx_state = 0;
+  if (h->npan >= HIER_MIN_PANELS) STCHK(hier_tables(h));
   return FDE_OK;
 }
 
@@ -1207,6 +1324,11 @@ extern "C" fde_status fde_bvm_set_option(fde_bvm *h, int option, int value) {
         return fail(FDE_EINVAL, "FDE_OPT_ORTHO must be FDE_ORTHO_MGS or FDE_ORTHO_CGS2");
       h->opt_ortho = value;
       return FDE_OK;
+    case FDE_OPT_COMPRESS:
+      if (value < 0 || value > 2) return fail(FDE_EINVAL, "FDE_OPT_COMPRESS must be 0, 1 or 2");
+      if (value != h->opt_compress) h->prec = -1;  // factor again before the next solve
+      h->opt_compress = value;
+      return FDE_OK;
     case FDE_OPT_X0_GATE:
       if (value < 0) return fail(FDE_EINVAL, "FDE_OPT_X0_GATE must be >= 0");
       h->opt_x0_gate = value;
@@ -1237,6 +1359,8 @@ extern "C" fde_status fde_bvm_get_option(fde_bvm *h, int option, int *value) {
     case FDE_OPT_BLOCKS: *value = h->opt_blocks; return FDE_OK;
     case FDE_OPT_BLOCKS_IN_USE: *value = h->blk_route; return FDE_OK;
     case FDE_OPT_ORTHO: *value = h->opt_ortho; return FDE_OK;
+    case FDE_OPT_COMPRESS: *value = h->opt_compress; return FDE_OK;
+    case FDE_OPT_COMPRESS_IN_USE: *value = h->prec >= 0 && h->hier ? 1 : 0; return FDE_OK;
     case FDE_OPT_PRECOND: *value = h->opt_precond; return FDE_OK;
     case FDE_OPT_X0_GATE: *value = h->opt_x0_gate; return FDE_OK;
     case FDE_OPT_X0_KEPT: *value = h->x0_kept; return FDE_OK;
@@ -1378,16 +1502,17 @@ static fde_status factor_plan_impl(Plan *P) {
   std::vector<int> it(count);
   for (int i = 0; i < count; ++i) {
     slots[i] = i;
+    if (P->hs[i]->hier) continue;  // not factored densely: no items
     maxpan = std::max(maxpan, P->hs[i]->npan);
     // the assembly writes the first two block rows and columns (the rest is formed by the
     // first trailing update)
     const double mm = P->hs[i]->m, rest = std::max(0.0, mm - assemble_lead());
     asm_bytes += (double)P->hs[i]->nb * (mm * mm - rest * rest) * sizeof(T) * 2.0;
   }
-  auto nrem_of = [&](int i, int p) { return P->hs[i]->npan - p - 1; };
+  auto nrem_of = [&](int i, int p) { return P->hs[i]->hier ? -1 : P->hs[i]->npan - p - 1; };
   // maps: assemble, then per pair (diag p, panel p, band p, diag p+1, panel p+1, rest p)
   std::vector<HostMap> hm;
-  for (int i = 0; i < count; ++i) it[i] = assemble_items(P->hs[i]->mp, P->hs[i]->nb);
+  for (int i = 0; i < count; ++i) it[i] = P->hs[i]->hier ? 0 : assemble_items(P->hs[i]->mp, P->hs[i]->nb);
   hm.push_back(make_map(slots, it));
   for (int p = 0; p < maxpan; p += 2) {
     for (int pp = p; pp <= p + 1; ++pp) {
@@ -1414,7 +1539,7 @@ static fde_status factor_plan_impl(Plan *P) {
   auto wdiag = [&](int p) {
     double w = 0;
     for (fde_bvm *h : P->hs)
-      if (p < h->npan) {
+      if (!h->hier && p < h->npan) {
         const double c = std::min(64, h->m - p * 64);
         w += h->nb * 8.0 * c * c * c / 3.0;
       }
@@ -1423,14 +1548,14 @@ static fde_status factor_plan_impl(Plan *P) {
   auto wpanel = [&](int p) {
     double w = 0;
     for (fde_bvm *h : P->hs)
-      if (p < h->npan) w += h->nb * 8.0 * 64.0 * 64.0 * std::max(0, h->m - (p + 1) * 64);
+      if (!h->hier && p < h->npan) w += h->nb * 8.0 * 64.0 * 64.0 * std::max(0, h->m - (p + 1) * 64);
     return w;
   };
   size_t mi = 1;
   for (int p = 0; p < maxpan; p += 2) {
     double wband = 0, wrest = 0;
     for (fde_bvm *h : P->hs) {
-      if (p >= h->npan) continue;
+      if (h->hier || p >= h->npan) continue;
       const double rem = std::max(0, h->m - (p + 1) * 64), rem2 = std::max(0.0, rem - 64.0);
       wband += h->nb * 8.0 * 64.0 * (rem * rem - rem2 * rem2);
       wrest += h->nb * 8.0 * 128.0 * rem2 * rem2;
@@ -1467,11 +1592,12 @@ static fde_status hess_factor(Plan *P) {
   double wlu = 0.0;
   for (int i = 0; i < count; ++i) {
     fde_bvm *h = P->hs[i];
+    slots[i] = i;
+    if (h->hier) continue;
     const double m = h->m;
     HIPCHK(run(L, "hess_reduce", 10.0 / 3.0 * m * m * m + 4.0 * m * m * m, [&] {
       return launch_hess_reduce(P->d_desc, i, h->m, h->hwk, st);
     }));
-    slots[i] = i;
     a[i] = h->nb;
     b[i] = h->nb * h->npan;
     max_mp = std::max(max_mp, h->mp);
@@ -1482,7 +1608,7 @@ static fde_status hess_factor(Plan *P) {
   STCHK(upload_maps(P, hm, dm));
   HIPCHK(run(L, "hess_lu", wlu, [&] { return launch_hess_lu<T>(P->d_desc, dm[0], hm[0].items, max_mp, P->d_flag, st); }));
   double winv = 0.0;
-  for (fde_bvm *h : P->hs) winv += h->nb * h->npan * 8.0 * 64.0 * 64.0 * 64.0 / 6.0;
+  for (fde_bvm *h : P->hs) winv += h->hier ? 0.0 : h->nb * h->npan * 8.0 * 64.0 * 64.0 * 64.0 / 6.0;
   HIPCHK(run(L, "hess_uinv", winv, [&] { return launch_hess_uinv<T>(P->d_desc, dm[1], hm[1].items, P->d_flag, st); }));
   return FDE_OK;
 }
@@ -1539,8 +1665,9 @@ static fde_status band_factor(Plan *P) {
   hipStream_t st = L->stream;
   int maxpan = 0;
   for (int i = 0; i < count; ++i) {
-    TraceRange tr("band reduction of J");
     fde_bvm *h = P->hs[i];
+    if (h->hier) continue;
+    TraceRange tr("band reduction of J");
     maxpan = std::max(maxpan, h->npan);
     // algorithmic flops: the panel QR of a w x 64 block 2 * 64^2 (w - 64/3); the two-sided update
     // with its product into Q 4 (2 mp) w 64 + 4 w^2 64 (right update of [A; Q], left update)
@@ -1585,11 +1712,12 @@ static fde_status band_factor(Plan *P) {
   for (int i = 0; i < count; ++i) slots[i] = i;
   std::vector<HostMap> hm;
   for (int j = 0; j < maxpan; ++j) {
-    for (int i = 0; i < count; ++i) it[i] = j < P->hs[i]->npan ? P->hs[i]->nb : 0;
+    auto npan = [&](int i) { return P->hs[i]->hier ? 0 : P->hs[i]->npan; };
+    for (int i = 0; i < count; ++i) it[i] = j < npan(i) ? P->hs[i]->nb : 0;
     hm.push_back(make_map(slots, it));  // panel j
-    for (int i = 0; i < count; ++i) it[i] = P->hs[i]->npan - j - 1 >= 1 ? P->hs[i]->nb : 0;
+    for (int i = 0; i < count; ++i) it[i] = npan(i) - j - 1 >= 1 ? P->hs[i]->nb : 0;
     hm.push_back(make_map(slots, it));  // row tile 0 of step j
-    for (int i = 0; i < count; ++i) it[i] = std::max(0, P->hs[i]->npan - j - 2) * P->hs[i]->nb;
+    for (int i = 0; i < count; ++i) it[i] = std::max(0, npan(i) - j - 2) * P->hs[i]->nb;
     hm.push_back(make_map(slots, it));  // row tiles 1 .. of step j
   }
   std::vector<ItemMap> dm;
@@ -1599,7 +1727,7 @@ static fde_status band_factor(Plan *P) {
   auto panel_work = [&](int j) {
     double w = 0.0;
     for (fde_bvm *h : P->hs) {
-      if (j >= h->npan) continue;
+      if (h->hier || j >= h->npan) continue;
       const double nr = j + 1 < h->npan ? 128.0 : 64.0;
       w += h->nb * 8.0 * 64.0 * 64.0 * (nr - 64.0 / 3.0) / 2.0;
     }
@@ -1624,6 +1752,175 @@ static fde_status band_factor(Plan *P) {
 
 static fde_status bccb_prepare(fde_bvm *h);
 
+// Factor storage of the hierarchical form for one precision: the ranks in use, leaf inverses, W',
+// G and the apply's panel partials.
+static fde_status hier_alloc(fde_bvm *h, fde_precision prec) {
+  const size_t esz = prec == FDE_FP64 ? sizeof(double2) : sizeof(float2), nb = h->nb;
+  h->hier_esz = esz;
+  size_t w = 0, g = 0;
+  for (int l = 0; l < HIER_LEVELS; ++l) {
+    h->hR[l] = l < h->nlev ? h->hrank[prec == FDE_FP64 ? 0 : 1][l] : 0;
+    w += (size_t)h->hR[l] * h->mp;
+    g += (size_t)hier_nodes_p(h->npan, l) * 2 * h->hR[l] * h->hR[l];
+  }
+  void **ptr[4] = {&h->d_hD, &h->d_hW, &h->d_hG, &h->d_ha};
+  const size_t need[4] = {nb * h->npan * 4096 * esz, nb * w * esz, nb * g * esz, 2 * nb * h->npan * 32 * esz};
+  for (int i = 0; i < 4; ++i) {
+    if (*ptr[i] && h->hier_bytes[i] == need[i]) continue;
+    HIPCHK(hipStreamSynchronize(h->stream));
+    dfree(h, *ptr[i]);
+    *ptr[i] = nullptr;
+    h->hier_bytes[i] = 0;
+    STCHK(dalloc(h, ptr[i], need[i]));
+    h->hier_bytes[i] = need[i];
+  }
+  return FDE_OK;
+}
+
+// The hierarchical factorization of every instance in that form: leaf inverses, W of all levels
+// from them, then level by level the node kernel and the elimination of the levels above.
+template <typename T>
+static fde_status hier_factor(Plan *P) {
+  fde_bvm *L = P->lead;
+  hipStream_t st = L->stream;
+  const int count = (int)P->hs.size();
+  std::vector<int> slots(count), it(count);
+  int nlev = 0;
+  auto fill = [&](const std::function<int(const fde_bvm *)> &n) {
+    for (int i = 0; i < count; ++i) {
+      slots[i] = i;
+      it[i] = P->hs[i]->hier ? n(P->hs[i]) : 0;
+      if (P->hs[i]->hier) nlev = std::max(nlev, P->hs[i]->nlev);
+    }
+    return make_map(slots, it);
+  };
+  // algorithmic flops: 8 per complex multiply-add, 4 per real times complex one
+  double wleaf = 0.0, winit = 0.0;
+  std::vector<double> wnode(HIER_LEVELS, 0.0), wcols(HIER_LEVELS, 0.0);
+  auto higher = [](const fde_bvm *h, int l) {
+    int n = 0;
+    for (int q = l + 1; q < h->nlev; ++q) n += h->hR[q];
+    return n;
+  };
+  for (const fde_bvm *h : P->hs) {
+    if (!h->hier) continue;
+    wleaf += 8.0 * h->nb * h->npan * 64.0 * 64.0 * 64.0;
+    winit += 4.0 * h->nb * h->mp * 64.0 * (3.0 * 64.0 + higher(h, -1));
+    for (int l = 0; l < h->nlev; ++l) {
+      const double r = h->hR[l], n = higher(h, l);
+      wnode[l] += h->nb * (12.0 * h->mp * r * r + 48.0 * hier_nodes_p(h->npan, l) * r * r * r);
+      wcols[l] += h->nb * n * (12.0 * h->mp * r + 16.0 * hier_nodes_p(h->npan, l) * r * r);
+    }
+  }
+  std::vector<HostMap> hm = {fill([](const fde_bvm *h) { return h->nb * h->npan; })};
+  for (int l = 0; l < nlev; ++l) {
+    hm.push_back(fill([&](const fde_bvm *h) { return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) : 0; }));
+    hm.push_back(fill([&](const fde_bvm *h) {
+      return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) * ((higher(h, l) + 31) / 32) : 0;
+    }));
+  }
+  std::vector<ItemMap> dm;
+  STCHK(upload_maps(P, hm, dm));
+  HIPCHK(run(L, "hier_leaf", wleaf, [&] { return launch_hier_leaf<T>(P->d_desc, dm[0], hm[0].items, P->d_flag, st); }));
+  HIPCHK(run(L, "hier_init", winit, [&] { return launch_hier_init<T>(P->d_desc, dm[0], hm[0].items, st); }));
+  for (int l = 0; l < nlev; ++l) {
+    const size_t a = 2 * l + 1, b = a + 1;
+    HIPCHK(run(L, "hier_node", wnode[l], [&] { return launch_hier_node<T>(P->d_desc, dm[a], hm[a].items, l, P->d_flag, st); }));
+    if (hm[b].items > 0)
+      HIPCHK(run(L, "hier_cols", wcols[l], [&] { return launch_hier_cols<T>(P->d_desc, dm[b], hm[b].items, l, st); }));
+  }
+  return FDE_OK;
+}
+
+// The Strang blocks of every instance of the plan: in hierarchical form where the handle's `hier`
+// is set, else by the dense route.
+static fde_status factor_blocks(Plan *P, int route, fde_precision prec) {
+  fde_bvm *L = P->lead;
+  for (fde_bvm *h : P->hs) {
+    h->pc = FDE_PC_STRANG;
+    if (h->blk_route != route && h->self) h->self->desc_dirty = true;
+    h->blk_route = route;
+    h->prec = -1;
+    h->dense_ok = false;
+    if (h->hier) continue;
+    if (route == FDE_BLOCKS_HESSENBERG) STCHK(hess_alloc(h));
+    if (route == FDE_BLOCKS_BAND) STCHK(band_alloc(h));
+  }
+  bool dense = false, hier = false;
+  for (fde_bvm *h : P->hs) hier = hier || h->hier;
+  const size_t esz = prec == FDE_FP64 ? sizeof(double2) : sizeof(float2);
+  for (fde_bvm *h : P->hs) {
+    const size_t Kb = (size_t)h->nb * h->mp * h->mp * esz;
+    const size_t Db = (size_t)h->nb * h->npan * 2 * 64 * 64 * esz;
+    if (h->hier) {
+      STCHK(hier_alloc(h, prec));
+      continue;
+    }
+    dense = true;
+    if (h->K_bytes != Kb) {
+      HIPCHK(hipStreamSynchronize(h->stream));
+      dfree(h, h->d_K);
+      dfree(h, h->d_dinv);
+      h->d_K = h->d_dinv = nullptr;
+      h->K_bytes = 0;
+      STCHK(dalloc(h, &h->d_K, Kb));
+      STCHK(dalloc(h, &h->d_dinv, Db));
+      h->K_bytes = Kb;
+      if (h->self) h->self->desc_dirty = true;
+    }
+  }
+  // plan_prepare uploads the descriptors only if one of them changed (a refactorisation of
+  // the same shape keeps them, and needs no host round trip here)
+  STCHK(plan_prepare(P, std::max(P->R, 1), prec));
+  hipEvent_t e0 = get_event(L), e1 = get_event(L);
+  HIPCHK(hipMemsetAsync(P->d_flag, 0, sizeof(int), L->stream));
+  HIPCHK(hipEventRecord(e0, L->stream));
+  if (hier) {
+    TraceRange tr("blocks: hierarchical form");
+    STCHK(prec == FDE_FP64 ? hier_factor<double>(P) : hier_factor<float>(P));
+  }
+  if (!dense) {
+  } else if (route == FDE_BLOCKS_HESSENBERG) {
+    TraceRange tr("blocks: Hessenberg route");
+    STCHK(prec == FDE_FP64 ? hess_factor<double>(P) : hess_factor<float>(P));
+  } else if (route == FDE_BLOCKS_BAND) {
+    TraceRange tr("blocks: band route");
+    STCHK(prec == FDE_FP64 ? band_factor<double>(P) : band_factor<float>(P));
+  } else {
+    TraceRange tr("blocks: block LU");
+    STCHK(prec == FDE_FP64 ? factor_plan_impl<double>(P) : factor_plan_impl<float>(P));
+  }
+  HIPCHK(hipEventRecord(e1, L->stream));
+  int *flag_pin = (int *)((char *)P->pin + P->pin_err) + 1;  // pinned: no staging copy
+  HIPCHK(hipMemcpyAsync(flag_pin, P->d_flag, sizeof(int), hipMemcpyDeviceToHost, L->stream));
+  std::vector<int> herr(P->hs.size(), 0);
+  if (route == FDE_BLOCKS_HESSENBERG)
+    for (size_t i = 0; i < P->hs.size(); ++i)
+      if (!P->hs[i]->hier)
+        HIPCHK(hipMemcpyAsync(&herr[i], P->hs[i]->hwk.err, sizeof(int), hipMemcpyDeviceToHost, L->stream));
+  if (route == FDE_BLOCKS_BAND)
+    for (size_t i = 0; i < P->hs.size(); ++i)
+      if (!P->hs[i]->hier)
+        HIPCHK(hipMemcpyAsync(&herr[i], P->hs[i]->d_berr, sizeof(int), hipMemcpyDeviceToHost, L->stream));
+  STCHK(sync_and_flush(L));
+  for (size_t i = 0; i < herr.size(); ++i)
+    if (herr[i]) {
+      if (route == FDE_BLOCKS_BAND) (void)hipMemset(P->hs[i]->d_berr, 0, sizeof(int));
+      return fail(FDE_EDEVICE, "the Hessenberg or band reduction of instance %zu did not complete", i);
+    }
+  float ms = 0.0f;
+  HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+  L->evpool.push_back(e0);
+  L->evpool.push_back(e1);
+  if (*flag_pin) return fail(FDE_ESINGULAR, "zero or non-finite pivot in a preconditioner block");
+  for (fde_bvm *h : P->hs) {
+    h->prec = prec;
+    h->t_factor_ms = ms;
+    h->dense_ok = !h->hier;
+  }
+  return FDE_OK;
+}
+
 static fde_status factor_plan(Plan *P, fde_precision prec) {
   if (prec != FDE_FP64 && prec != FDE_MIXED_C32) return fail(FDE_EINVAL, "unknown precision %d", (int)prec);
   TraceRange tr_factor("fde_precond_factor");
@@ -1639,6 +1936,8 @@ static fde_status factor_plan(Plan *P, fde_precision prec) {
     for (fde_bvm *h : P->hs) {
       h->prec = -1;
       h->pc = kind;
+      h->hier = 0;
+      h->dense_ok = false;
       if (kind != FDE_PC_NONE) STCHK(bccb_prepare(h));
       if (h->self) h->self->desc_dirty = true;
     }
@@ -1669,76 +1968,19 @@ static fde_status factor_plan(Plan *P, fde_precision prec) {
     }
     route = band ? FDE_BLOCKS_BAND : FDE_BLOCKS_LU;
   }
+  const bool automatic = P->hs[0]->opt_blocks == FDE_BLOCKS_AUTO;
   for (fde_bvm *h : P->hs) {
-    if (route == FDE_BLOCKS_HESSENBERG && h->m > hess_reduce_max_m())
+    int use = 0;
+    if (h->opt_compress == 2 || (h->opt_compress == 1 && automatic && h->npan >= HIER_MIN_PANELS)) {
+      STCHK(hier_tables(h));
+      use = h->hx_state > 0 ? 1 : 0;
+    }
+    if (!use && route == FDE_BLOCKS_HESSENBERG && h->m > hess_reduce_max_m())
       return fail(FDE_EUNSUPPORTED, "the Hessenberg route takes m <= %d (m = %d)", hess_reduce_max_m(), h->m);
+    if (use != h->hier && h->self) h->self->full_ok = false;
+    h->hier = use;
   }
-  for (fde_bvm *h : P->hs) {
-    h->pc = FDE_PC_STRANG;
-    if (h->blk_route != route && h->self) h->self->desc_dirty = true;
-    h->blk_route = route;
-    if (route == FDE_BLOCKS_HESSENBERG) STCHK(hess_alloc(h));
-    if (route == FDE_BLOCKS_BAND) STCHK(band_alloc(h));
-  }
-  const size_t esz = prec == FDE_FP64 ? sizeof(double2) : sizeof(float2);
-  for (fde_bvm *h : P->hs) {
-    const size_t Kb = (size_t)h->nb * h->mp * h->mp * esz;
-    const size_t Db = (size_t)h->nb * h->npan * 2 * 64 * 64 * esz;
-    h->prec = -1;
-    if (h->K_bytes != Kb) {
-      HIPCHK(hipStreamSynchronize(h->stream));
-      dfree(h, h->d_K);
-      dfree(h, h->d_dinv);
-      h->d_K = h->d_dinv = nullptr;
-      h->K_bytes = 0;
-      STCHK(dalloc(h, &h->d_K, Kb));
-      STCHK(dalloc(h, &h->d_dinv, Db));
-      h->K_bytes = Kb;
-      if (h->self) h->self->desc_dirty = true;
-    }
-  }
-  // plan_prepare uploads the descriptors only if one of them changed (a refactorisation of
-  // the same shape keeps them, and needs no host round trip here)
-  STCHK(plan_prepare(P, std::max(P->R, 1), prec));
-  hipEvent_t e0 = get_event(L), e1 = get_event(L);
-  HIPCHK(hipMemsetAsync(P->d_flag, 0, sizeof(int), L->stream));
-  HIPCHK(hipEventRecord(e0, L->stream));
-  if (route == FDE_BLOCKS_HESSENBERG) {
-    TraceRange tr("blocks: Hessenberg route");
-    STCHK(prec == FDE_FP64 ? hess_factor<double>(P) : hess_factor<float>(P));
-  } else if (route == FDE_BLOCKS_BAND) {
-    TraceRange tr("blocks: band route");
-    STCHK(prec == FDE_FP64 ? band_factor<double>(P) : band_factor<float>(P));
-  } else {
-    TraceRange tr("blocks: block LU");
-    STCHK(prec == FDE_FP64 ? factor_plan_impl<double>(P) : factor_plan_impl<float>(P));
-  }
-  HIPCHK(hipEventRecord(e1, L->stream));
-  int *flag_pin = (int *)((char *)P->pin + P->pin_err) + 1;  // pinned: no staging copy
-  HIPCHK(hipMemcpyAsync(flag_pin, P->d_flag, sizeof(int), hipMemcpyDeviceToHost, L->stream));
-  std::vector<int> herr(P->hs.size(), 0);
-  if (route == FDE_BLOCKS_HESSENBERG)
-    for (size_t i = 0; i < P->hs.size(); ++i)
-      HIPCHK(hipMemcpyAsync(&herr[i], P->hs[i]->hwk.err, sizeof(int), hipMemcpyDeviceToHost, L->stream));
-  if (route == FDE_BLOCKS_BAND)
-    for (size_t i = 0; i < P->hs.size(); ++i)
-      HIPCHK(hipMemcpyAsync(&herr[i], P->hs[i]->d_berr, sizeof(int), hipMemcpyDeviceToHost, L->stream));
-  STCHK(sync_and_flush(L));
-  for (size_t i = 0; i < herr.size(); ++i)
-    if (herr[i]) {
-      if (route == FDE_BLOCKS_BAND) (void)hipMemset(P->hs[i]->d_berr, 0, sizeof(int));
-      return fail(FDE_EDEVICE, "the Hessenberg or band reduction of instance %zu did not complete", i);
-    }
-  float ms = 0.0f;
-  HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-  L->evpool.push_back(e0);
-  L->evpool.push_back(e1);
-  if (*flag_pin) return fail(FDE_ESINGULAR, "zero or non-finite pivot in a preconditioner block");
-  for (fde_bvm *h : P->hs) {
-    h->prec = prec;
-    h->t_factor_ms = ms;
-  }
-  return FDE_OK;
+  return factor_blocks(P, route, prec);
 }
 
 extern "C" fde_status fde_precond_factor(fde_bvm *h, fde_precision prec) {
@@ -1755,8 +1997,10 @@ extern "C" fde_status fde_precond_factor(fde_bvm *h, fde_precision prec) {
 static fde_status ensure_full_maps(Plan *P) {
   const int count = (int)P->hs.size();
   const int prec = P->hs[0]->prec;
-  if (P->full_ok && P->full.prec == prec && P->full.pc == P->hs[0]->pc &&
-      P->full.route == P->hs[0]->blk_route)
+  int route = P->hs[0]->blk_route;  // of the instances in dense form
+  for (int q = count - 1; q >= 0; --q)
+    if (!P->hs[q]->hier) route = P->hs[q]->blk_route;
+  if (P->full_ok && P->full.prec == prec && P->full.pc == P->hs[0]->pc && P->full.route == route)
     return FDE_OK;
   std::vector<int> slots(count), a(count), b(count), c(count), d(count), e(count), f(count), g(count),
       qq(count);
@@ -1772,34 +2016,52 @@ static fde_status ensure_full_maps(Plan *P) {
     auto it = g_tuned_cols.find(plan_shape_key(P, prec));
     if (it != g_tuned_cols.end()) S.tfft_cols = it->second;
   }
+  std::vector<std::vector<int>> hu(HIER_LEVELS + 1, std::vector<int>(count, 0));
   for (int q = 0; q < count; ++q) {
     fde_bvm *h = P->hs[q];
     slots[q] = q;
-    g[q] = h->nb;
+    if (h->hier) {
+      const double esz = h->prec == FDE_FP64 ? 16.0 : 8.0;
+      double in = 64.0;
+      const int chunks = h->nb * ((h->npan + HIER_CHUNK - 1) / HIER_CHUNK);
+      hu[HIER_LEVELS][q] = chunks;
+      for (int l = 0; l < h->nlev; ++l) {
+        if ((2 << l) <= HIER_CHUNK) {
+          in += h->hR[l];
+        } else {
+          hu[l][q] = chunks;
+          S.hup_bytes[l] += (double)h->nb * h->mp * (h->hR[l] * esz + 32.0);
+        }
+      }
+      S.hsub_bytes += (double)h->nb * h->mp * (in * esz + 32.0);
+    }
+    g[q] = h->hier ? 0 : h->nb;
     a[q] = h->s;
     b[q] = h->mp / S.tfft_cols;
-    c[q] = h->nb * P->desc[q].W;
+    c[q] = h->hier ? 0 : h->nb * P->desc[q].W;
     d[q] = h->nblk;
     e[q] = h->s;
     f[q] = h->need_Ju0 ? 1 : 0;
     S.max_log2L = std::max(S.max_log2L, h->log2L);
     S.max_log2s = std::max(S.max_log2s, h->log2s);
     S.max_mp = std::max(S.max_mp, h->mp);
-    qq[q] = qgemm_items(h->nb, h->mp);
+    qq[q] = h->hier ? 0 : qgemm_items(h->nb, h->mp);
+    S.vec_bytes += 8.0 * h->n();
+    S.tfft_bytes += 8.0 * h->n() + 16.0 * h->nb * h->m;
+    if (h->hier) continue;
     const double esz = h->prec == FDE_FP64 ? 16.0 : 8.0;
     const double fac = h->blk_route != FDE_BLOCKS_LU ? 0.5 * h->m * (h->m + 1.0)
                                                              : (double)h->m * h->m;
     S.trsv_bytes += (double)h->nb * fac * esz + 32.0 * h->nb * h->m;
     S.qg_flops += 2.0 * (2.0 * (h->nb - 1)) * h->m * h->m;  // 2 (nb - 1) real rows times Q
-    S.vec_bytes += 8.0 * h->n();
-    S.tfft_bytes += 8.0 * h->n() + 16.0 * h->nb * h->m;
     S.bccb_bytes += 32.0 * h->nb * h->m;  // one complex read and write per (frequency, node)
     // band L solve: the band's L11^{-1} and L21 pieces (2 x 64 x 64 per panel) and the vector
     S.band_l_bytes += (double)h->nb * h->npan * 2.0 * 64.0 * 64.0 * esz + 32.0 * h->nb * h->m;
   }
-  const std::vector<HostMap> hm = {make_map(slots, a), make_map(slots, b), make_map(slots, c),
-                                   make_map(slots, d), make_map(slots, e), make_map(slots, f),
-                                   make_map(slots, g), make_map(slots, qq)};
+  std::vector<HostMap> hm = {make_map(slots, a), make_map(slots, b), make_map(slots, c),
+                             make_map(slots, d), make_map(slots, e), make_map(slots, f),
+                             make_map(slots, g), make_map(slots, qq)};
+  for (const std::vector<int> &u : hu) hm.push_back(make_map(slots, u));
   size_t need = 0;
   for (const HostMap &m : hm) need += m.ids.size() + m.pre.size();
   HIPCHK(hipStreamSynchronize(P->lead->stream));
@@ -1838,8 +2100,14 @@ static fde_status ensure_full_maps(Plan *P) {
   S.n_blk = hm[6].items;
   S.qg = dm[7];
   S.n_qg = hm[7].items;
+  for (int l = 0; l < HIER_LEVELS; ++l) {
+    S.hup[l] = dm[8 + l];
+    S.n_hup[l] = hm[8 + l].items;
+  }
+  S.hsub = dm[8 + HIER_LEVELS];
+  S.n_hsub = hm[8 + HIER_LEVELS].items;
   S.pc = P->hs[0]->pc;
-  S.route = P->hs[0]->blk_route;
+  S.route = route;
   S.n_mv = hm[0].items;
   S.n_tfft = hm[1].items;
   S.n_trsv = hm[2].items;
@@ -1852,9 +2120,10 @@ static fde_status ensure_full_maps(Plan *P) {
   for (fde_bvm *h : P->hs) S.kry_one_n = std::max(S.kry_one_n, h->n());
   for (fde_bvm *h : P->hs)
     if (h->nblk != 1) S.kry_one_n = 0;
-  S.npan_u = P->hs[0]->npan;
+  S.npan_u = -1;
   for (fde_bvm *h : P->hs)
-    if (h->npan != S.npan_u) S.npan_u = 0;
+    if (!h->hier) S.npan_u = S.npan_u < 0 || h->npan == S.npan_u ? h->npan : 0;
+  S.npan_u = std::max(S.npan_u, 0);
   P->full = S;
   P->full_ok = true;
   return FDE_OK;
@@ -1917,6 +2186,25 @@ static fde_status op_precond(Plan *P, const SolveMaps &S, int src, int sj, int d
   HIPCHK(run(L, "time_rfft", S.tfft_bytes, [&] {
     return launch_time_rfft(P->d_desc, S.tfft, S.n_tfft, S.max_log2s, S.tfft_cols, src, sj, st, ctr, P->d_epoch);
   }));
+  if (S.n_hsub > 0) {
+    const bool f64 = S.prec == FDE_FP64;
+    HIPCHK(run(L, "hier_sub", S.hsub_bytes, [&] {
+      return f64 ? launch_hier_sub<double>(P->d_desc, S.hsub, S.n_hsub, st)
+                 : launch_hier_sub<float>(P->d_desc, S.hsub, S.n_hsub, st);
+    }));
+    for (int l = 0; l < HIER_LEVELS; ++l)
+      if (S.n_hup[l] > 0)
+        HIPCHK(run(L, "hier_up", S.hup_bytes[l], [&] {
+          return f64 ? launch_hier_up<double>(P->d_desc, S.hup[l], S.n_hup[l], l, st)
+                     : launch_hier_up<float>(P->d_desc, S.hup[l], S.n_hup[l], l, st);
+        }));
+  }
+  if (S.n_trsv == 0) {
+    HIPCHK(run(L, "time_irfft", S.tfft_bytes, [&] {
+      return launch_time_irfft(P->d_desc, S.tfft, S.n_tfft, S.max_log2s, S.tfft_cols, dst, dj, st);
+    }));
+    return FDE_OK;
+  }
   if (S.route == FDE_BLOCKS_BAND) {
     // Q^T v_k (the frequency vectors are rows: the row v_k^T Q), the band L solve, U^{-1}, Q
     HIPCHK(run(L, "qgemm", S.qg_flops, [&] { return launch_qgemm(P->d_desc, S.qg, S.n_qg, 0, 0, st); }));
@@ -2378,6 +2666,9 @@ static fde_status copy_out(fde_bvm *h, double *dst, const double *src, size_t co
 static fde_status autotune_trsv(Plan *P, int prec) {
   fde_bvm *L = P->lead;
   if (!L->opt_autotune || L->opt_trsv_w != 0 || !g_coop_ok || L->pc != FDE_PC_STRANG) return FDE_OK;
+  bool dense = false;
+  for (const fde_bvm *h : P->hs) dense = dense || !h->hier;
+  if (!dense) return FDE_OK;
   const std::string key = plan_shape_key(P, prec);
   {
     std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -2389,7 +2680,7 @@ static fde_status autotune_trsv(Plan *P, int prec) {
   // four panels (one workgroup streams a whole factor: beyond that it cannot win, and timing
   // it would cost more than the solves it could speed up)
   int npan_max = 0;
-  for (fde_bvm *h : P->hs) npan_max = std::max(npan_max, h->npan);
+  for (fde_bvm *h : P->hs) npan_max = std::max(npan_max, h->hier ? 0 : h->npan);
   std::vector<int> cands;
   if (npan_max <= 4) cands.push_back(-1);
   for (int w = 1; w <= wtop; w = w < 4 ? w + 1 : w + w / 2) cands.push_back(w);
@@ -2709,7 +3000,7 @@ static __device__ __align__(256) unsigned char scratch[NA_BYTES];
 struct NoallocHead {
   InstDesc desc;
   int ids[1];
-  int pre_tfft[2], pre_trsv[2], pre_blk[2];
+  int pre_tfft[2], pre_trsv[2], pre_blk[2], pre_hier[2];
   int err;
   unsigned long long ctr;       // epochs drawn by the applies that used this array
   unsigned long long epoch[2];  // epoch of the current apply, claimed-unit counter
@@ -2737,7 +3028,7 @@ static fde_status noalloc_scratch(void **out) {
 
 // Writes the launch head of one apply (the counter is left as it is); the block solve's error
 // flag starts at zero.
-__global__ void k_noalloc_head(NoallocHead *hd, InstDesc d, int n_tfft, int n_trsv, int n_blk) {
+__global__ void k_noalloc_head(NoallocHead *hd, InstDesc d, int n_tfft, int n_trsv, int n_blk, int n_hier) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   hd->desc = d;
   hd->ids[0] = 0;
@@ -2747,6 +3038,8 @@ __global__ void k_noalloc_head(NoallocHead *hd, InstDesc d, int n_tfft, int n_tr
   hd->pre_trsv[1] = n_trsv;
   hd->pre_blk[0] = 0;
   hd->pre_blk[1] = n_blk;
+  hd->pre_hier[0] = 0;
+  hd->pre_hier[1] = n_hier;
   hd->err = 0;
 }
 
@@ -2780,14 +3073,22 @@ extern "C" fde_status fde_apply_precond_noalloc(fde_bvm *h, const double *v, dou
   d.Vh = (double2 *)(b + NA_HEAD + NA_FLAGS);
   d.Vts = d.Vh;
   hipStream_t st = h->stream;
-  hipLaunchKernelGGL(k_noalloc_head, dim3(1), dim3(64), 0, st, hd, d, n_tfft, n_trsv, n_blk);
+  const int n_hier = h->nb * ((h->npan + HIER_CHUNK - 1) / HIER_CHUNK);
+  hipLaunchKernelGGL(k_noalloc_head, dim3(1), dim3(64), 0, st, hd, d, n_tfft, n_trsv, n_blk, n_hier);
   HIPCHK(hipGetLastError());
   const InstDesc *D = &hd->desc;
   const ItemMap tfft{hd->ids, hd->pre_tfft, 1, nullptr};
   const ItemMap trsv{hd->ids, hd->pre_trsv, 1, nullptr};
   const ItemMap blk{hd->ids, hd->pre_blk, 1, nullptr};
   HIPCHK(launch_time_rfft(D, tfft, n_tfft, h->log2s, cols, VS_SIO, 0, st, &hd->ctr, hd->epoch));
-  if (h->self->trsv_solo)  // the handle's plan takes the ordinary one-workgroup launch (same bits)
+  if (h->hier) {  // its panel partials are the handle's own, everything else as below
+    const ItemMap hm{hd->ids, hd->pre_hier, 1, nullptr};
+    const bool f64 = h->prec == FDE_FP64;
+    HIPCHK(f64 ? launch_hier_sub<double>(D, hm, n_hier, st) : launch_hier_sub<float>(D, hm, n_hier, st));
+    for (int l = 0; l < h->nlev; ++l)
+      if ((2 << l) > HIER_CHUNK)
+        HIPCHK(f64 ? launch_hier_up<double>(D, hm, n_hier, l, st) : launch_hier_up<float>(D, hm, n_hier, l, st));
+  } else if (h->self->trsv_solo)  // the handle's plan takes the ordinary one-workgroup launch (same bits)
     HIPCHK(h->prec == FDE_FP64 ? launch_trsv<double>(D, trsv, n_trsv, 0, st) : launch_trsv<float>(D, trsv, n_trsv, 0, st));
   else
     HIPCHK(h->prec == FDE_FP64
@@ -2834,9 +3135,25 @@ extern "C" fde_status fde_toeplitz_apply(fde_bvm *h, const double *x, double *y,
   return sync_and_flush(h);
 }
 
+// The dense factors behind a factorization in hierarchical form, made when they are first asked for
+// (the solves keep the hierarchical form).
+static fde_status ensure_dense(fde_bvm *h) {
+  if (!h->hier || h->dense_ok) return FDE_OK;
+  const fde_precision prec = (fde_precision)h->prec;
+  const double ms = h->t_factor_ms;
+  h->hier = 0;
+  const fde_status st = factor_blocks(h->self, h->blk_route, prec);
+  h->hier = 1;
+  h->prec = prec;
+  h->t_factor_ms = ms;
+  h->dense_ok = st == FDE_OK;
+  return st;
+}
+
 extern "C" fde_status fde_get_hessenberg(fde_bvm *h, double *H, double *Q) {
   if (!h || !H || !Q) return fail(FDE_EINVAL, "NULL argument");
   const bool band = h->blk_route == FDE_BLOCKS_BAND;
+  if (h->prec >= 0 && h->pc == FDE_PC_STRANG && h->blk_route != FDE_BLOCKS_LU) STCHK(ensure_dense(h));
   if (h->prec < 0 || h->blk_route == FDE_BLOCKS_LU || !(band ? (void *)h->d_bAQ : (void *)h->d_hH))
     return fail(FDE_EINVAL, "no Hessenberg or band factorization stored");
   const size_t m = h->m, mp = h->mp;
@@ -2854,6 +3171,7 @@ extern "C" fde_status fde_get_factor_block(fde_bvm *h, int k, double *out) {
   if (!h || !out) return fail(FDE_EINVAL, "NULL argument");
   if (h->prec < 0) return fail(FDE_EINVAL, "no factorization stored");
   if (k < 0 || k >= h->nb) return fail(FDE_EINVAL, "block %d out of range 0..%d", k, h->nb - 1);
+  STCHK(ensure_dense(h));
   const int m = h->m, mp = h->mp;
   const size_t esz = h->prec == FDE_FP64 ? sizeof(double2) : sizeof(float2);
   std::vector<char> raw((size_t)mp * mp * esz);
