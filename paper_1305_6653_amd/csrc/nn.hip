@@ -1,7 +1,7 @@
 // Learned warm start: a small network that maps one problem instance (alpha, d+(x), d-(x),
 // f(x,t) on the grid) to an initial guess of the all-at-once solution.  Everything runs
 // here on gfx950: feature packing, bf16 MFMA GEMMs with FP32 accumulation (convolutions
-// as im2col + GEMM), ReLU, the fixed synthesis basis, relative-MSE loss, backward pass and
+// as GEMMs over their input rows in place), ReLU, the fixed synthesis basis, relative-MSE loss, backward pass and
 // Adam.  Weights are kept as FP32 masters plus bf16 copies used by the GEMMs.
 //
 // Network (activations position-major, channels last):
@@ -36,67 +36,234 @@ __device__ __forceinline__ unsigned short f2bf(float x) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (unsigned short)(u >> 16);
 }
-__device__ __forceinline__ float bf2f(unsigned short b) { return __uint_as_float(((unsigned)b) << 16); }
 
 // ---------------------------------------------------------------------------------------
-// GEMM  C[M][N] (+)= op(A)[M][K] op(B)[K][N]; element (i,k) of op(A) is A[i*sa0 + k*sa1],
-// element (k,j) of op(B) is B[k*sb0 + j*sb1].  A, B are FP32 or bf16 (TA/TB), converted to
-// bf16 in LDS; v_mfma_f32_16x16x16_bf16 with FP32 accumulation.  64x64 tile per workgroup,
-// 4 waves of 32x32.  Epilogue: + bias[j] (optional), ReLU (optional), accumulate into C
-// (beta = 1) or overwrite.  Lane layout (measured): A[i][k] in lane i + 16*(k/4), element
+// GEMM  C[M][N] (+)= op(A)[M][K] op(B)[K][N]; element (i,k) of op(A) is A[i*sa + k] (AK) or
+// A[i + k*sa], element (k,j) of op(B) is B[j*sb + k] (BK) or B[j + k*sb].  A, B are FP32 or bf16
+// (TA/TB), converted to bf16 on the way to LDS; v_mfma_f32_16x16x16_bf16 with FP32 accumulation.
+// Epilogue: + bias[j] (optional), ReLU (optional), zero where mask <= 0 (optional), accumulate
+// into C (beta = 1) or overwrite.  Lane layout (measured): A[i][k] in lane i + 16*(k/4), element
 // k%4; B[k][j] in lane j + 16*(k/4), element k%4; D[4*(lane/16) + v][lane%16].
-template <typename T> __device__ __forceinline__ float ldf(const T *p, size_t i);
-template <> __device__ __forceinline__ float ldf<float>(const float *p, size_t i) { return p[i]; }
-template <> __device__ __forceinline__ float ldf<unsigned short>(const unsigned short *p, size_t i) {
-  return bf2f(p[i]);
+//
+// These products are small (0.1 to 2 GFLOP) and were bound by their K steps, one global round trip
+// and two barriers per 16: 60 to 127 us each.  A step is 64 deep, a thread loads 4 x 4 elements of
+// each operand (vector loads, transposed in registers where the contiguous direction is not k) two
+// steps ahead, and the LDS tiles are double-buffered, so a step is one barrier.  Tiles are 64 x TN:
+// 64 wide, or 16 where 64 would leave CUs without a workgroup.  Either way an element sums
+// the same 16-deep MFMA steps in the same order, so the choice does not show in the result.
+typedef unsigned short us4 __attribute__((ext_vector_type(4)));
+static constexpr int GKLD = 72;  // LDS row stride, 64 k and a pad
+
+// The rows of a convolution's input matrix (stride 2, width 5, pad 2): row (b, o) is 5 C consecutive
+// values of X [.][L][C] from position 2 o - 2 on, zero outside the positions 0 .. L - 1, so it is
+// read in place; idx (optional) maps b to X's instance.  lo, hi: the columns inside.
+struct ConvRows {
+  const int *idx;
+  int L, C, log2Lo;
+  __device__ __forceinline__ long line(int r, int &lo, int &hi) const {
+    const int o = r & ((1 << log2Lo) - 1), b = r >> log2Lo, p0 = 2 * o - 2;
+    lo = p0 < 0 ? -p0 * C : 0;
+    hi = min(5, L - p0) * C;
+    return ((long)(idx ? idx[b] : b) * L + p0) * C;
+  }
+};
+
+// One operand's tile of ROWS rows (rows of A, columns of B) x 64 k, this thread's elements as read.
+// KC: v[i] = four consecutive k of row row + i; else v[e] = rows row .. + 3 at k + e.  CONV: the
+// lines (rows if KC, else k) are a convolution's input rows instead of s apart.
+template <typename T, bool KC, int ROWS, bool CONV>
+struct TileLoad {
+  typedef T t4 __attribute__((ext_vector_type(4)));
+  static constexpr int NR = ROWS / 16;
+  t4 v[NR];
+  int row, k;
+
+  __device__ __forceinline__ void init() {
+    const int t = threadIdx.x;
+    if (KC) {
+      k = 4 * (t & 15);
+      row = NR * (t >> 4);
+    } else {
+      row = 4 * (t & (ROWS / 4 - 1));
+      k = t / (ROWS / 4) * NR;
+    }
+  }
+  static __device__ __forceinline__ unsigned short cvt(float x) { return f2bf(x); }
+  static __device__ __forceinline__ unsigned short cvt(unsigned short x) { return x; }
+
+  // s: stride of the direction that is not contiguous; rows r0 .. < rmax, k0 .. < kend; vec: four
+  // contiguous elements may be loaded together (base and strides are multiples of four elements)
+  __device__ __forceinline__ void load(const T *__restrict__ p, long s, const ConvRows &cv, int r0, int rmax, int k0,
+                                       int kend, bool vec) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int r = r0 + row + (KC ? i : 0), kk = k0 + k + (KC ? 0 : i);
+      const bool in = r < rmax && kk < kend;
+      const int at = KC ? kk : r, ln = KC ? r : kk;  // position in the line, and the line
+      int lo = 0, hi = KC ? kend : rmax;
+      long base = (long)ln * s;
+      if (CONV && in) {
+        base = cv.line(ln, lo, hi);
+        hi = min(hi, KC ? kend : rmax);
+      }
+      const T *q = p + base + at;
+      t4 x = {0, 0, 0, 0};
+      if (in && vec && at >= lo && at + 4 <= hi) {
+        x = *(const t4 *)q;
+      } else if (in) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (at + e >= lo && at + e < hi) x[e] = q[e];
+      }
+      v[i] = x;
+    }
+  }
+  __device__ __forceinline__ void store(unsigned short *tile) const {  // [ROWS][GKLD], k contiguous
+    if constexpr (KC) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const us4 o = {cvt(v[i][0]), cvt(v[i][1]), cvt(v[i][2]), cvt(v[i][3])};
+        *(us4 *)(tile + (row + i) * GKLD + k) = o;
+      }
+    } else if constexpr (NR == 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const us4 o = {cvt(v[0][i]), cvt(v[1][i]), cvt(v[2][i]), cvt(v[3][i])};
+        *(us4 *)(tile + (row + i) * GKLD + k) = o;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tile[(row + i) * GKLD + k] = cvt(v[0][i]);
+    }
+  }
+};
+
+// db[j] = sum_i dY[i][j], i in order, for 16 columns: the whole workgroup brings the rows to LDS 256
+// at a time, two stages ahead, and 16 threads add them, a chain of dependent adds.  (A thread per
+// column that loaded for itself took 220 ns a row, 1.9 ms for 8192 rows.)
+static constexpr int CS_ROWS = 256, CS_COLS = 16, CS_LD = CS_ROWS + 4;
+__device__ __forceinline__ void colsum_block(const float *__restrict__ dY, int rows, int cols, int c0,
+                                             float *__restrict__ db, float *lds /* 2 CS_COLS CS_LD */) {
+  const int t = threadIdx.x, lc = t & 15, lr = t >> 4, c = c0 + lc;
+  float x[2][16], acc = 0.0f;
+  auto load = [&](float *y, int r0) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = r0 + lr + 16 * i;
+      y[i] = (r < rows && c < cols) ? dY[(size_t)r * cols + c] : 0.0f;
+    }
+  };
+  auto stage = [&](float *y, int r0, float *buf) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) buf[lc * CS_LD + lr + 16 * i] = y[i];
+    __syncthreads();
+    if (r0 + 2 * CS_ROWS < rows) load(y, r0 + 2 * CS_ROWS);
+    if (t < 16) {
+      const int n = min(CS_ROWS, rows - r0);
+      const float *col = buf + t * CS_LD;
+      if (n == CS_ROWS) {
+#pragma unroll 2
+        for (int i = 0; i < CS_ROWS; i += 32) {
+          float4 q[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) q[e] = *(const float4 *)(col + i + 4 * e);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            acc += q[e].x;
+            acc += q[e].y;
+            acc += q[e].z;
+            acc += q[e].w;
+          }
+        }
+      } else {
+        for (int i = 0; i < n; ++i) acc += col[i];
+      }
+    }
+  };
+  load(x[0], 0);
+  load(x[1], CS_ROWS);
+  for (int r0 = 0; r0 < rows; r0 += 2 * CS_ROWS) {
+    stage(x[0], r0, lds);
+    if (r0 + CS_ROWS < rows) stage(x[1], r0 + CS_ROWS, lds + CS_COLS * CS_LD);
+  }
+  if (t < 16 && c < cols) db[c] = acc;
 }
 
 // Split-K: blockIdx.z handles k in [z*kc, (z+1)*kc); with gridDim.z > 1 the raw products go
 // to ws[z][M][N] and k_splitk_reduce applies the epilogue after summing z in order.
-template <typename TA, typename TB>
-__global__ __launch_bounds__(256) void k_gemm(const TA *__restrict__ A, long sa0, long sa1,
-                                              const TB *__restrict__ B, long sb0, long sb1,
+// Workgroups with blockIdx.x >= gx sum columns of B instead (a bias gradient beside its weight
+// gradient: B is dY [K][N], db [N]); only those of blockIdx.y = blockIdx.z = 0 have work.
+template <typename TA, typename TB, bool AK, bool BK, int TN, bool CONV>
+__global__ __launch_bounds__(256) void k_gemm(const TA *__restrict__ A, long sa, ConvRows cv, const TB *__restrict__ B, long sb,
                                               float *__restrict__ Cm, int M, int N, int K,
-                                              const float *__restrict__ bias, int relu, int beta,
-                                              int kc, float *__restrict__ ws) {
-  __shared__ unsigned short As[64][17];
-  __shared__ unsigned short Bs[16][65];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  const int kbeg = blockIdx.z * kc, kend = min(K, kbeg + kc);
-  v4f acc[2][2];
-  for (int r = 0; r < 2; ++r)
-    for (int c = 0; c < 2; ++c)
-      for (int v = 0; v < 4; ++v) acc[r][c][v] = 0.0f;
-  for (int k0 = kbeg; k0 < kend; k0 += 16) {
-    for (int e = tid; e < 64 * 16; e += 256) {
-      const int ii = e >> 4, kk = e & 15;
-      const int gi = i0 + ii, gk = k0 + kk;
-      float a = 0.0f;
-      if (gi < M && gk < kend) a = ldf<TA>(A, (size_t)gi * sa0 + (size_t)gk * sa1);
-      As[ii][kk] = f2bf(a);
-      const int jj = e & 63, kb = e >> 6;
-      const int gj = j0 + jj, gkb = k0 + kb;
-      float b = 0.0f;
-      if (gj < N && gkb < kend) b = ldf<TB>(B, (size_t)gkb * sb0 + (size_t)gj * sb1);
-      Bs[kb][jj] = f2bf(b);
+                                              const float *__restrict__ bias, int relu,
+                                              const float *__restrict__ mask, int beta, int kc, int vec,
+                                              float *__restrict__ ws, int gx, float *__restrict__ db) {
+  constexpr int NC = TN == 64 ? 2 : 1;
+  constexpr int TILE = (64 + TN) * GKLD, SUMS = sizeof(TB) == 4 ? 4 * CS_COLS * CS_LD : 0;
+  __shared__ __align__(16) unsigned short lds[2 * TILE > SUMS ? 2 * TILE : SUMS];
+  if ((int)blockIdx.x >= gx) {
+    if constexpr (sizeof(TB) == 4) {
+      if (blockIdx.y == 0 && blockIdx.z == 0)
+        colsum_block((const float *)B, K, N, ((int)blockIdx.x - gx) * CS_COLS, db, (float *)lds);
     }
-    __syncthreads();
-    const int li = lane & 15, lk = (lane >> 4) * 4;
-    v4s a[2], b[2];
-    for (int r = 0; r < 2; ++r)
-      for (int e = 0; e < 4; ++e) a[r][e] = (short)As[wr + r * 16 + li][lk + e];
-    for (int c = 0; c < 2; ++c)
-      for (int e = 0; e < 4; ++e) b[c][e] = (short)Bs[lk + e][wc + c * 16 + li];
-    for (int r = 0; r < 2; ++r)
-      for (int c = 0; c < 2; ++c)
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[r], b[c], acc[r][c], 0, 0, 0);
-    __syncthreads();
+    return;
   }
-  const int li = lane & 15, lg = lane >> 4;
-  for (int r = 0; r < 2; ++r)
-    for (int c = 0; c < 2; ++c)
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * TN;
+  const int wr = TN == 64 ? (wave >> 1) * 32 : wave * 16, wc = TN == 64 ? (wave & 1) * 32 : 0;
+  const int kbeg = blockIdx.z * kc, kend = min(K, kbeg + kc);
+  const int li = lane & 15, lk = (lane >> 4) * 4;
+  v4f acc[NC][NC];
+#pragma unroll
+  for (int r = 0; r < NC; ++r)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[r][c][v] = 0.0f;
+  TileLoad<TA, AK, 64, CONV> la[2];
+  TileLoad<TB, BK, TN, false> lb[2];
+  auto fetch = [&](int h, int k0) {
+    la[h].load(A, sa, cv, i0, M, k0, kend, vec & 1);
+    lb[h].load(B, sb, cv, j0, N, k0, kend, vec & 2);
+  };
+  auto step = [&](int h, int k0) {  // the stage of register set h, which then loads two stages ahead
+    unsigned short *As = lds + h * TILE, *Bs = As + 64 * GKLD;
+    la[h].store(As);
+    lb[h].store(Bs);
+    __syncthreads();
+    if (k0 + 128 < kend) fetch(h, k0 + 128);
+#pragma unroll
+    for (int ks = 0; ks < 64; ks += 16) {
+      if (k0 + ks >= kend) break;
+      v4s a[NC], b[NC];
+#pragma unroll
+      for (int r = 0; r < NC; ++r) a[r] = *(const v4s *)(As + (wr + r * 16 + li) * GKLD + ks + lk);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) b[c] = *(const v4s *)(Bs + (wc + c * 16 + li) * GKLD + ks + lk);
+#pragma unroll
+      for (int r = 0; r < NC; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[r], b[c], acc[r][c], 0, 0, 0);
+    }
+  };
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    la[h].init();
+    lb[h].init();
+    if (kbeg + 64 * h < kend) fetch(h, kbeg + 64 * h);
+  }
+  for (int k0 = kbeg; k0 < kend; k0 += 128) {
+    step(0, k0);
+    if (k0 + 64 < kend) step(1, k0 + 64);
+  }
+  const int lg = lane >> 4;
+#pragma unroll
+  for (int r = 0; r < NC; ++r)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int gi = i0 + wr + r * 16 + 4 * lg + v, gj = j0 + wc + c * 16 + li;
         if (gi >= M || gj >= N) continue;
@@ -107,6 +274,7 @@ __global__ __launch_bounds__(256) void k_gemm(const TA *__restrict__ A, long sa0
         }
         if (bias) x += bias[gj];
         if (relu) x = x > 0.0f ? x : 0.0f;
+        if (mask && !(mask[(size_t)gi * N + gj] > 0.0f)) x = 0.0f;
         float *dst = Cm + (size_t)gi * N + gj;
         *dst = beta ? *dst + x : x;
       }
@@ -114,41 +282,24 @@ __global__ __launch_bounds__(256) void k_gemm(const TA *__restrict__ A, long sa0
 
 __global__ void k_splitk_reduce(const float *__restrict__ ws, int splits, int M, int N,
                                 float *__restrict__ Cm, const float *__restrict__ bias, int relu,
-                                int beta) {
+                                const float *__restrict__ mask, int beta) {
   const size_t total = (size_t)M * N;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (size_t)gridDim.x * blockDim.x) {
     float x = 0.0f;
+#pragma unroll 8
     for (int z = 0; z < splits; ++z) x += ws[(size_t)z * total + e];
     if (bias) x += bias[e % N];
     if (relu) x = x > 0.0f ? x : 0.0f;
+    if (mask && !(mask[e] > 0.0f)) x = 0.0f;
     Cm[e] = beta ? Cm[e] + x : x;
   }
 }
 
-// im2col for a stride-2, width-5, pad-2 convolution over positions:
-// cols[b*Lo + o][t*C + c] = X[b][2o + t - 2][c] (0 outside), X given as [B][L][C] with an
-// optional row index map (rows of X taken from idx[b]).
-__global__ void k_im2col(const float *__restrict__ X, const int *__restrict__ idx, int B, int L,
-                         int C, int Lo, float *__restrict__ cols) {
-  const size_t total = (size_t)B * Lo * 5 * C;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e % C);
-    const size_t r = e / C;
-    const int t = (int)(r % 5);
-    const size_t ro = r / 5;
-    const int o = (int)(ro % Lo), b = (int)(ro / Lo);
-    const int src = 2 * o + t - 2;
-    const int bb = idx ? idx[b] : b;
-    cols[e] = (src >= 0 && src < L) ? X[((size_t)bb * L + src) * C + c] : 0.0f;
-  }
-}
-
 // col2im (gather form): dX[b][i][c] = sum over taps t with (i + 2 - t) = 2o, 0 <= o < Lo, of
-// dcols[b*Lo + o][t*C + c].
+// dcols[b*Lo + o][t*C + c], and zero where the layer below's ReLU output Y is not positive.
 __global__ void k_col2im(const float *__restrict__ dcols, int B, int L, int C, int Lo,
-                         float *__restrict__ dX) {
+                         const float *__restrict__ Y, float *__restrict__ dX) {
   const size_t total = (size_t)B * L * C;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (size_t)gridDim.x * blockDim.x) {
@@ -163,57 +314,74 @@ __global__ void k_col2im(const float *__restrict__ dcols, int B, int L, int C, i
       if (o >= Lo) continue;
       acc += dcols[((size_t)b * Lo + o) * 5 * C + (size_t)t * C + c];
     }
-    dX[e] = acc;
+    dX[e] = Y[e] > 0.0f ? acc : 0.0f;
   }
-}
-
-// dpre = dY * (Y > 0)
-__global__ void k_relu_bwd(const float *__restrict__ Y, float *__restrict__ dY, size_t n) {
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
-    if (!(Y[e] > 0.0f)) dY[e] = 0.0f;
-}
-
-// db[j] = sum_i dY[i][j]  (fixed order)
-__global__ void k_colsum(const float *__restrict__ dY, int rows, int cols, float *__restrict__ db) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= cols) return;
-  float acc = 0.0f;
-  for (int i = 0; i < rows; ++i) acc += dY[(size_t)i * cols + j];
-  db[j] = acc;
 }
 
 // Relative MSE: loss_b = ||U_b - T_b/r_b||^2 / ||T_b/r_b||^2; dU = 2 (U - T/r) / (||T/r||^2 B).
-// One workgroup per instance (rows of T taken through idx).  part[b] = loss_b.
-__global__ __launch_bounds__(256) void k_loss(const float *__restrict__ U, const double *__restrict__ T,
+// One workgroup of 1024 per instance (rows of T taken through idx).  part[b] = loss_b.  The sums are
+// those of 256 threads striding over the instance, each adding its elements in order: four
+// quarters of the workgroup load 32 elements a thread of each such chain at once and run their
+// parts of it one after the other (48 us to 20 at 64 x 32640: the loads were the chain).
+static constexpr int LS_NT = 1024, LS_E = 32;
+__global__ __launch_bounds__(LS_NT) void k_loss(const float *__restrict__ U, const double *__restrict__ T,
                                               const float *__restrict__ rms, const int *__restrict__ idx,
                                               int n, int B, float *__restrict__ dU,
                                               float *__restrict__ part) {
-  __shared__ float red[2][4];
-  const int b = blockIdx.x;
+  __shared__ float red[2][4], chain[2][256];
+  const int b = blockIdx.x, t = threadIdx.x & 255, g = threadIdx.x >> 8;
   const int bb = idx ? idx[b] : b;
   const float inv = 1.0f / rms[bb];
   const float *u = U + (size_t)b * n;
-  const double *t = T + (size_t)bb * n;
+  const double *tt = T + (size_t)bb * n;
   float se = 0.0f, st = 0.0f;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const float tv = (float)t[i] * inv, d = u[i] - tv;
-    se += d * d;
-    st += tv * tv;
+  for (int base = 0; base < n; base += 4 * LS_E * 256) {
+    float uv[LS_E], dv[LS_E];
+    const int i0 = base + g * LS_E * 256 + t;
+#pragma unroll
+    for (int e = 0; e < LS_E; ++e) {
+      const int i = min(i0 + 256 * e, n - 1);  // loads without branches; what is past n is not added
+      uv[e] = u[i];
+      dv[e] = (float)tt[i];
+    }
+    for (int h = 0; h < 4; ++h) {
+      if (g == h) {
+        if (h > 0 || base > 0) {
+          se = chain[0][t];
+          st = chain[1][t];
+        }
+#pragma unroll
+        for (int e = 0; e < LS_E; ++e)
+          if (i0 + 256 * e < n) {
+            const float tv = dv[e] * inv, d = fmaf(-dv[e], inv, uv[e]);
+            se = fmaf(d, d, se);
+            st = fmaf(tv, tv, st);
+          }
+        chain[0][t] = se;
+        chain[1][t] = st;
+      }
+      __syncthreads();
+    }
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    se += __shfl_xor(se, o, 64);
-    st += __shfl_xor(st, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = se;
-    red[1][threadIdx.x >> 6] = st;
+  if (threadIdx.x < 256) {
+    se = chain[0][t];
+    st = chain[1][t];
+    for (int o = 32; o > 0; o >>= 1) {
+      se += __shfl_xor(se, o, 64);
+      st += __shfl_xor(st, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[0][threadIdx.x >> 6] = se;
+      red[1][threadIdx.x >> 6] = st;
+    }
   }
   __syncthreads();
   se = red[0][0] + red[0][1] + red[0][2] + red[0][3];
   st = red[1][0] + red[1][1] + red[1][2] + red[1][3];
   const float sc = 2.0f / (fmaxf(st, 1e-30f) * (float)B);
   if (dU)
-    for (int i = threadIdx.x; i < n; i += 256) dU[(size_t)b * n + i] = sc * (u[i] - (float)t[i] * inv);
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n; i += LS_NT) dU[(size_t)b * n + i] = sc * fmaf(-(float)tt[i], inv, u[i]);
   if (threadIdx.x == 0) part[b] = se / fmaxf(st, 1e-30f);
 }
 
@@ -326,7 +494,6 @@ struct fde_nn {
   unsigned short *pb = nullptr, *bsyn_b = nullptr;
   int maxB = 0;
   std::vector<float *> act;   // act[0] = X rows [B][256][Cin]; act[l+1] = layer l output
-  std::vector<float *> cols;  // im2col buffers of conv layers
   float *coef = nullptr, *U = nullptr, *dU = nullptr, *dcoef = nullptr, *dA = nullptr,
         *dB = nullptr, *dcols = nullptr, *part = nullptr, *rms = nullptr;
   float *X = nullptr;  // features of the last fde_nn_features call
@@ -366,10 +533,19 @@ static void nn_free(fde_nn *n) {
 // Split-K workspace shared by all GEMMs of one network (stream-ordered use).
 static constexpr size_t NN_WS_FLOATS = (size_t)16 << 20;
 
-template <typename TA, typename TB>
-static hipError_t gemm(hipStream_t st, float *ws, const TA *A, long sa0, long sa1, const TB *B,
-                       long sb0, long sb1, float *Cm, int M, int N, int K, const float *bias,
-                       int relu, int beta) {
+// Whether an operand's four-element vector loads are aligned: its base, and the stride of its other
+// direction.
+template <typename T>
+static bool vec_ok(const T *p, long s) {
+  return ((size_t)p % (4 * sizeof(T))) == 0 && s % 4 == 0;
+}
+
+// db (optional, TB = float and op(B) = dY [K][N] row-major): the column sums of B, in the same launch.
+// CONV: A's lines are the convolution input rows cv (sa is not used).
+template <typename TA, typename TB, bool AK, bool BK, bool CONV = false>
+static hipError_t gemm(hipStream_t st, float *ws, const TA *A, long sa, const TB *B, long sb, float *Cm, int M,
+                       int N, int K, const float *bias, int relu, const float *mask, int beta,
+                       float *db = nullptr, ConvRows cv = ConvRows{nullptr, 0, 0, 0}) {
   const int tiles = ((N + 63) / 64) * ((M + 63) / 64);
   int splits = 1;
   // fill the chip when the output has few tiles and K is long (>= 512 per split)
@@ -378,12 +554,19 @@ static hipError_t gemm(hipStream_t st, float *ws, const TA *A, long sa0, long sa
     splits *= 2;
   const int kc = ((K + splits - 1) / splits + 15) / 16 * 16;
   splits = (K + kc - 1) / kc;
-  dim3 grid((N + 63) / 64, (M + 63) / 64, splits);
-  hipLaunchKernelGGL((k_gemm<TA, TB>), grid, dim3(256), 0, st, A, sa0, sa1, B, sb0, sb1, Cm, M, N, K,
-                     bias, relu, beta, kc, ws);
+  const int vec = (vec_ok(A, CONV ? cv.C : sa) ? 1 : 0) | (vec_ok(B, sb) ? 2 : 0);
+  const bool wide = (long)tiles * splits >= 256;
+  const int tn = wide ? 64 : 16, gx = (N + tn - 1) / tn, cs = db ? (N + CS_COLS - 1) / CS_COLS : 0;
+  dim3 grid(gx + cs, (M + 63) / 64, splits);
+  if (wide)
+    hipLaunchKernelGGL((k_gemm<TA, TB, AK, BK, 64, CONV>), grid, dim3(256), 0, st, A, sa, cv, B, sb, Cm, M, N, K, bias, relu,
+                       mask, beta, kc, vec, ws, gx, db);
+  else
+    hipLaunchKernelGGL((k_gemm<TA, TB, AK, BK, 16, CONV>), grid, dim3(256), 0, st, A, sa, cv, B, sb, Cm, M, N, K, bias, relu,
+                       mask, beta, kc, vec, ws, gx, db);
   if (splits > 1) {
     hipLaunchKernelGGL(k_splitk_reduce, dim3(grid1((size_t)M * N)), dim3(256), 0, st, ws, splits, M,
-                       N, Cm, bias, relu, beta);
+                       N, Cm, bias, relu, mask, beta);
   }
   return hipGetLastError();
 }
@@ -440,17 +623,13 @@ extern "C" fde_status fde_nn_create(const fde_nn_config *c, fde_nn **out) {
   NA(n->bsyn, (size_t)n->nc * n->nout);
   NA(n->bsyn_b, (size_t)n->nc * n->nout);
   n->act.assign(7, nullptr);
-  n->cols.assign(3, nullptr);
   NA(n->act[0], (size_t)B * 256 * n->cin);
   NA(n->X, (size_t)B * 256 * n->cin);
   size_t maxcols = 0;
   for (int l = 0; l < 6; ++l) {
     const Layer &L = n->layers[l];
     NA(n->act[l + 1], (size_t)B * L.lout * L.kout);
-    if (L.conv) {
-      NA(n->cols[l], (size_t)B * L.lout * L.kin);
-      maxcols = std::max(maxcols, (size_t)B * L.lout * L.kin);
-    }
+    if (L.conv) maxcols = std::max(maxcols, (size_t)B * L.lout * L.kin);
   }
   size_t maxact = (size_t)B * 256 * n->cin;
   for (int l = 0; l < 6; ++l) maxact = std::max(maxact, (size_t)B * n->layers[l].lout * n->layers[l].kout);
@@ -579,6 +758,12 @@ extern "C" fde_status fde_nn_features(fde_nn *n, int B, const double *const *f, 
   return FDE_OK;
 }
 
+static ConvRows conv_rows(const Layer &L, const int *rows) {
+  int lg = 0;
+  while ((1 << lg) < L.lout) ++lg;
+  return ConvRows{rows, L.lin, L.cin, lg};
+}
+
 // forward over rows idx[0..B) of X (device features [*][256][Cin]); result in n->U, n->coef
 static fde_status nn_forward(fde_nn *n, const float *X, const int *idx, int B) {
   hipStream_t st = n->stream;
@@ -590,66 +775,57 @@ static fde_status nn_forward(fde_nn *n, const float *X, const int *idx, int B) {
     const float *bias = n->p + L.b_off;
     const unsigned short *W = n->pb + L.w_off;
     if (L.conv) {
-      const size_t tot = (size_t)B * L.lout * L.kin;
-      hipLaunchKernelGGL(k_im2col, dim3(grid1(tot)), dim3(256), 0, st, in, rows, B, L.lin, L.cin,
-                         L.lout, n->cols[l]);
-      NNCHK(hipGetLastError());
-      NNCHK(gemm<float, unsigned short>(st, n->ws, n->cols[l], L.kin, 1, W, L.kout, 1, outp, B * L.lout,
-                                        L.kout, L.kin, bias, L.relu ? 1 : 0, 0));
+      NNCHK(gemm<float, unsigned short, true, false, true>(st, n->ws, in, 0, W, L.kout, outp, B * L.lout, L.kout, L.kin,
+                                                           bias, L.relu ? 1 : 0, nullptr, 0, nullptr, conv_rows(L, rows)));
     } else {
-      NNCHK(gemm<float, unsigned short>(st, n->ws, in, L.kin, 1, W, L.kout, 1, outp, B, L.kout, L.kin, bias,
-                                        L.relu ? 1 : 0, 0));
+      NNCHK(gemm<float, unsigned short, true, false>(st, n->ws, in, L.kin, W, L.kout, outp, B, L.kout, L.kin, bias,
+                                                     L.relu ? 1 : 0, nullptr, 0));
     }
     in = outp;
     rows = nullptr;
   }
   // synthesis U = coef Bsyn
-  NNCHK(gemm<float, unsigned short>(st, n->ws, n->coef, n->nc, 1, n->bsyn_b, n->nout, 1, n->U, B, n->nout,
-                                    n->nc, nullptr, 0, 0));
+  NNCHK(gemm<float, unsigned short, true, false>(st, n->ws, n->coef, n->nc, n->bsyn_b, n->nout, n->U, B, n->nout,
+                                                 n->nc, nullptr, 0, nullptr, 0));
   return FDE_OK;
 }
 
 static fde_status nn_backward(fde_nn *n, const float *X, const int *idx, int B) {
   hipStream_t st = n->stream;
-  NNCHK(hipMemsetAsync(n->g, 0, n->nparam * sizeof(float), st));
-  // dcoef = dU Bsyn^T
+  // dcoef = dU Bsyn^T.  Every gradient of the parameter vector is written below; a layer's dY
+  // already carries its ReLU's zeros (the mask of the product or gather that forms it).
   float *dY = n->dA, *dX = n->dB;
-  NNCHK(gemm<float, unsigned short>(st, n->ws, n->dU, n->nout, 1, n->bsyn_b, 1, n->nout, dY, B, n->nc,
-                                    n->nout, nullptr, 0, 0));
+  NNCHK(gemm<float, unsigned short, true, true>(st, n->ws, n->dU, n->nout, n->bsyn_b, n->nout, dY, B, n->nc,
+                                                n->nout, nullptr, 0, nullptr, 0));
   for (int l = 5; l >= 0; --l) {
     const Layer &L = n->layers[l];
-    const float *Y = n->act[l + 1];
     const int rowsN = L.conv ? B * L.lout : B;
-    if (L.relu) {
-      hipLaunchKernelGGL(k_relu_bwd, dim3(grid1((size_t)rowsN * L.kout)), dim3(256), 0, st, Y, dY,
-                         (size_t)rowsN * L.kout);
-      NNCHK(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_colsum, dim3((L.kout + 255) / 256), dim3(256), 0, st, dY, rowsN, L.kout,
-                       n->g + L.b_off);
-    NNCHK(hipGetLastError());
-    // dW = in^T dY   (in = cols for conv, previous activation for fc)
-    const float *in = L.conv ? n->cols[l] : n->act[l];
-    NNCHK(gemm<float, float>(st, n->ws, in, 1, L.kin, dY, L.kout, 1, n->g + L.w_off, L.kin, L.kout, rowsN,
-                             nullptr, 0, 0));
+    // dW = in^T dY (in: the convolution's input rows, or the previous activation), db = column sums
+    const float *in = l == 0 ? X : n->act[l];
+    if (L.conv)
+      NNCHK(gemm<float, float, false, false, true>(st, n->ws, in, 0, dY, L.kout, n->g + L.w_off, L.kin, L.kout, rowsN,
+                                                   nullptr, 0, nullptr, 0, n->g + L.b_off,
+                                                   conv_rows(L, l == 0 ? idx : nullptr)));
+    else
+      NNCHK(gemm<float, float, false, false>(st, n->ws, in, L.kin, dY, L.kout, n->g + L.w_off, L.kin, L.kout, rowsN,
+                                             nullptr, 0, nullptr, 0, n->g + L.b_off));
     if (l == 0) break;
-    // d(in) = dY W^T
+    // d(in) = dY W^T, zeroed by the ReLU of the layer below (every layer below the last has one)
     const unsigned short *W = n->pb + L.w_off;
+    const float *mask = n->act[l];
     if (L.conv) {
-      NNCHK(gemm<float, unsigned short>(st, n->ws, dY, L.kout, 1, W, 1, L.kout, n->dcols, rowsN, L.kin,
-                                        L.kout, nullptr, 0, 0));
+      NNCHK(gemm<float, unsigned short, true, true>(st, n->ws, dY, L.kout, W, L.kout, n->dcols, rowsN, L.kin,
+                                                    L.kout, nullptr, 0, nullptr, 0));
       const size_t tot = (size_t)B * L.lin * L.cin;
       hipLaunchKernelGGL(k_col2im, dim3(grid1(tot)), dim3(256), 0, st, n->dcols, B, L.lin, L.cin,
-                         L.lout, dX);
+                         L.lout, mask, dX);
       NNCHK(hipGetLastError());
     } else {
-      NNCHK(gemm<float, unsigned short>(st, n->ws, dY, L.kout, 1, W, 1, L.kout, dX, rowsN, L.kin, L.kout,
-                                        nullptr, 0, 0));
+      NNCHK(gemm<float, unsigned short, true, true>(st, n->ws, dY, L.kout, W, L.kout, dX, rowsN, L.kin, L.kout,
+                                                    nullptr, 0, mask, 0));
     }
     std::swap(dY, dX);
   }
-  (void)X;
-  (void)idx;
   return FDE_OK;
 }
 
@@ -672,7 +848,7 @@ extern "C" fde_status fde_nn_loss_grad(fde_nn *n, const float *X, const double *
   if (s0 != FDE_OK) return s0;
   s0 = nn_forward(n, X, didx, B);
   if (s0 != FDE_OK) return s0;
-  hipLaunchKernelGGL(k_loss, dim3(B), dim3(256), 0, n->stream, n->U, T, rms, didx, n->nout, B, n->dU, n->part);
+  hipLaunchKernelGGL(k_loss, dim3(B), dim3(LS_NT), 0, n->stream, n->U, T, rms, didx, n->nout, B, n->dU, n->part);
   NNCHK(hipGetLastError());
   s0 = nn_backward(n, X, didx, B);
   if (s0 != FDE_OK) return s0;
