@@ -58,6 +58,10 @@ struct InstDesc {
   double *H, *y, *nrm;        // Hessenberg column [R+2], LSQ solution [R], norms [2]
   double *h2;                 // [R+2] second Gram-Schmidt pass of the current column
   unsigned *gctr;             // [1] chunks done in the current Gram-Schmidt launch (0 between)
+  // Gram-Schmidt in two launches (k_krylov.hip): chunks (0: the launch chain), their partials
+  // [2 R + 3][nwide] and the strictly lower part of V^T V of the current cycle, [R + 1][R + 1]
+  int nwide, ldgram;
+  double *wpart, *gram;
 };
 
 // Nodes of level `lev` over npan panels: pairs of 1 << lev panels whose right half is not empty.

@@ -30,10 +30,11 @@ __global__ __launch_bounds__(GM_NT) void k_gm_givens(const InstDesc *__restrict_
                                                      GmresCtl *__restrict__ ctl,
                                                      GmresWork *__restrict__ work,
                                                      int *__restrict__ gates, int count, int j,
-                                                     int R) {
+                                                     int R, int wide_done) {
   const int i = blockIdx.x * GM_NT + threadIdx.x;
   if (i >= count) return;
   if (!gates[GATE_ACTIVE * count + i]) return;
+  if (wide_done && D[i].nwide) return;  // done with the orthogonalisation (k_mgs_apply)
   gm_givens_one(D[i], ctl[i], work[i], gates, count, i, j, R);
 }
 
@@ -92,10 +93,10 @@ hipError_t launch_gm_restart(const InstDesc *D, GmresCtl *ctl, GmresWork *work, 
 }
 
 hipError_t launch_gm_givens(const InstDesc *D, GmresCtl *ctl, GmresWork *work, int *gates,
-                            int count, int j, int R, hipStream_t st) {
+                            int count, int j, int R, int wide_done, hipStream_t st) {
   if (count <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_gm_givens, gm_grid(count), dim3(GM_NT), 0, st, D, ctl, work, gates, count,
-                     j, R);
+                     j, R, wide_done);
   return hipGetLastError();
 }
 

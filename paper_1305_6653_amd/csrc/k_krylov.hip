@@ -20,6 +20,8 @@
 #include "gmres_step.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
+
 namespace fde {
 
 static constexpr int KR_NT = 256;
@@ -268,6 +270,234 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_step(const InstDesc *__restrict__
   }
   acc = block_sum<KR_NT>(acc, red);
   if (threadIdx.x == 0) pout[c.b] = acc;
+}
+
+// ---------------------------------------------------------------------------------------
+// Modified Gram-Schmidt in two passes over the basis, for vectors of more than WD_MIN entries.  MGS
+// takes h_i = v_i . (w - sum_{k<i} h_k v_k), one reduction after the other; the same numbers are
+// the solution of the triangular system
+//   h_i = v_i . w - sum_{k<i} (v_i . v_k) h_k,
+// so the dots with w and the dots of the newest v_j with the older vectors (the other v_i . v_k
+// are kept from earlier steps) are taken in one pass, and w -= V h in a second.  No orthogonality
+// of V is assumed, so the loss of orthogonality is corrected as MGS corrects it.  Launches per
+// step: 3 (with v_{j+1}) instead of j + 4, and every basis vector is read twice instead of w, v_i
+// and v_{i-1} being read and w written per projection: 255 x 128 (19 steps) 1.34 ms of j + 2
+// launches of 6.4 us, and 4095 x 256 1.66 ms.  Below WD_MIN the chain is as fast.
+static constexpr size_t WD_MIN = 7 * 1024;
+static constexpr int WD_G = 16;  // basis vectors per pass
+
+int wide_chunks(size_t n) {
+  if (n <= WD_MIN) return 0;
+  return (int)std::min<size_t>((n + 511) / 512, 256);
+}
+
+struct WideChunk {  // pairs [begin, end) of chunk b (n is even: s is a power of two above 1)
+  const InstDesc *d;
+  int b;
+  size_t begin, end, n2;
+};
+__device__ __forceinline__ WideChunk wide_chunk(const InstDesc *__restrict__ D, const ItemMap &map) {
+  const int q = item_slot(map, blockIdx.x);
+  WideChunk c;
+  c.d = nullptr;
+  if (item_gated(map, q)) return c;
+  c.d = &D[map.ids[q]];
+  c.b = blockIdx.x - map.pre[q];
+  c.n2 = (size_t)c.d->s * c.d->m / 2;
+  const size_t len = (c.n2 + c.d->nwide - 1) / c.d->nwide;
+  c.begin = min((size_t)c.b * len, c.n2);
+  c.end = min(c.begin + len, c.n2);
+  return c;
+}
+
+// true in every thread of the chunk that finishes last; its loads of the others' partials see them
+__device__ __forceinline__ bool wide_last(const InstDesc &d, int *sh) {
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned done = __hip_atomic_fetch_add(d.gctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int last = done == (unsigned)d.nwide - 1;
+    if (last) __hip_atomic_store(d.gctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *sh = last;
+  }
+  __syncthreads();
+  return *sh != 0;
+}
+
+// Sum of the nw partials of one value by a row of 16 lanes (fixed order: stride-16 runs, then
+// the row's butterfly); result in every lane of the row.
+__device__ __forceinline__ double wide_sum16(const double *p, int nw) {
+  double t = 0.0;
+#pragma unroll 16
+  for (int b = threadIdx.x & 15; b < nw; b += 16) t += ld_coh1(p + b);
+  t += dpp_f64<0xB1>(t);
+  t += dpp_f64<0x4E>(t);
+  t += dpp_f64<0x141>(t);
+  t += dpp_f64<0x140>(t);
+  return t;
+}
+
+__global__ __launch_bounds__(KR_NT) void k_mgs_dots(const InstDesc *__restrict__ D, ItemMap map, int j) {
+  __shared__ double red[KR_NT / 64][2 * WD_G], hs[GM_RMAX + 1], ls[GM_RMAX + 1];
+  __shared__ double gl[GM_RMAX][GM_RMAX + 1];
+  __shared__ int sh;
+  const WideChunk c = wide_chunk(D, map);
+  if (!c.d) return;
+  const InstDesc &d = *c.d;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = d.nwide;
+  const double2 *w = (const double2 *)d.w, *V = (const double2 *)d.V, *vj = V + (size_t)j * c.n2;
+  double *pa = d.wpart, *pl = d.wpart + (size_t)(j + 1) * nw;
+  for (int i0 = 0; i0 <= j; i0 += WD_G) {
+    const int ng = min(j + 1 - i0, WD_G);
+    double acc[2 * WD_G];  // v_i . w, then v_i . v_j
+#pragma unroll
+    for (int t = 0; t < 2 * WD_G; ++t) acc[t] = 0.0;
+    for (size_t e = c.begin + threadIdx.x; e < c.end; e += KR_NT) {
+      const double2 we = w[e], ve = vj[e];
+      double2 x[WD_G];
+#pragma unroll
+      for (int t = 0; t < WD_G; ++t)
+        if (t < ng) x[t] = V[(size_t)(i0 + t) * c.n2 + e];
+#pragma unroll
+      for (int t = 0; t < WD_G; ++t)
+        if (t < ng) {
+          acc[t] = fma(x[t].y, we.y, fma(x[t].x, we.x, acc[t]));
+          acc[WD_G + t] = fma(x[t].y, ve.y, fma(x[t].x, ve.x, acc[WD_G + t]));
+        }
+    }
+    // 32 sums over 64 lanes by halving: a lane keeps half of its values and adds its partner's
+    // share of them, until lanes 2 v and 2 v + 1 hold value v
+#pragma unroll
+    for (int cnt = WD_G, off = 32; cnt >= 1; cnt >>= 1, off >>= 1) {
+      const bool hi = (lane & off) != 0;
+#pragma unroll
+      for (int t = 0; t < WD_G; ++t)
+        if (t < cnt) {
+          const double send = hi ? acc[t] : acc[t + cnt], keep = hi ? acc[t + cnt] : acc[t];
+          acc[t] = keep + __shfl_xor(send, off, 64);
+        }
+    }
+    acc[0] += __shfl_xor(acc[0], 1, 64);
+    if ((lane & 1) == 0) red[wv][lane >> 1] = acc[0];
+    __syncthreads();
+    if (threadIdx.x < 2 * WD_G) {
+      const int t = threadIdx.x, i = i0 + (t & (WD_G - 1));
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < KR_NT / 64; ++q) s += red[q][t];
+      if (t < WD_G ? i <= j : i < j) st_coh1((t < WD_G ? pa : pl) + (size_t)i * nw + c.b, s);
+    }
+    __syncthreads();
+  }
+  if (!wide_last(d, &sh)) return;
+  for (int e = threadIdx.x; e < j * j; e += KR_NT) {
+    const int r = e / j, k = e % j;
+    if (k < r) gl[r][k] = d.gram[(size_t)r * d.ldgram + k];
+  }
+  for (int i = threadIdx.x >> 4; i < 2 * j + 1; i += KR_NT / 16) {
+    const double s = wide_sum16(d.wpart + (size_t)i * nw, nw);
+    if ((threadIdx.x & 15) == 0) {
+      if (i <= j) {
+        hs[i] = s;
+      } else {
+        ls[i - j - 1] = s;
+        d.gram[(size_t)j * d.ldgram + i - j - 1] = s;
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {  // forward substitution, lane i = row i
+    double h = lane <= j ? hs[lane] : 0.0;
+    for (int k = 0; k < j; ++k) {
+      const double hk = __shfl(h, k, 64);
+      if (lane > k && lane <= j) h = fma(-(lane == j ? ls[k] : gl[lane][k]), hk, h);
+    }
+    if (lane <= j) d.H[lane] = h;
+  }
+}
+
+// w -= V h (i order for every element), the norm, and in the last chunk the Givens update
+__global__ __launch_bounds__(KR_NT) void k_mgs_apply(const InstDesc *__restrict__ D, ItemMap map, int j,
+                                                     GmresCtl *__restrict__ ctl, GmresWork *__restrict__ work,
+                                                     int *__restrict__ gates, int count, int R) {
+  __shared__ double red[KR_NT / 64], cf[GM_RMAX + 2], csl[GM_RMAX], snl[GM_RMAX];
+  __shared__ int sh;
+  const WideChunk c = wide_chunk(D, map);
+  if (!c.d) return;
+  const InstDesc &d = *c.d;
+  const int nw = d.nwide;
+  if (threadIdx.x <= j) cf[threadIdx.x] = d.H[threadIdx.x];
+  __syncthreads();
+  double2 *w = (double2 *)d.w;
+  const double2 *V = (const double2 *)d.V;
+  double nn = 0.0;
+  for (size_t e = c.begin + threadIdx.x; e < c.end; e += KR_NT) {
+    double2 we = w[e];
+    for (int i0 = 0; i0 <= j; i0 += WD_G) {
+      double2 x[WD_G];
+#pragma unroll
+      for (int t = 0; t < WD_G; ++t)
+        if (i0 + t <= j) x[t] = V[(size_t)(i0 + t) * c.n2 + e];
+#pragma unroll
+      for (int t = 0; t < WD_G; ++t)
+        if (i0 + t <= j) {
+          we.x = fma(-cf[i0 + t], x[t].x, we.x);
+          we.y = fma(-cf[i0 + t], x[t].y, we.y);
+        }
+    }
+    w[e] = we;
+    nn = fma(we.y, we.y, fma(we.x, we.x, nn));
+  }
+  nn = block_sum<KR_NT>(nn, red);
+  if (threadIdx.x == 0) st_coh1(d.wpart + c.b, nn);
+  if (!wide_last(d, &sh)) return;
+  const int inst = map.ids[item_slot(map, blockIdx.x)];
+  for (int r = threadIdx.x; r < j; r += KR_NT) {
+    csl[r] = work[inst].cs[r];
+    snl[r] = work[inst].sn[r];
+  }
+  if (threadIdx.x < 16) {
+    const double nrm = sqrt(wide_sum16(d.wpart, nw));
+    if (threadIdx.x == 0) cf[j + 1] = nrm;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    d.H[j + 1] = cf[j + 1];
+    gm_givens_core(cf, csl, snl, work[inst].g[j], ctl[inst], work[inst], gates, count, inst, j, R);
+  }
+}
+
+// v_{j+1} = w / ||w||
+__global__ __launch_bounds__(KR_NT) void k_mgs_scale(const InstDesc *__restrict__ D, ItemMap map, int j) {
+  const WideChunk c = wide_chunk(D, map);
+  if (!c.d) return;
+  const double nrm = c.d->H[j + 1], inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+  const double2 *w = (const double2 *)c.d->w;
+  double2 *v = (double2 *)c.d->V + (size_t)(j + 1) * c.n2;
+#pragma unroll 4
+  for (size_t e = c.begin + threadIdx.x; e < c.end; e += KR_NT) {
+    const double2 x = w[e];
+    v[e] = make_double2(x.x * inv, x.y * inv);
+  }
+}
+
+hipError_t launch_mgs_dots(const InstDesc *D, const ItemMap &map, int items, int j, hipStream_t st) {
+  if (items <= 0) return hipSuccess;
+  if (j >= GM_RMAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_mgs_dots, dim3(items), dim3(KR_NT), 0, st, D, map, j);
+  return hipGetLastError();
+}
+hipError_t launch_mgs_apply(const InstDesc *D, const ItemMap &map, int items, int j, GmresCtl *ctl,
+                            GmresWork *work, int *gates, int count, int R, hipStream_t st) {
+  if (items <= 0) return hipSuccess;
+  if (j >= GM_RMAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_mgs_apply, dim3(items), dim3(KR_NT), 0, st, D, map, j, ctl, work, gates, count, R);
+  return hipGetLastError();
+}
+hipError_t launch_mgs_scale(const InstDesc *D, const ItemMap &map, int items, int j, hipStream_t st) {
+  if (items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_mgs_scale, dim3(items), dim3(KR_NT), 0, st, D, map, j);
+  return hipGetLastError();
 }
 
 // Arnoldi step j of instances whose vectors are one chunk (nblk = 1): the modified

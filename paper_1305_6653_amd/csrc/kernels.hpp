@@ -105,6 +105,13 @@ hipError_t launch_mgs_step(const InstDesc *D, const ItemMap &map, int items, int
 hipError_t launch_cgs_dot(const InstDesc *D, const ItemMap &map, int items, int j, hipStream_t st);
 hipError_t launch_cgs_update(const InstDesc *D, const ItemMap &map, int items, int j, int pass,
                              hipStream_t st);
+// The same Arnoldi step in three launches for instances with wide_chunks(n) > 0 chunks (items):
+// the dots, w's update with its norm and the Givens update of the control record, and v_{j+1}.
+int wide_chunks(size_t n);
+hipError_t launch_mgs_dots(const InstDesc *D, const ItemMap &map, int items, int j, hipStream_t st);
+hipError_t launch_mgs_apply(const InstDesc *D, const ItemMap &map, int items, int j, GmresCtl *ctl,
+                            GmresWork *work, int *gates, int count, int R, hipStream_t st);
+hipError_t launch_mgs_scale(const InstDesc *D, const ItemMap &map, int items, int j, hipStream_t st);
 hipError_t launch_normalize(const InstDesc *D, const ItemMap &map, int items, int src_sel,
                             int src_j, int dst_sel, int dst_j, int psel, int hidx, hipStream_t st);
 hipError_t launch_residual(const InstDesc *D, const ItemMap &map, int items, hipStream_t st);
@@ -129,9 +136,10 @@ hipError_t launch_gm_init(const InstDesc *D, GmresCtl *ctl, int *gates, int coun
 hipError_t launch_gm_restart(const InstDesc *D, GmresCtl *ctl, GmresWork *work, int *gates,
                              int count, hipStream_t st);
 // Arnoldi step j done: rotate the new Hessenberg column, update the residual estimate and
-// retire instances that converged, ran out of iterations or reached the end of the cycle.
+// retire instances that converged, ran out of iterations or reached the end of the cycle
+// (wide_done: not those whose launch_mgs_apply has done it).
 hipError_t launch_gm_givens(const InstDesc *D, GmresCtl *ctl, GmresWork *work, int *gates,
-                            int count, int j, int R, hipStream_t st);
+                            int count, int j, int R, int wide_done, hipStream_t st);
 // end of cycle: y = H^{-1} g into the descriptors' y (y[0] = k, 0 if the instance did not run)
 hipError_t launch_gm_backsolve(const InstDesc *D, GmresCtl *ctl, GmresWork *work, int count,
                                hipStream_t st);

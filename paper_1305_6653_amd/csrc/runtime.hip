@@ -363,8 +363,10 @@ struct HostMap {
 // Item maps of the solve-phase launches over every instance of a plan.
 struct SolveMaps {
   ItemMap mv, tfft, trsv, kry, rhs, ju0, blk, qg, hsub, hup[HIER_LEVELS];
+  ItemMap kchain, kwide;  // the Gram-Schmidt items: instances in the launch chain, and in two passes
+  int n_kchain = 0, n_kwide = 0;
   int n_hsub = 0, n_hup[HIER_LEVELS] = {};  // hierarchical instances (trsv, blk, qg: the others)
-  double hsub_bytes = 0, hup_bytes[HIER_LEVELS] = {};
+  double wide_bytes = 0, hsub_bytes = 0, hup_bytes[HIER_LEVELS] = {};
   int n_mv = 0, n_tfft = 0, n_trsv = 0, n_kry = 0, n_rhs = 0, n_ju0 = 0, n_blk = 0, n_qg = 0;
   int pc = 0, route = FDE_BLOCKS_LU;
   int max_log2L = 1, max_log2s = 1, max_mp = 64;
@@ -381,6 +383,7 @@ static SolveMaps gated(const SolveMaps &S, const int *gate) {
   SolveMaps G = S;
   for (ItemMap *m : {&G.mv, &G.tfft, &G.trsv, &G.kry, &G.rhs, &G.ju0, &G.blk, &G.qg, &G.hsub}) m->gate = gate;
   for (ItemMap &m : G.hup) m.gate = gate;
+  G.kchain.gate = G.kwide.gate = gate;
   return G;
 }
 
@@ -391,6 +394,8 @@ struct Plan {
   InstDesc *d_desc = nullptr;
   double *d_part = nullptr, *d_H = nullptr, *d_y = nullptr, *d_nrm = nullptr, *d_h2 = nullptr;
   unsigned *d_gctr = nullptr;
+  double *d_wide = nullptr;  // partials and Gram rows of the two-pass Gram-Schmidt
+  std::vector<size_t> wide_off;
   int *d_err = nullptr, *d_flag = nullptr;
   int *d_arena = nullptr;
   size_t arena_ints = 0;
@@ -676,7 +681,7 @@ static fde_status plan_prepare(Plan *P, int R, int prec) {
   for (fde_bvm *h : P->hs) STCHK(ensure_krylov(h, R));
   if (P->R < R || !P->d_H) {
     for (void *p : {(void *)P->d_part, (void *)P->d_H, (void *)P->d_y, (void *)P->d_nrm, (void *)P->d_h2,
-                    (void *)P->d_gctr}) {
+                    (void *)P->d_gctr, (void *)P->d_wide}) {
       if (!p) continue;
       auto it = std::find(P->allocs.begin(), P->allocs.end(), p);
       if (it != P->allocs.end()) P->allocs.erase(it);
@@ -705,6 +710,15 @@ static fde_status plan_prepare(Plan *P, int R, int prec) {
     STCHK(plan_alloc(P, &p, (size_t)count * sizeof(unsigned)));
     P->d_gctr = (unsigned *)p;
     HIPCHK(hipMemset(P->d_gctr, 0, (size_t)count * sizeof(unsigned)));
+    size_t wide = 0;
+    P->wide_off.assign(count, 0);
+    for (int i = 0; i < count; ++i) {
+      P->wide_off[i] = wide;
+      const int nw = wide_chunks(P->hs[i]->n());
+      if (nw) wide += (size_t)(2 * R + 3) * nw + (size_t)(R + 1) * (R + 1);
+    }
+    STCHK(plan_alloc(P, &p, wide * sizeof(double)));
+    P->d_wide = (double *)p;
     P->R = R;
     P->desc_dirty = true;
   }
@@ -722,6 +736,10 @@ static fde_status plan_prepare(Plan *P, int R, int prec) {
     d.partm = d.part0 + 2 * (size_t)h->nblk;
     d.h2 = P->d_h2 + (size_t)i * (R + 2);
     d.gctr = P->d_gctr + i;
+    d.nwide = wide_chunks(h->n());
+    d.ldgram = P->R + 1;
+    d.wpart = P->d_wide + P->wide_off[i];
+    d.gram = d.wpart + (size_t)(2 * P->R + 3) * d.nwide;
     d.H = P->d_H + (size_t)i * (R + 2);
     d.y = P->d_y + (size_t)i * (R + 1);
     d.nrm = P->d_nrm + (size_t)i * 2;
@@ -2047,6 +2065,7 @@ static fde_status ensure_full_maps(Plan *P) {
     S.max_mp = std::max(S.max_mp, h->mp);
     qq[q] = h->hier ? 0 : qgemm_items(h->nb, h->mp);
     S.vec_bytes += 8.0 * h->n();
+    if (wide_chunks(h->n())) S.wide_bytes += 8.0 * h->n();
     S.tfft_bytes += 8.0 * h->n() + 16.0 * h->nb * h->m;
     if (h->hier) continue;
     const double esz = h->prec == FDE_FP64 ? 16.0 : 8.0;
@@ -2062,6 +2081,13 @@ static fde_status ensure_full_maps(Plan *P) {
                              make_map(slots, d), make_map(slots, e), make_map(slots, f),
                              make_map(slots, g), make_map(slots, qq)};
   for (const std::vector<int> &u : hu) hm.push_back(make_map(slots, u));
+  std::vector<int> kc(count), kw(count);
+  for (int q = 0; q < count; ++q) {
+    kw[q] = wide_chunks(P->hs[q]->n());
+    kc[q] = kw[q] ? 0 : P->hs[q]->nblk;
+  }
+  hm.push_back(make_map(slots, kc));
+  hm.push_back(make_map(slots, kw));
   size_t need = 0;
   for (const HostMap &m : hm) need += m.ids.size() + m.pre.size();
   HIPCHK(hipStreamSynchronize(P->lead->stream));
@@ -2106,6 +2132,10 @@ static fde_status ensure_full_maps(Plan *P) {
   }
   S.hsub = dm[8 + HIER_LEVELS];
   S.n_hsub = hm[8 + HIER_LEVELS].items;
+  S.kchain = dm[9 + HIER_LEVELS];
+  S.n_kchain = hm[9 + HIER_LEVELS].items;
+  S.kwide = dm[10 + HIER_LEVELS];
+  S.n_kwide = hm[10 + HIER_LEVELS].items;
   S.pc = P->hs[0]->pc;
   S.route = route;
   S.n_mv = hm[0].items;
@@ -2511,15 +2541,29 @@ static fde_status gmres_plan(Plan *P, const fde_solve_opts &o, const std::vector
         HIPCHK(run(L, "cgs", (j + 3.0) * S.vec_bytes,
                    [&] { return launch_cgs_update(P->d_desc, Sact.kry, S.n_kry, j, 1, stream); }));
       } else {
+        if (S.n_kwide > 0) {
+          HIPCHK(run(L, "mgs", (j + 3.0) * S.wide_bytes,
+                     [&] { return launch_mgs_dots(P->d_desc, Sact.kwide, S.n_kwide, j, stream); }));
+          HIPCHK(run(L, "mgs", (j + 3.0) * S.wide_bytes, [&] {
+            return launch_mgs_apply(P->d_desc, Sact.kwide, S.n_kwide, j, P->d_ctl, P->d_work, P->d_gates, count, R,
+                                    stream);
+          }));
+          HIPCHK(run(L, "normalize", 2.0 * S.wide_bytes,
+                     [&] { return launch_mgs_scale(P->d_desc, Sact.kwide, S.n_kwide, j, stream); }));
+          if (S.n_kchain == 0) continue;
+        }
         for (int i = 0; i <= j + 1; ++i) {
-          HIPCHK(run(L, "mgs", (i == 0 ? 2.0 : 4.0) * S.vec_bytes,
-                     [&] { return launch_mgs_step(P->d_desc, Sact.kry, S.n_kry, i, j, stream); }));
+          HIPCHK(run(L, "mgs", (i == 0 ? 2.0 : 4.0) * (S.vec_bytes - S.wide_bytes),
+                     [&] { return launch_mgs_step(P->d_desc, Sact.kchain, S.n_kchain, i, j, stream); }));
         }
       }
-      HIPCHK(run(L, "normalize", 2.0 * S.vec_bytes, [&] {
-        return launch_normalize(P->d_desc, Sact.kry, S.n_kry, VS_W, 0, VS_V, j + 1, (j + 1) & 1, j + 1, stream);
+      const bool cgs = ortho == FDE_ORTHO_CGS2;
+      const ItemMap &km = cgs ? Sact.kry : Sact.kchain;
+      HIPCHK(run(L, "normalize", 2.0 * (S.vec_bytes - (cgs ? 0.0 : S.wide_bytes)), [&] {
+        return launch_normalize(P->d_desc, km, cgs ? S.n_kry : S.n_kchain, VS_W, 0, VS_V, j + 1, (j + 1) & 1, j + 1,
+                                stream);
       }));
-      HIPCHK(launch_gm_givens(P->d_desc, P->d_ctl, P->d_work, P->d_gates, count, j, R, stream));
+      HIPCHK(launch_gm_givens(P->d_desc, P->d_ctl, P->d_work, P->d_gates, count, j, R, cgs ? 0 : 1, stream));
     }
     g_step = -1;
     return FDE_OK;
