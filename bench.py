@@ -48,7 +48,7 @@ PMC_KERNEL_GROUP = {
     "hess_lsolve": "hessenberg",
     "band_panel": "band", "band_update": "band", "band_init": "band", "band_finish": "band",
     "band_lu_panel": "factor", "band_lu_rows": "factor", "band_lu_step": "factor", "band_lsolve": "factor",
-    "hier_leaf": "hier", "hier_init": "hier", "hier_node": "hier", "hier_cols": "hier", "hier_sub": "hier",
+    "hier_leaf": "hier", "hier_node": "hier", "hier_cols": "hier", "hier_sub": "hier",
     "hier_up": "hier",
 }
 # Per measured workload: the source hashes of every kernel group when its counters were taken,
@@ -136,7 +136,7 @@ def measured_mfma_peak(prec):
 
 FLOP_KERNELS = ("lu_diag", "lu_panel", "lu_update", "hess_lu", "hess_reduce", "hess_uinv",
                 "band_panel", "band_update", "band_lu_panel", "band_lu_rows", "band_lu_step", "qgemm",
-                "hier_leaf", "hier_init", "hier_node", "hier_cols")
+                "hier_leaf", "hier_node", "hier_cols")
 
 
 def kernel_table(prof, steps, prec):
@@ -151,7 +151,7 @@ def kernel_table(prof, steps, prec):
             rate = v["work"] / (v["total_ms"] * 1e-3)
             if k in FLOP_KERNELS:
                 fp32 = k in ("lu_diag", "lu_panel", "lu_update", "band_lu_rows", "band_lu_panel", "band_lu_step",
-                             "hess_lu", "hess_uinv", "hier_leaf", "hier_init", "hier_node", "hier_cols")
+                             "hess_lu", "hess_uinv", "hier_leaf", "hier_node", "hier_cols")
                 peak = PEAK_FP32_TFLOPS if (prec == "mixed" and fp32) else PEAK_FP64_TFLOPS
                 row["TFLOPs"] = round(rate / 1e12, 3)
                 row["frac"] = round(rate / 1e12 / peak, 4)
@@ -310,7 +310,7 @@ def timed_steps(S, u0, f, out, prec, steps, warmup, pc=None):
               "time_irfft", "bvm_matvec", "mgs", "cgs", "arnoldi", "normalize", "residual", "update_x", "rhs", "dot",
               "hess_reduce", "hess_formq", "hess_lu", "hess_uinv", "qgemm", "hess_lsolve",
               "band_init", "band_panel", "band_update", "band_finish", "band_lu_panel", "band_lu_rows",
-              "band_lu_step", "band_lsolve", "hier_leaf", "hier_init", "hier_node", "hier_cols", "hier_sub",
+              "band_lu_step", "band_lsolve", "hier_leaf", "hier_node", "hier_cols", "hier_sub",
               "hier_up"):
         q = S.profile_query(k)
         if q["count"]:
@@ -326,12 +326,12 @@ def roofline(prof, prec, workload_name=None, read_peak=None):
     name, q = max(prof.items(), key=lambda kv: kv[1]["total_ms"])
     avg_ms = q["total_ms"] / q["count"]
     traffic = measured_traffic(workload_name, prec, name)
-    if name.startswith("hess_") or name in ("band_panel", "band_lu_panel", "hier_leaf"):
-        # the Hessenberg reduction, the shifted LUs, the band panels and the leaf inverses: flops on the vector ALUs
-        # in chains of dependent steps (latency-bound), priced against the vector peak of the
-        # precision they run in (the reductions are FP64 in either form)
+    if name.startswith("hess_") or name in ("band_panel", "band_lu_panel"):
+        # the Hessenberg reduction, the shifted LUs and the band panels: flops on the vector ALUs in
+        # chains of dependent steps (latency-bound), priced against the vector peak of the precision
+        # they run in (the reductions are FP64 in either form)
         achieved = q["work"] / (q["total_ms"] * 1e-3) / 1e12
-        fp32 = prec == "mixed" and name in ("hess_lu", "hess_uinv", "band_lu_panel", "hier_leaf")
+        fp32 = prec == "mixed" and name in ("hess_lu", "hess_uinv", "band_lu_panel")
         peak = PEAK_FP32_TFLOPS if fp32 else PEAK_FP64_TFLOPS
         return {"kernel": name, "bound": "alu", "achieved": round(achieved, 4),
                 "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 5),

@@ -10,6 +10,7 @@ namespace fde {
 
 // Hierarchical form of the blocks (k_hier.hip): levels of 64 << l rows a half, ranks up to 32
 static constexpr int HIER_LEVELS = 6, HIER_RMAX = 32;
+static constexpr int HIER_R0 = 20, HIER_R0_32 = 16;  // level 0's largest rank, FP64 and FP32 (any alpha in (1, 2))
 static constexpr int HIER_CHUNK = 4;  // panels per workgroup of the apply's first kernel
 
 struct InstDesc {

@@ -101,193 +101,586 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// ------------------------------------------------------------------------------------
-// Leaf inverses.  Item = (instance, block, panel); one workgroup of 256 forms the 64 x 64
-// diagonal block from the weights and inverts it by Gauss-Jordan without pivoting (strict row
-// dominance).  Thread t holds row t % 64, columns 16 (t / 64) .. + 15 in registers; a step's pivot
-// row and column go through double-buffered LDS vectors, one barrier a step.  Bound by those 64
-// dependent steps, so four workgroups share a CU.
-template <typename T>
-__global__ __launch_bounds__(256) void k_hier_leaf(const InstDesc *__restrict__ Dd, ItemMap map, int *flag) {
-  __shared__ c_t<T> colb[2][HP], rowb[2][HP];
-  const int q = item_slot(map, blockIdx.x);
-  const InstDesc &d = Dd[map.ids[q]];
-  const int local = blockIdx.x - map.pre[q];
-  const int npan = d.npan, k = local / npan, p = local % npan;
-  const int r = threadIdx.x & 63, cq = threadIdx.x >> 6;
-  const double2 mu = d.mu[k], lam = d.lam[k];
-  const int row = p * HP + r, m = d.m;
-  const bool inr = row < m;
-  const double dp = inr ? d.scale * d.dp[row] : 0.0, dm = inr ? d.scale * d.dm[row] : 0.0;
-  c_t<T> a[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int c = 16 * cq + i, dd = r - c;
-    const bool ok = inr && p * HP + c < m;
-    const double gp = ok && dd >= -1 ? d.g[dd + 1] : 0.0;
-    const double gm = ok && dd <= 1 ? d.g[1 - dd] : 0.0;
-    const double J = fma(dp, gp, dm * gm);
-    double re = -d.tau * mu.x * J, im = -d.tau * mu.y * J;
-    if (dd == 0) {
-      re = inr ? re + lam.x : 1.0;
-      im = inr ? im + lam.y : 0.0;
-    }
-    a[i] = mk<T>((T)re, (T)im);
-  }
-  bool bad = false;
-  for (int jo = 0; jo < 4; ++jo) {
-#pragma unroll
-    for (int ji = 0; ji < 16; ++ji) {
-      const int j = 16 * jo + ji, b = ji & 1;
-      if (cq == jo) colb[b][r] = a[ji];
-      if (r == j) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) rowb[b][16 * cq + i] = a[i];
-      }
-      __syncthreads();
-      const c_t<T> pv = rowb[b][j];
-      const T m2 = pv.x * pv.x + pv.y * pv.y;
-      bad = bad || !(m2 > (T)0) || !isfinite(m2);
-      const T iv = (T)1 / m2;
-      const c_t<T> inv = mk<T>(pv.x * iv, -pv.y * iv);
-      const c_t<T> f = colb[b][r];
-      const c_t<T> fi = hmul<T>(f, inv);
-      const bool own = r == j;
-      const c_t<T> t = mk<T>(own ? -inv.x : fi.x, own ? -inv.y : fi.y);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const c_t<T> pr = rowb[b][16 * cq + i];
-        const c_t<T> base = mk<T>(own ? (T)0 : a[i].x, own ? (T)0 : a[i].y);
-        a[i] = hfms<T>(t, pr, base);
-      }
-      if (cq == jo) a[ji] = mk<T>(-t.x, -t.y);
-    }
-  }
-  if (bad) *flag = 1;
-  c_t<T> *D = (c_t<T> *)d.hD + ((size_t)k * npan + p) * HP * HP;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) D[(16 * cq + i) * HP + r] = a[i];
+// Data movement between lanes (li, lk) = (lane % 16, lane / 16) without LDS.
+template <int CTRL> __device__ __forceinline__ int dpp_mov(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) { return __int_as_float(dpp_mov<CTRL>(__float_as_int(v))); }
+template <int CTRL> __device__ __forceinline__ double dpp_mov(double v) {
+  return __hiloint2double(dpp_mov<CTRL>(__double2hiint(v)), dpp_mov<CTRL>(__double2loint(v)));
+}
+// lane li = I of the same lk
+template <int I, typename V> __device__ __forceinline__ V row_bcast(V v) {
+  v.x = dpp_mov<0x150 + I>(v.x);
+  v.y = dpp_mov<0x150 + I>(v.y);
+  return v;
+}
+// lane `src` (through LDS's crossbar)
+__device__ __forceinline__ float lane_get(float v, int src) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * src, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_get(double v, int src) {
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(4 * src, __double2hiint(v)),
+                          __builtin_amdgcn_ds_bpermute(4 * src, __double2loint(v)));
+}
+// the same for one lane of the wavefront
+__device__ __forceinline__ float lane_read(float v, int src) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
+}
+__device__ __forceinline__ double lane_read(double v, int src) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
+}
+// 1 / v by the hardware's estimate and Newton steps (within an ulp; NaN for 0 and infinities, which
+// the pivots' final check counts on)
+__device__ __forceinline__ float recip(float v) {
+  const float r = __builtin_amdgcn_rcpf(v);
+  return fmaf(r, fmaf(-v, r, 1.0f), r);
+}
+__device__ __forceinline__ double recip(double v) {
+  double r = __builtin_amdgcn_rcp(v);
+  r = fma(r, fma(-v, r, 1.0), r);
+  return fma(r, fma(-v, r, 1.0), r);
+}
+template <typename T> __device__ __forceinline__ c_t<T> inverse(c_t<T> p) {
+  const T iv = recip(p.x * p.x + p.y * p.y);
+  return mk<T>(p.x * iv, -p.y * iv);
+}
+
+// A barrier for data in LDS alone: stores to global memory stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // ------------------------------------------------------------------------------------
-// One Newton step on the leaf inverse, then W of every level from it: K_leaf^{-1} U.  Item =
-// (instance, block, panel).
-//
-// X <- X + X (I - K X).  Gauss-Jordan leaves an error of cond(K_leaf) eps in X (the leaf of a
-// frequency near zero is close to a singular M-matrix), the largest error of the whole form; the
-// step takes it to the size of X's own rounding (forward errors of S^{-1} v 5 to 20 times
-// smaller).  K X = lambda X - c (J X) with J real, so it costs one real-by-complex and one complex
-// product, on MFMA.
-//
-// Then wave w owns rows 16 w .. + 15 of the panel, its 16 x 64 slice of the inverse in registers as
-// the MFMA operand, and walks the 16-column tiles of all levels; U is formed from X and d on the
-// way in.
-static constexpr int HLS = HP + 1;  // LDS column stride of a leaf
+// Products of 16 x 16 tiles.  A tile of results sits in the lane layout that the next product reads
+// as its right operand, so a chain of products stays in registers: lane (li, lk) holds column li,
+// rows 4 lk + v (left operands loaded with rowperm) or rows 4 v + lk (with rowstr: for the R-row
+// tiles, of which the rows from R on then are whole steps and are skipped).
+template <typename T> __device__ __forceinline__ int rowstr(int i);
+template <> __device__ __forceinline__ int rowstr<double>(int i) { return i; }
+template <> __device__ __forceinline__ int rowstr<float>(int i) { return 4 * (i & 3) + (i >> 2); }
+
+template <typename T> struct ctile {
+  acc_t<T> re, im;
+  __device__ __forceinline__ void zero() { re = im = acc_t<T>{0, 0, 0, 0}; }
+};
+template <typename T>
+__device__ __forceinline__ void tile_fma(ctile<T> &c, c_t<T> a, T bx, T by) {
+  c.re = mfma16(a.x, bx, c.re);
+  c.re = mfma16(-a.y, by, c.re);
+  c.im = mfma16(a.x, by, c.im);
+  c.im = mfma16(a.y, bx, c.im);
+}
+template <typename T>
+__device__ __forceinline__ void tile_fms(ctile<T> &c, c_t<T> a, T bx, T by) {
+  c.re = mfma16(-a.x, bx, c.re);
+  c.re = mfma16(a.y, by, c.re);
+  c.im = mfma16(-a.x, by, c.im);
+  c.im = mfma16(-a.y, bx, c.im);
+}
+template <typename T>
+__device__ __forceinline__ void tile_fma(ctile<T> &c, T a, T bx, T by) {
+  c.re = mfma16(a, bx, c.re);
+  c.im = mfma16(a, by, c.im);
+}
+
+// Gauss-Jordan without pivoting on a 16 x 16 block that a wavefront holds as a left operand: lane
+// (li, lk) row rowperm(li), columns 4 lk + s.  Step I takes row rowperm(I) as the pivot; a pivot row
+// is scaled at the end (rinv), which saves the selects of a row treated apart in every step.
+template <typename T, int I>
+__device__ __forceinline__ void gj16_step(c_t<T> *a, c_t<T> &rinv, int lane) {
+  constexpr int pj = sizeof(T) == 8 ? 4 * (I & 3) + (I >> 2) : I, lkp = pj >> 2, sp = pj & 3;
+  const int li = lane & 15, lk = lane >> 4;
+  const c_t<T> f = mk<T>(lane_get(a[sp].x, 16 * lkp + li), lane_get(a[sp].y, 16 * lkp + li));
+  const c_t<T> inv = inverse<T>(row_bcast<I>(f));
+  const bool own = li == I;
+  const c_t<T> t = hmul<T>(mk<T>(own ? (T)0 : f.x, own ? (T)0 : f.y), inv);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) a[s] = hfms<T>(t, row_bcast<I>(a[s]), a[s]);
+  if (lk == lkp) a[sp] = mk<T>(own ? (T)1 : -t.x, -t.y);
+  if (own) rinv = inv;
+}
+template <typename T, int I>
+__device__ __forceinline__ void gj16_from(c_t<T> *a, c_t<T> &rinv, int lane) {
+  if constexpr (I < 16) {
+    gj16_step<T, I>(a, rinv, lane);
+    gj16_from<T, I + 1>(a, rinv, lane);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void gj16(c_t<T> *a, int lane) {
+  c_t<T> rinv = mk<T>((T)1, (T)0);
+  gj16_from<T, 0>(a, rinv, lane);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) a[s] = hmul<T>(a[s], rinv);
+}
+
+// In-place inverse of an R x R matrix in LDS ([column][row], stride R) by the four wavefronts w of
+// a group, Gauss-Jordan with partial pivoting and no row exchanges: lane (r, half) holds row r,
+// columns 8 i + 2 w + half.  Every wavefront of the workgroup calls it (one barrier a step).  col: 64
+// entries of LDS, piv: 32.
+template <typename T> __device__ __forceinline__ unsigned mag_key(T m2);
+template <> __device__ __forceinline__ unsigned mag_key<float>(float m2) { return __float_as_uint(m2); }
+template <> __device__ __forceinline__ unsigned mag_key<double>(double m2) { return (unsigned)__double2hiint(m2); }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_hier_init(const InstDesc *__restrict__ Dd, ItemMap map) {
+__device__ __forceinline__ void group_invert(c_t<T> *M, int R, int w, c_t<T> *col, int *piv, bool &bad) {
+  const int lane = threadIdx.x & 63, r = lane & 31, hf = lane >> 5;
+  c_t<T> a[4], rinv = mk<T>((T)1, (T)0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = 8 * i + 2 * w + hf;
+    const bool in = r < R && c < R;
+    const c_t<T> v = M[in ? c * R + r : 0];
+    a[i] = mk<T>(in ? v.x : (T)0, in ? v.y : (T)0);
+  }
+  bool used = r >= R;
+  int mine = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll 1
+    for (int j = 8 * i; j < min(R, 8 * i + 8); ++j) {
+      const bool owner = w == ((j >> 1) & 3) && hf == (j & 1);
+      if (owner) col[32 * (j & 1) + r] = a[i];
+      lds_barrier();
+      const c_t<T> v = col[32 * (j & 1) + r];
+      // the largest entry (to 15 bits) in a row not used yet, the first of equals
+      unsigned key = used ? 0u : (mag_key<T>(v.x * v.x + v.y * v.y) & ~31u) | (unsigned)(31 - r);
+      key = max(key, (unsigned)dpp_mov<0x128>((int)key));
+      key = max(key, (unsigned)dpp_mov<0x124>((int)key));
+      key = max(key, (unsigned)dpp_mov<0x122>((int)key));
+      key = max(key, (unsigned)dpp_mov<0x121>((int)key));
+      const int pr = 31 - (int)(max((unsigned)__builtin_amdgcn_readlane((int)key, 0),
+                                    (unsigned)__builtin_amdgcn_readlane((int)key, 16)) & 31);
+      const c_t<T> inv = inverse<T>(mk<T>(lane_read(v.x, pr), lane_read(v.y, pr)));
+      const bool own = r == pr;
+      const c_t<T> t = hmul<T>(mk<T>(own ? (T)0 : v.x, own ? (T)0 : v.y), inv);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (8 * q < R) a[q] = hfms<T>(t, mk<T>(lane_get(a[q].x, 32 * hf + pr), lane_get(a[q].y, 32 * hf + pr)), a[q]);
+      if (owner) a[i] = mk<T>(own ? (T)1 : -t.x, -t.y);
+      if (own) {
+        rinv = inv;
+        used = true;
+        mine = j;
+        piv[j] = pr;  // every wavefront of the group writes the same
+      }
+    }
+  lds_barrier();
+  // row r holds the unknown that it was the pivot of, column c the right-hand side of c's pivot row
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = 8 * i + 2 * w + hf;
+    if (r < R && c < R) {
+      const c_t<T> v = hmul<T>(a[i], rinv);
+      bad = bad || !isfinite(v.x + v.y);
+      M[piv[c] * R + mine] = v;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Leaf inverses, the W columns of all levels from them (K_leaf^{-1} U), and level 0 in full.
+// Item = (instance, block, pair of panels); eight wavefronts, four to a leaf.
+//
+// Leaf.  Wavefront w of a leaf holds columns 16 w .. + 15 of the 64 x 64 diagonal block as four
+// tiles, and block Gauss-Jordan (no pivoting: strict row dominance) runs over its four 16-column
+// blocks: the owner puts the block into LDS, every wavefront inverts the 16 x 16 pivot for itself
+// (16 dependent steps, no barrier), and updates its tiles on MFMA.  One barrier per block.
+//
+// Newton.  X <- X + X (I - K X).  Gauss-Jordan leaves an error of cond(K_leaf) eps in X (the leaf of
+// a frequency near zero is close to a singular M-matrix), the largest error of the whole form; the
+// step takes it to the size of X's own rounding (forward errors of S^{-1} v 5 to 20 times
+// smaller).  K X = lambda X - c (J X) with J real, so it costs one real-by-complex and one complex
+// product.
+//
+// Level 0.  W_0 and G on two wavefronts per leaf (a 16-column tile each), the R x R inverse and W_0' on
+// four.  The columns of the levels above then pass through the pair, one 16-column tile of one leaf
+// per wavefront, U -> K_leaf^{-1} U -> A -> z -> W - W_0' z, without leaving registers (the two
+// wavefronts of a tile exchange their A): they are written once, where separate kernels for the
+// leaves, the columns and level 0 wrote them twice and read them three times.
+//
+// In FP64 one workgroup fills a CU's LDS, so what counts is that its phases are short: MFMA is busy
+// for half of the time (block Gauss-Jordan is bound by its 16-step chains, the R x R inverses by theirs
+// of 20), and the code (54 KB) stays within the instruction cache, with the block loop rolled.  4095 x
+// 256: 2.84 ms FP64 and 1.09 mixed (two workgroups per CU) for leaves, columns and level 0, from 4.48
+// and 1.94 in four launches with three passes over the columns.
+template <typename T> struct HierLds {
+  static constexpr int R0 = sizeof(T) == 8 ? HIER_R0 : HIER_R0_32;  // level 0's largest rank
+  // behind the two leaves: two R0 x R0 matrices and four columns of 32 for their inverses; later the
+  // exchange of A, R0 x 16 real numbers per wavefront
+  static constexpr size_t leaves = 2 * HP * HP * sizeof(c_t<T>);
+  static constexpr size_t small = (2 * R0 * R0 + 128) * sizeof(c_t<T>), swap = 8 * R0 * 16 * sizeof(T);
+  static constexpr size_t bytes = leaves + (small > swap ? small : swap);
+};
+// [column][row] of a leaf in LDS; rows are exchanged within 16 so that a column read (16 rows) and a
+// tile write (16 columns) both meet every bank once
+__device__ __forceinline__ int lx(int c, int r) { return c * HP + (r ^ (c & 15)); }
+
+// K_leaf^{-1} U for one column per li: U's column `col` of level lev at panel p, X its leaf inverse
+template <typename T>
+__device__ __forceinline__ void leaf_tile(const InstDesc &d, const c_t<T> *X, int lane, int p, int lev, int col, bool ok,
+                                          ctile<T> *W) {
+  const int li = lane & 15, lk = lane >> 4, m = d.m;
+  const int side = (p >> lev) & 1, c = (2 * (p >> (lev + 1)) + 1) << lev;  // first panel of the right half
+  ok = ok && c < d.npan;
+  // the e_0 column carries the other side's coefficient (the g_0 entry next to the diagonal)
+  const double *dv = (side == 0) != (col == 0) ? d.dm : d.dp;
+  const double *tab = hier_x(d, lev) + col;
+  T u[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int i = 16 * (e >> 2) + 4 * lk + (e & 3), row = p * HP + i;
+    const int pi = side ? (p - c) * HP + i : (c - p) * HP - 1 - i;
+    const bool in = ok && row < m;
+    const double t = d.scale * (gld(dv + (row < m ? row : 0)) * gld(tab + (in ? pi : 0) * 32));
+    u[e] = in ? (T)t : (T)0;
+  }
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) W[mt].zero();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int k = 16 * (e >> 2) + 4 * lk + (e & 3);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      const c_t<T> a = X[lx(k, 16 * mt + rowperm<T>(li))];
+      W[mt].re = mfma16(a.x, u[e], W[mt].re);
+      W[mt].im = mfma16(a.y, u[e], W[mt].im);
+    }
+  }
+}
+// The products below take R <= 4 NE rows or columns: tiles of 4 NE with zeros in rows R and above.
+// a = V^T B over the 64 rows of a panel: tab the level's table, row i of the panel at row off + dir i
+// of it
+template <typename T, int NE>
+__device__ __forceinline__ void panel_gram(const double *tab, int lane, int off, int dir, int R, const ctile<T> *B, ctile<T> *a) {
+  constexpr int NT = (NE + 3) / 4;
+  const int li = lane & 15, lk = lane >> 4;
+  T x[NT][16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const double *row = tab + (off + dir * (16 * (e >> 2) + 4 * lk + (e & 3))) * 32;
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) {
+      const int r = 16 * rt + rowstr<T>(li);
+      const double v = gld(row + r);
+      x[rt][e] = r < R ? (T)v : (T)0;
+    }
+  }
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) a[rt].zero();
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) tile_fma<T>(a[rt], x[rt][e], B[e >> 2].re[e & 3], B[e >> 2].im[e & 3]);
+}
+// c -= G a for R x R G ([column][row]), in LDS or in global memory
+template <typename T, int NE, bool LDS>
+__device__ __forceinline__ void small_fms(const c_t<T> *G, int lane, int R, const ctile<T> *a, ctile<T> *c) {
+  constexpr int NT = (NE + 3) / 4;
+  const int li = lane & 15, lk = lane >> 4;
+  c_t<T> g[NT][NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) {
+      const int r = 16 * rt + rowstr<T>(li), cc = 4 * e + lk;
+      const c_t<T> *at = G + (r < R && cc < R ? cc * R + r : 0), v = LDS ? *at : cload<T>(at);
+      g[rt][e] = mk<T>(r < R ? v.x : (T)0, r < R ? v.y : (T)0);
+    }
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) tile_fms<T>(c[rt], g[rt][e], a[e >> 2].re[e & 3], a[e >> 2].im[e & 3]);
+}
+// B -= W' z over the 64 rows of a panel (W: its R columns)
+template <typename T, int NE>
+__device__ __forceinline__ void panel_update(const c_t<T> *W, int lane, int R, const ctile<T> *z, ctile<T> *B) {
+  const int li = lane & 15, lk = lane >> 4;
+  W += rowperm<T>(li);
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int cc = 4 * e + lk;
+    c_t<T> w[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) w[mt] = cload<T>(W + (cc < R ? cc : 0) * HP + 16 * mt);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) tile_fms<T>(B[mt], w[mt], z[e >> 2].re[e & 3], z[e >> 2].im[e & 3]);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void panel_store(c_t<T> *o, const ctile<T> *B) {
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[16 * mt + v] = mk<T>(B[mt].re[v], B[mt].im[v]);
+}
+
+template <typename T>
+__global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const InstDesc *__restrict__ Dd, ItemMap map, int *flag) {
   extern __shared__ double hier_lds[];
-  c_t<T> *S = (c_t<T> *)hier_lds;
-  __shared__ T gt[2 * HP];  // g_t at index t + 63, zero for t < 0
+  __shared__ double gt[2 * HP];  // g_t at index t + 63, zero for t < 0
+  __shared__ int piv[2][32];
   const int q = item_slot(map, blockIdx.x);
   const InstDesc &d = Dd[map.ids[q]];
   const int local = blockIdx.x - map.pre[q];
-  const int npan = d.npan, k = local / npan, p = local % npan, m = d.m;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  c_t<T> *D0 = (c_t<T> *)d.hD + ((size_t)k * npan + p) * HP * HP;
-  for (int t = threadIdx.x; t < 2 * HP; t += 256) gt[t] = t >= 63 && t - 63 <= m ? (T)d.g[t - 63] : (T)0;
-  __syncthreads();
-  c_t<T> A[16];
-  {  // R = I - K X, columns 16 w .. + 15, into LDS
-    const int colg = p * HP + 16 * w + li;
+  const int npan = d.npan, m = d.m, pairs = (npan + 1) / 2, k = local / pairs, pair = local % pairs;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int leaf = wv >> 2, w = wv & 3, p = 2 * pair + leaf;
+  const bool mine = p < npan, live = 2 * pair + 1 < npan;
+  c_t<T> *LX = (c_t<T> *)hier_lds + leaf * HP * HP;
+  c_t<T> *LM = (c_t<T> *)hier_lds + 2 * HP * HP, *pcol = LM + 2 * HierLds<T>::R0 * HierLds<T>::R0 + 64 * leaf;
+  const c_t<T> mc = minus_c<T>(d, k);
+  for (int t = threadIdx.x; t < 2 * HP; t += 512) gt[t] = t >= 63 && t - 63 <= m ? d.g[t - 63] : 0.0;
+  lds_barrier();
+  const int cl = 16 * w + li;  // this lane's column of the leaf
+  ctile<T> X[4];
+  bool bad = false;
+  if (mine) {
+    const double2 mu = d.mu[k], lam = d.lam[k];
+    const bool incol = p * HP + cl < m;
 #pragma unroll
-    for (int s = 0; s < 16; ++s) A[s] = cload<T>(D0 + (16 * w + li) * HP + 4 * s + lk);
-    const c_t<T> mc = minus_c<T>(d, k);
-    const c_t<T> lam = mk<T>((T)d.lam[k].x, (T)d.lam[k].y);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int i = 16 * mt + li, row = p * HP + i;
-      const T dp = row < m ? (T)(d.scale * d.dp[row]) : (T)0, dm = row < m ? (T)(d.scale * d.dm[row]) : (T)0;
-      acc_t<T> re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < 16; ++s) {
-        const int kc = 4 * s + lk;
-        T J = fma(dp, gt[i - kc + 64], dm * gt[kc - i + 64]);
-        if (p * HP + kc >= m) J = (T)0;
-        re = mfma16(J, A[s].x, re);
-        im = mfma16(J, A[s].y, im);
-      }
+    for (int I = 0; I < 4; ++I)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int r = 16 * mt + mfma_row<T>(lk, v);
-        const c_t<T> x = cload<T>(D0 + (16 * w + li) * HP + r);
-        c_t<T> t = mk<T>(r == 16 * w + li ? (T)1 : (T)0, (T)0);
-        t = hfms<T>(lam, x, t);
-        t = hfms<T>(mc, mk<T>(re[v], im[v]), t);
-        if (p * HP + r >= m || colg >= m) t = mk<T>((T)0, (T)0);
-        S[(16 * w + li) * HLS + r] = t;
+        const int i = 16 * I + 4 * lk + v, row = p * HP + i, dd = i - cl;
+        const bool in = row < m;
+        const double dp = d.scale * gld(d.dp + (in ? row : 0)), dm = d.scale * gld(d.dm + (in ? row : 0));
+        const double Jv = fma(dp, gt[dd + 64], dm * gt[64 - dd]), J = in && incol ? Jv : 0.0;
+        double re = -d.tau * mu.x * J, im = -d.tau * mu.y * J;
+        if (dd == 0) {
+          re = in ? re + lam.x : 1.0;
+          im = in ? im + lam.y : 0.0;
+        }
+        X[I].re[v] = (T)re;
+        X[I].im[v] = (T)im;
       }
+  }
+  T dpr[4], dmr[4];  // d+- at rows 16 mt + rowperm(li), for the Newton step
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const int row = p * HP + 16 * mt + rowperm<T>(li);
+    dpr[mt] = row < m ? (T)(d.scale * gld(d.dp + (row < m ? row : 0))) : (T)0;
+    dmr[mt] = row < m ? (T)(d.scale * gld(d.dm + (row < m ? row : 0))) : (T)0;
+  }
+#pragma unroll 1
+  for (int J = 0; J < 4; ++J) {  // X[i] is row tile (J + i) % 4
+    c_t<T> *buf = LX + (J & 1) * 16 * HP;  // the pivot block, two of them in turn
+    if (mine && w == J) {
+#pragma unroll
+      for (int I = 0; I < 4; ++I)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) buf[lx(li, 16 * ((J + I) & 3) + 4 * lk + v)] = mk<T>(X[I].re[v], X[I].im[v]);
+    }
+    lds_barrier();
+    if (mine) {
+      const bool own = w == J;
+      c_t<T> P[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) P[s] = buf[lx(4 * lk + s, 16 * J + rowperm<T>(li))];
+      gj16<T>(P, lane);
+      // P times this wavefront's block row; the pivot block itself becomes P, the rest of its column -A P
+      ctile<T> B;
+      B.zero();
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const T one = 4 * lk + s == li ? (T)1 : (T)0;
+        tile_fma<T>(B, P[s], own ? one : X[0].re[s], own ? (T)0 : X[0].im[s]);
+      }
+#pragma unroll
+      for (int I = 1; I < 4; ++I) {
+        if (own) X[I].zero();
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          tile_fms<T>(X[I], buf[lx(4 * lk + s, 16 * ((J + I) & 3) + rowperm<T>(li))], B.re[s], B.im[s]);
+        X[I - 1] = X[I];
+      }
+      X[3] = B;
     }
   }
-  __syncthreads();
-  const int rw = 16 * w + rowperm<T>(li);
+  lds_barrier();
+  ctile<T> E[4];
+  if (mine) {  // E = I - K X; X into LDS
+    const c_t<T> lam = mk<T>((T)d.lam[k].x, (T)d.lam[k].y);
+    T chk = (T)0;
+    // g_{i-j+1} and g_{j-i+1} for row i = 16 mt + rowperm(li), column j = 16 t + 4 lk + s.  Rows j of X
+    // from m on are zero in the columns before m, and E is only taken there.
+    const double *gp = gt + 64 + rowperm<T>(li) - 4 * lk, *gm = gt + 64 - rowperm<T>(li) + 4 * lk;
 #pragma unroll
-  for (int s = 0; s < 16; ++s) A[s] = cload<T>(D0 + (4 * s + lk) * HP + rw);
-  c_t<T> nx[4][4];
+    for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    acc_t<T> re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      const c_t<T> b = S[(16 * n + li) * HLS + 4 * s + lk];
-      re = mfma16(A[s].x, b.x, re);
-      re = mfma16(-A[s].y, b.y, re);
-      im = mfma16(A[s].x, b.y, im);
-      im = mfma16(A[s].y, b.x, im);
+      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + 4 * lk + v)] = mk<T>(X[mt].re[v], X[mt].im[v]);
+      E[mt].zero();
     }
-    c_t<T> *o = D0 + (16 * n + li) * HP + 16 * w + 4 * lk;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const c_t<T> x = cload<T>(o + v);
-      nx[n][v] = mk<T>(x.x + re[v], x.y + im[v]);
-      o[v] = nx[n][v];
+    for (int e = 0; e < 16; ++e) {
+      const int t = e >> 2, s = e & 3;
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        const T J = fma(dpr[mt], (T)gp[16 * (mt - t) - s], dmr[mt] * (T)gm[16 * (t - mt) + s]);
+        tile_fma<T>(E[mt], J, X[t].re[s], X[t].im[s]);
+      }
+      chk += X[t].re[s] + X[t].im[s];
+    }
+    bad = !isfinite(chk);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 16 * mt + 4 * lk + v;
+        c_t<T> t = mk<T>(r == cl ? (T)1 : (T)0, (T)0);
+        t = hfms<T>(lam, mk<T>(X[mt].re[v], X[mt].im[v]), t);
+        t = hfms<T>(mc, mk<T>(E[mt].re[v], E[mt].im[v]), t);
+        const bool in = p * HP + r < m && p * HP + cl < m;
+        E[mt].re[v] = in ? t.x : (T)0;
+        E[mt].im[v] = in ? t.y : (T)0;
+      }
+  }
+  lds_barrier();
+  if (mine) {
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      ctile<T> c;
+      c.zero();
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        tile_fma<T>(c, LX[lx(16 * (e >> 2) + 4 * lk + (e & 3), 16 * mt + rowperm<T>(li))], E[e >> 2].re[e & 3],
+                    E[e >> 2].im[e & 3]);
+      X[mt].re += c.re;
+      X[mt].im += c.im;
     }
   }
-  __syncthreads();  // R is used up: the new inverse takes its place
+  lds_barrier();
+  if (mine) {
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
+    for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) S[(16 * n + li) * HLS + 16 * w + 4 * lk + v] = nx[n][v];
-  __syncthreads();
+      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + 4 * lk + v)] = mk<T>(X[mt].re[v], X[mt].im[v]);
+  }
+  lds_barrier();
+  if (mine) {
+    c_t<T> *D = (c_t<T> *)d.hD + ((size_t)k * npan + p) * HP * HP;
 #pragma unroll
-  for (int s = 0; s < 16; ++s) A[s] = S[(4 * s + lk) * HLS + rw];
-  for (int lev = 0; lev < d.nlev; ++lev) {
-    const int R = d.hR[lev], node = p >> (lev + 1), side = (p >> lev) & 1;
-    const int c = (2 * node + 1) << lev;  // first panel of the right half
-    const bool live = c < npan;
-    const double *X = hier_x(d, lev);
-    c_t<T> *W = hier_w<T>(d, lev, k);
-    for (int n = 0; n < R; n += 16) {
-      const int col = n + li;
-      const bool ok = live && col < R;
-      // the e_0 column carries the other side's coefficient (the g_0 entry next to the diagonal)
-      const double *dv = (side == 0) != (col == 0) ? d.dm : d.dp;
-      acc_t<T> re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    for (int i = 0; i < 16; ++i) D[(16 * w + i) * HP + lane] = LX[lx(16 * w + i, lane)];
+  }
+  if (d.nlev == 0) {
+    if (bad) *flag = 1;
+    return;
+  }
+  constexpr int NE = HierLds<T>::R0 / 4, NT = (NE + 3) / 4;
+  const int R = d.hR[0];
+  c_t<T> *W0 = hier_w<T>(d, 0, k), *G = hier_g<T>(d, 0, k, pair);
+  if (live) {
+    const int ct = w ^ (2 * leaf), col = 16 * ct + li;  // the two leaves' tiles on different SIMDs
+    const bool tile = 16 * ct < R;
+    c_t<T> *Ml = LM + leaf * R * R;
+    ctile<T> g[NT], c[NT];
+    if (tile) {
+      ctile<T> W[4];
+      leaf_tile<T>(d, LX, lane, p, 0, col < R ? col : 0, col < R, W);
+      if (col < R) panel_store<T>(W0 + ((size_t)p * R + col) * HP + 4 * lk, W);
+      panel_gram<T, NE>(hier_x(d, 0), lane, leaf ? 0 : HP - 1, leaf ? 1 : -1, R, W, g);
 #pragma unroll
-      for (int s = 0; s < 16; ++s) {
-        const int i = 4 * s + lk, row = p * HP + i;
-        const int pi = side ? (p - c) * HP + i : (c - p) * HP - 1 - i;
-        T u = (T)0;
-        if (ok && row < m) u = (T)(d.scale * (dv[row] * X[(size_t)pi * 32 + col]));
-        re = mfma16(A[s].x, u, re);
-        im = mfma16(A[s].y, u, im);
-      }
-      if (col < R) {
-        c_t<T> *o = W + ((size_t)p * R + col) * HP + 16 * w + 4 * lk;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = mk<T>(re[v], im[v]);
+      for (int e = 0; e < NE; ++e) {
+        const int r = 4 * e + lk;
+        const c_t<T> t = hmul<T>(mc, mk<T>(g[e >> 2].re[e & 3], g[e >> 2].im[e & 3]));
+        g[e >> 2].re[e & 3] = t.x;
+        g[e >> 2].im[e & 3] = t.y;
+        if (r < R && col < R) {
+          G[((size_t)leaf * R + col) * R + r] = t;
+          Ml[col * R + r] = t;
+        }
       }
     }
+    __syncthreads();  // W_0 and G as well
+    if (tile) {  // I - G_other G_own
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          c[rt].re[v] = 16 * rt + 4 * v + lk == col ? (T)1 : (T)0;
+          c[rt].im[v] = (T)0;
+        }
+      small_fms<T, NE, true>(LM + (1 - leaf) * R * R, lane, R, g, c);
+    }
+    lds_barrier();
+    if (tile && col < R) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+        if (4 * e + lk < R) Ml[col * R + 4 * e + lk] = mk<T>(c[e >> 2].re[e & 3], c[e >> 2].im[e & 3]);
+    }
+    lds_barrier();
+    group_invert<T>(Ml, R, w, pcol, piv[leaf], bad);
+    lds_barrier();
+    {  // W_0' = W_0 (-c (I - G_other G_own)^{-1}), rows 16 w .. + 15
+      c_t<T> *Wp = W0 + (size_t)p * R * HP + 16 * w;
+      c_t<T> a[NE];
+#pragma unroll
+      for (int e = 0; e < NE; ++e) a[e] = cload<T>(Wp + (4 * e + lk < R ? 4 * e + lk : 0) * HP + rowperm<T>(li));
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) {
+        const int cc = 16 * ct + li;
+        ctile<T> o;
+        o.zero();
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          const bool in = cc < R && 4 * e + lk < R;
+          const c_t<T> b = hmul<T>(mc, Ml[in ? cc * R + 4 * e + lk : 0]);
+          tile_fma<T>(o, a[e], in ? b.x : (T)0, in ? b.y : (T)0);
+        }
+        if (cc < R) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) Wp[cc * HP + 4 * lk + v] = mk<T>(o.re[v], o.im[v]);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (bad) *flag = 1;
+  int ncol = 0;
+  for (int l = 1; l < d.nlev; ++l) ncol += d.hR[l];
+  const int slot = w ^ (2 * leaf);  // the two wavefronts of a tile sit on different SIMDs
+  T *xb = (T *)LM + (wv * NE) * 64, *xo = (T *)LM + ((wv ^ 6) * NE) * 64;  // own and partner's A
+#pragma unroll 1
+  for (int t0 = 0; 16 * t0 < ncol; t0 += 4) {
+    int ln = lane;  // opaque, so that the operands' addresses are not held across iterations
+    asm volatile("" : "+v"(ln)::"memory");
+    int col = 16 * (t0 + slot) + (ln & 15), lev = 1;
+    const bool act = mine && 16 * (t0 + slot) < ncol, ok = col < ncol;
+    if (!ok) col = 0;
+    while (col >= d.hR[lev]) col -= d.hR[lev++];
+    ctile<T> B[4], a[NT], z[NT];
+    if (act) leaf_tile<T>(d, LX, ln, p, lev, col, ok, B);
+    if (live) {
+      if (act) {
+        panel_gram<T, NE>(hier_x(d, 0), ln, leaf ? 0 : HP - 1, leaf ? 1 : -1, R, B, a);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) xb[64 * e + ln] = a[e >> 2].re[e & 3];
+      }
+      lds_barrier();
+      if (act) {
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt) z[rt].zero();
+#pragma unroll
+        for (int e = 0; e < NE; ++e) z[e >> 2].re[e & 3] = xo[64 * e + ln];
+      }
+      lds_barrier();
+      if (act) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) xb[64 * e + ln] = a[e >> 2].im[e & 3];
+      }
+      lds_barrier();
+      if (act) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) z[e >> 2].im[e & 3] = xo[64 * e + ln];
+        small_fms<T, NE, false>(G + (size_t)(1 - leaf) * R * R, ln, R, a, z);
+        panel_update<T, NE>(W0 + (size_t)p * R * HP, ln, R, z, B);
+      }
+      lds_barrier();
+    }
+    if (act && ok) panel_store<T>(hier_w<T>(d, lev, k) + ((size_t)p * d.hR[lev] + col) * HP + 4 * (ln >> 4), B);
   }
 }
 
@@ -873,16 +1266,10 @@ __global__ __launch_bounds__(256, 2) void k_hier_up(const InstDesc *__restrict__
 template <typename T>
 hipError_t launch_hier_leaf(const InstDesc *D, const ItemMap &map, int items, int *flag, hipStream_t st) {
   if (items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hier_leaf<T>, dim3(items), dim3(256), 0, st, D, map, flag);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t launch_hier_init(const InstDesc *D, const ItemMap &map, int items, hipStream_t st) {
-  if (items <= 0) return hipSuccess;
-  const size_t lds = HP * HLS * sizeof(c_t<T>);
-  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_init<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const size_t lds = HierLds<T>::bytes;
+  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_leaf<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hier_init<T>, dim3(items), dim3(256), lds, st, D, map);
+  hipLaunchKernelGGL(k_hier_leaf<T>, dim3(items), dim3(512), lds, st, D, map, flag);
   return hipGetLastError();
 }
 template <typename T>
@@ -918,7 +1305,6 @@ hipError_t launch_hier_up(const InstDesc *D, const ItemMap &map, int items, int 
 
 #define HIER_INST(T)                                                                                       \
   template hipError_t launch_hier_leaf<T>(const InstDesc *, const ItemMap &, int, int *, hipStream_t);     \
-  template hipError_t launch_hier_init<T>(const InstDesc *, const ItemMap &, int, hipStream_t);            \
   template hipError_t launch_hier_node<T>(const InstDesc *, const ItemMap &, int, int, int *, hipStream_t); \
   template hipError_t launch_hier_cols<T>(const InstDesc *, const ItemMap &, int, int, hipStream_t);       \
   template hipError_t launch_hier_sub<T>(const InstDesc *, const ItemMap &, int, hipStream_t);        \

@@ -202,12 +202,11 @@ hipError_t launch_qgemm(const InstDesc *D, const ItemMap &map, int items, int tr
                         hipStream_t st);
 
 // ---- the blocks in hierarchical form (k_hier.hip) ----
-// items: leaf and init nb npan per instance; node nb nodes(lev); cols nb nodes(lev) times the
-// 32-column chunks of the higher levels' columns 
+// items: leaf (leaf inverses, W of all levels, level 0) nb ceil(npan / 2) per instance; for the
+// levels from 1 on, node nb nodes(lev) and cols nb nodes(lev) times the 32-column chunks of the
+// higher levels' columns
 template <typename T>
 hipError_t launch_hier_leaf(const InstDesc *D, const ItemMap &map, int items, int *flag, hipStream_t st);
-template <typename T>
-hipError_t launch_hier_init(const InstDesc *D, const ItemMap &map, int items, hipStream_t st);
 template <typename T>
 hipError_t launch_hier_node(const InstDesc *D, const ItemMap &map, int items, int lev, int *flag, hipStream_t st);
 template <typename T>

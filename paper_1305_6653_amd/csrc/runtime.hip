@@ -946,6 +946,7 @@ static bool hier_basis(const fde_bvm *h, std::vector<double> &table, int rank[2]
     rank[0][l] = (r + 1 + 3) & ~3;
     rank[1][l] = (std::min(r32, r) + 1 + 3) & ~3;
   }
+  if (nlev > 0 && (rank[0][0] > HIER_R0 || rank[1][0] > HIER_R0_32)) return false;
   return true;
 }
 
@@ -1813,7 +1814,7 @@ static fde_status hier_factor(Plan *P) {
     return make_map(slots, it);
   };
   // algorithmic flops: 8 per complex multiply-add, 4 per real times complex one
-  double wleaf = 0.0, winit = 0.0;
+  double wleaf = 0.0;
   std::vector<double> wnode(HIER_LEVELS, 0.0), wcols(HIER_LEVELS, 0.0);
   auto higher = [](const fde_bvm *h, int l) {
     int n = 0;
@@ -1822,16 +1823,16 @@ static fde_status hier_factor(Plan *P) {
   };
   for (const fde_bvm *h : P->hs) {
     if (!h->hier) continue;
-    wleaf += 8.0 * h->nb * h->npan * 64.0 * 64.0 * 64.0;
-    winit += 4.0 * h->nb * h->mp * 64.0 * (3.0 * 64.0 + higher(h, -1));
+    wleaf += 4.0 * h->nb * h->mp * 64.0 * (5.0 * 64.0 + higher(h, -1));
     for (int l = 0; l < h->nlev; ++l) {
       const double r = h->hR[l], n = higher(h, l);
       wnode[l] += h->nb * (12.0 * h->mp * r * r + 48.0 * hier_nodes_p(h->npan, l) * r * r * r);
       wcols[l] += h->nb * n * (12.0 * h->mp * r + 16.0 * hier_nodes_p(h->npan, l) * r * r);
     }
   }
-  std::vector<HostMap> hm = {fill([](const fde_bvm *h) { return h->nb * h->npan; })};
-  for (int l = 0; l < nlev; ++l) {
+  wleaf += wnode[0] + wcols[0];
+  std::vector<HostMap> hm = {fill([](const fde_bvm *h) { return h->nb * ((h->npan + 1) / 2); })};
+  for (int l = 1; l < nlev; ++l) {
     hm.push_back(fill([&](const fde_bvm *h) { return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) : 0; }));
     hm.push_back(fill([&](const fde_bvm *h) {
       return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) * ((higher(h, l) + 31) / 32) : 0;
@@ -1840,9 +1841,8 @@ static fde_status hier_factor(Plan *P) {
   std::vector<ItemMap> dm;
   STCHK(upload_maps(P, hm, dm));
   HIPCHK(run(L, "hier_leaf", wleaf, [&] { return launch_hier_leaf<T>(P->d_desc, dm[0], hm[0].items, P->d_flag, st); }));
-  HIPCHK(run(L, "hier_init", winit, [&] { return launch_hier_init<T>(P->d_desc, dm[0], hm[0].items, st); }));
-  for (int l = 0; l < nlev; ++l) {
-    const size_t a = 2 * l + 1, b = a + 1;
+  for (int l = 1; l < nlev; ++l) {
+    const size_t a = 2 * l - 1, b = a + 1;
     HIPCHK(run(L, "hier_node", wnode[l], [&] { return launch_hier_node<T>(P->d_desc, dm[a], hm[a].items, l, P->d_flag, st); }));
     if (hm[b].items > 0)
       HIPCHK(run(L, "hier_cols", wcols[l], [&] { return launch_hier_cols<T>(P->d_desc, dm[b], hm[b].items, l, st); }));
