@@ -36,8 +36,6 @@ namespace fde {
 
 static constexpr int HP = 64;       // leaf order, panel
 static constexpr int HCH = HIER_CHUNK;
-static constexpr int HS = 33;       // LDS column stride of the small matrices (32 rows and a pad)
-static constexpr int HSLOT = 32 * HS;
 
 template <typename T>
 __device__ __forceinline__ c_t<T> hmul(c_t<T> a, c_t<T> b) {
@@ -89,12 +87,6 @@ __device__ __forceinline__ c_t<T> *hier_g(const InstDesc &d, int lev, int k, int
 __device__ __forceinline__ const double *hier_x(const InstDesc &d, int lev) {
   return d.hx + (size_t)((HP << lev) - HP) * 32;
 }
-
-// The row of a 16-row tile that element i of an MFMA operand holds, chosen so that the four
-// results of a lane (mfma_row) are four consecutive rows 4 (lane / 16) + v.
-template <typename T> __device__ __forceinline__ int rowperm(int i);
-template <> __device__ __forceinline__ int rowperm<float>(int i) { return i; }
-template <> __device__ __forceinline__ int rowperm<double>(int i) { return 4 * (i & 3) + (i >> 2); }
 
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -155,9 +147,11 @@ __device__ __forceinline__ void lds_barrier() {
 
 // ------------------------------------------------------------------------------------
 // Products of 16 x 16 tiles.  A tile of results sits in the lane layout that the next product reads
-// as its right operand, so a chain of products stays in registers: lane (li, lk) holds column li,
-// rows 4 lk + v (left operands loaded with rowperm) or rows 4 v + lk (with rowstr: for the R-row
-// tiles, of which the rows from R on then are whole steps and are skipped).
+// as its right operand, so a chain of products stays in registers: lane (li, lk) holds column li.
+// Along a panel its rows are MFMA's own, mfma_row(lk, v): loads and stores of a tile then move 64
+// (FP64) or 32 (FP32, two 16-byte accesses a lane) consecutive bytes of 16 columns at a time.  Along
+// the R columns of V they are 4 v + lk (left operand rows by rowstr), of which those from R on are
+// whole steps and are skipped.
 template <typename T> __device__ __forceinline__ int rowstr(int i);
 template <> __device__ __forceinline__ int rowstr<double>(int i) { return i; }
 template <> __device__ __forceinline__ int rowstr<float>(int i) { return 4 * (i & 3) + (i >> 2); }
@@ -187,11 +181,11 @@ __device__ __forceinline__ void tile_fma(ctile<T> &c, T a, T bx, T by) {
 }
 
 // Gauss-Jordan without pivoting on a 16 x 16 block that a wavefront holds as a left operand: lane
-// (li, lk) row rowperm(li), columns 4 lk + s.  Step I takes row rowperm(I) as the pivot; a pivot row
-// is scaled at the end (rinv), which saves the selects of a row treated apart in every step.
+// (li, lk) row li, columns mfma_row(lk, s).  A pivot row is scaled at the end (rinv), which saves the
+// selects of a row treated apart in every step.
 template <typename T, int I>
 __device__ __forceinline__ void gj16_step(c_t<T> *a, c_t<T> &rinv, int lane) {
-  constexpr int pj = sizeof(T) == 8 ? 4 * (I & 3) + (I >> 2) : I, lkp = pj >> 2, sp = pj & 3;
+  constexpr int lkp = sizeof(T) == 8 ? I & 3 : I >> 2, sp = sizeof(T) == 8 ? I >> 2 : I & 3;
   const int li = lane & 15, lk = lane >> 4;
   const c_t<T> f = mk<T>(lane_get(a[sp].x, 16 * lkp + li), lane_get(a[sp].y, 16 * lkp + li));
   const c_t<T> inv = inverse<T>(row_bcast<I>(f));
@@ -319,6 +313,10 @@ template <typename T> struct HierLds {
 // tile write (16 columns) both meet every bank once
 __device__ __forceinline__ int lx(int c, int r) { return c * HP + (r ^ (c & 15)); }
 
+template <typename T, int N> __device__ __forceinline__ void zero_tiles(ctile<T> *t) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i].zero();
+}
 // K_leaf^{-1} U for one column per li: U's column `col` of level lev at panel p, X its leaf inverse
 template <typename T>
 __device__ __forceinline__ void leaf_tile(const InstDesc &d, const c_t<T> *X, int lane, int p, int lev, int col, bool ok,
@@ -332,7 +330,7 @@ __device__ __forceinline__ void leaf_tile(const InstDesc &d, const c_t<T> *X, in
   T u[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    const int i = 16 * (e >> 2) + 4 * lk + (e & 3), row = p * HP + i;
+    const int i = 16 * (e >> 2) + mfma_row<T>(lk, e & 3), row = p * HP + i;
     const int pi = side ? (p - c) * HP + i : (c - p) * HP - 1 - i;
     const bool in = ok && row < m;
     const double t = d.scale * (gld(dv + (row < m ? row : 0)) * gld(tab + (in ? pi : 0) * 32));
@@ -342,17 +340,17 @@ __device__ __forceinline__ void leaf_tile(const InstDesc &d, const c_t<T> *X, in
   for (int mt = 0; mt < 4; ++mt) W[mt].zero();
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    const int k = 16 * (e >> 2) + 4 * lk + (e & 3);
+    const int k = 16 * (e >> 2) + mfma_row<T>(lk, e & 3);
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
-      const c_t<T> a = X[lx(k, 16 * mt + rowperm<T>(li))];
+      const c_t<T> a = X[lx(k, 16 * mt + li)];
       W[mt].re = mfma16(a.x, u[e], W[mt].re);
       W[mt].im = mfma16(a.y, u[e], W[mt].im);
     }
   }
 }
 // The products below take R <= 4 NE rows or columns: tiles of 4 NE with zeros in rows R and above.
-// a = V^T B over the 64 rows of a panel: tab the level's table, row i of the panel at row off + dir i
+// a += V^T B over the 64 rows of a panel: tab the level's table, row i of the panel at row off + dir i
 // of it
 template <typename T, int NE>
 __device__ __forceinline__ void panel_gram(const double *tab, int lane, int off, int dir, int R, const ctile<T> *B, ctile<T> *a) {
@@ -361,7 +359,7 @@ __device__ __forceinline__ void panel_gram(const double *tab, int lane, int off,
   T x[NT][16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    const double *row = tab + (off + dir * (16 * (e >> 2) + 4 * lk + (e & 3))) * 32;
+    const double *row = tab + (off + dir * (16 * (e >> 2) + mfma_row<T>(lk, e & 3))) * 32;
 #pragma unroll
     for (int rt = 0; rt < NT; ++rt) {
       const int r = 16 * rt + rowstr<T>(li);
@@ -370,36 +368,29 @@ __device__ __forceinline__ void panel_gram(const double *tab, int lane, int off,
     }
   }
 #pragma unroll
-  for (int rt = 0; rt < NT; ++rt) a[rt].zero();
-#pragma unroll
   for (int e = 0; e < 16; ++e)
 #pragma unroll
     for (int rt = 0; rt < NT; ++rt) tile_fma<T>(a[rt], x[rt][e], B[e >> 2].re[e & 3], B[e >> 2].im[e & 3]);
 }
-// c -= G a for R x R G ([column][row]), in LDS or in global memory
+// c -= (row tile rt of G) a for R x R G ([column][row]), in LDS or in global memory
 template <typename T, int NE, bool LDS>
-__device__ __forceinline__ void small_fms(const c_t<T> *G, int lane, int R, const ctile<T> *a, ctile<T> *c) {
-  constexpr int NT = (NE + 3) / 4;
-  const int li = lane & 15, lk = lane >> 4;
-  c_t<T> g[NT][NE];
+__device__ __forceinline__ void small_fms(const c_t<T> *G, int lane, int R, int rt, const ctile<T> *a, ctile<T> &c) {
+  const int r = 16 * rt + rowstr<T>(lane & 15), lk = lane >> 4;
+  c_t<T> g[NE];
 #pragma unroll
-  for (int e = 0; e < NE; ++e)
+  for (int e = 0; e < NE; ++e) {
+    const int cc = 4 * e + lk;
+    const c_t<T> *at = G + (r < R && cc < R ? cc * R + r : 0), v = LDS ? *at : cload<T>(at);
+    g[e] = mk<T>(r < R ? v.x : (T)0, r < R ? v.y : (T)0);
+  }
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt) {
-      const int r = 16 * rt + rowstr<T>(li), cc = 4 * e + lk;
-      const c_t<T> *at = G + (r < R && cc < R ? cc * R + r : 0), v = LDS ? *at : cload<T>(at);
-      g[rt][e] = mk<T>(r < R ? v.x : (T)0, r < R ? v.y : (T)0);
-    }
-#pragma unroll
-  for (int e = 0; e < NE; ++e)
-#pragma unroll
-    for (int rt = 0; rt < NT; ++rt) tile_fms<T>(c[rt], g[rt][e], a[e >> 2].re[e & 3], a[e >> 2].im[e & 3]);
+  for (int e = 0; e < NE; ++e) tile_fms<T>(c, g[e], a[e >> 2].re[e & 3], a[e >> 2].im[e & 3]);
 }
 // B -= W' z over the 64 rows of a panel (W: its R columns)
 template <typename T, int NE>
 __device__ __forceinline__ void panel_update(const c_t<T> *W, int lane, int R, const ctile<T> *z, ctile<T> *B) {
   const int li = lane & 15, lk = lane >> 4;
-  W += rowperm<T>(li);
+  W += li;
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
     const int cc = 4 * e + lk;
@@ -410,12 +401,57 @@ __device__ __forceinline__ void panel_update(const c_t<T> *W, int lane, int R, c
     for (int mt = 0; mt < 4; ++mt) tile_fms<T>(B[mt], w[mt], z[e >> 2].re[e & 3], z[e >> 2].im[e & 3]);
   }
 }
+// W <- mc W Q, R x R Q in LDS, over 16 rows of n panels
+template <typename T, int NE>
+__device__ __forceinline__ void scale_rows(c_t<T> *W, int n, int R, const c_t<T> *Q, c_t<T> mc, int lane) {
+  constexpr int NT = (NE + 3) / 4;
+  const int li = lane & 15, lk = lane >> 4;
+  c_t<T> q[NT][NE];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int c = 16 * ct + li, r = 4 * e + lk;
+      const bool in = c < R && r < R;
+      const c_t<T> b = hmul<T>(mc, Q[in ? c * R + r : 0]);
+      q[ct][e] = mk<T>(in ? b.x : (T)0, in ? b.y : (T)0);
+    }
+#pragma unroll 1
+  for (int pp = 0; pp < n; ++pp, W += R * HP) {
+    c_t<T> a[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) a[e] = cload<T>(W + (4 * e + lk < R ? 4 * e + lk : 0) * HP + li);
+    ctile<T> o[NT];
+    zero_tiles<T, NT>(o);
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) tile_fma<T>(o[ct], a[e], q[ct][e].x, q[ct][e].y);
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct)
+      if (16 * ct + li < R) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) W[(16 * ct + li) * HP + mfma_row<T>(lk, v)] = mk<T>(o[ct].re[v], o[ct].im[v]);
+      }
+  }
+}
+template <typename T>
+__device__ __forceinline__ void panel_load(const c_t<T> *in, ctile<T> *B) {
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const c_t<T> x = cload<T>(in + 16 * mt + mfma_row<T>(0, v));
+      B[mt].re[v] = x.x;
+      B[mt].im[v] = x.y;
+    }
+}
 template <typename T>
 __device__ __forceinline__ void panel_store(c_t<T> *o, const ctile<T> *B) {
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[16 * mt + v] = mk<T>(B[mt].re[v], B[mt].im[v]);
+    for (int v = 0; v < 4; ++v) o[16 * mt + mfma_row<T>(0, v)] = mk<T>(B[mt].re[v], B[mt].im[v]);
 }
 
 template <typename T>
@@ -445,7 +481,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
     for (int I = 0; I < 4; ++I)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int i = 16 * I + 4 * lk + v, row = p * HP + i, dd = i - cl;
+        const int i = 16 * I + mfma_row<T>(lk, v), row = p * HP + i, dd = i - cl;
         const bool in = row < m;
         const double dp = d.scale * gld(d.dp + (in ? row : 0)), dm = d.scale * gld(d.dm + (in ? row : 0));
         const double Jv = fma(dp, gt[dd + 64], dm * gt[64 - dd]), J = in && incol ? Jv : 0.0;
@@ -458,10 +494,10 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
         X[I].im[v] = (T)im;
       }
   }
-  T dpr[4], dmr[4];  // d+- at rows 16 mt + rowperm(li), for the Newton step
+  T dpr[4], dmr[4];  // d+- at rows 16 mt + li, for the Newton step
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
-    const int row = p * HP + 16 * mt + rowperm<T>(li);
+    const int row = p * HP + 16 * mt + li;
     dpr[mt] = row < m ? (T)(d.scale * gld(d.dp + (row < m ? row : 0))) : (T)0;
     dmr[mt] = row < m ? (T)(d.scale * gld(d.dm + (row < m ? row : 0))) : (T)0;
   }
@@ -472,21 +508,21 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
 #pragma unroll
       for (int I = 0; I < 4; ++I)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) buf[lx(li, 16 * ((J + I) & 3) + 4 * lk + v)] = mk<T>(X[I].re[v], X[I].im[v]);
+        for (int v = 0; v < 4; ++v) buf[lx(li, 16 * ((J + I) & 3) + mfma_row<T>(lk, v))] = mk<T>(X[I].re[v], X[I].im[v]);
     }
     lds_barrier();
     if (mine) {
       const bool own = w == J;
       c_t<T> P[4];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) P[s] = buf[lx(4 * lk + s, 16 * J + rowperm<T>(li))];
+      for (int s = 0; s < 4; ++s) P[s] = buf[lx(mfma_row<T>(lk, s), 16 * J + li)];
       gj16<T>(P, lane);
       // P times this wavefront's block row; the pivot block itself becomes P, the rest of its column -A P
       ctile<T> B;
       B.zero();
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const T one = 4 * lk + s == li ? (T)1 : (T)0;
+        const T one = mfma_row<T>(lk, s) == li ? (T)1 : (T)0;
         tile_fma<T>(B, P[s], own ? one : X[0].re[s], own ? (T)0 : X[0].im[s]);
       }
 #pragma unroll
@@ -494,7 +530,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
         if (own) X[I].zero();
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          tile_fms<T>(X[I], buf[lx(4 * lk + s, 16 * ((J + I) & 3) + rowperm<T>(li))], B.re[s], B.im[s]);
+          tile_fms<T>(X[I], buf[lx(mfma_row<T>(lk, s), 16 * ((J + I) & 3) + li)], B.re[s], B.im[s]);
         X[I - 1] = X[I];
       }
       X[3] = B;
@@ -505,13 +541,13 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
   if (mine) {  // E = I - K X; X into LDS
     const c_t<T> lam = mk<T>((T)d.lam[k].x, (T)d.lam[k].y);
     T chk = (T)0;
-    // g_{i-j+1} and g_{j-i+1} for row i = 16 mt + rowperm(li), column j = 16 t + 4 lk + s.  Rows j of X
+    // g_{i-j+1} and g_{j-i+1} for row i = 16 mt + li, column j = 16 t + mfma_row(lk, s).  Rows j of X
     // from m on are zero in the columns before m, and E is only taken there.
-    const double *gp = gt + 64 + rowperm<T>(li) - 4 * lk, *gm = gt + 64 - rowperm<T>(li) + 4 * lk;
+    const double *gp = gt + 64 + li - mfma_row<T>(lk, 0), *gm = gt + 64 - li + mfma_row<T>(lk, 0);
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + 4 * lk + v)] = mk<T>(X[mt].re[v], X[mt].im[v]);
+      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + mfma_row<T>(lk, v))] = mk<T>(X[mt].re[v], X[mt].im[v]);
       E[mt].zero();
     }
 #pragma unroll
@@ -519,7 +555,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
       const int t = e >> 2, s = e & 3;
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        const T J = fma(dpr[mt], (T)gp[16 * (mt - t) - s], dmr[mt] * (T)gm[16 * (t - mt) + s]);
+        const T J = fma(dpr[mt], (T)gp[16 * (mt - t) - mfma_row<T>(0, s)], dmr[mt] * (T)gm[16 * (t - mt) + mfma_row<T>(0, s)]);
         tile_fma<T>(E[mt], J, X[t].re[s], X[t].im[s]);
       }
       chk += X[t].re[s] + X[t].im[s];
@@ -529,7 +565,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int r = 16 * mt + 4 * lk + v;
+        const int r = 16 * mt + mfma_row<T>(lk, v);
         c_t<T> t = mk<T>(r == cl ? (T)1 : (T)0, (T)0);
         t = hfms<T>(lam, mk<T>(X[mt].re[v], X[mt].im[v]), t);
         t = hfms<T>(mc, mk<T>(E[mt].re[v], E[mt].im[v]), t);
@@ -546,7 +582,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
       c.zero();
 #pragma unroll
       for (int e = 0; e < 16; ++e)
-        tile_fma<T>(c, LX[lx(16 * (e >> 2) + 4 * lk + (e & 3), 16 * mt + rowperm<T>(li))], E[e >> 2].re[e & 3],
+        tile_fma<T>(c, LX[lx(16 * (e >> 2) + mfma_row<T>(lk, e & 3), 16 * mt + li)], E[e >> 2].re[e & 3],
                     E[e >> 2].im[e & 3]);
       X[mt].re += c.re;
       X[mt].im += c.im;
@@ -557,7 +593,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + 4 * lk + v)] = mk<T>(X[mt].re[v], X[mt].im[v]);
+      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + mfma_row<T>(lk, v))] = mk<T>(X[mt].re[v], X[mt].im[v]);
   }
   lds_barrier();
   if (mine) {
@@ -580,7 +616,8 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
     if (tile) {
       ctile<T> W[4];
       leaf_tile<T>(d, LX, lane, p, 0, col < R ? col : 0, col < R, W);
-      if (col < R) panel_store<T>(W0 + ((size_t)p * R + col) * HP + 4 * lk, W);
+      if (col < R) panel_store<T>(W0 + ((size_t)p * R + col) * HP + mfma_row<T>(lk, 0), W);
+      zero_tiles<T, NT>(g);
       panel_gram<T, NE>(hier_x(d, 0), lane, leaf ? 0 : HP - 1, leaf ? 1 : -1, R, W, g);
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
@@ -603,7 +640,8 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
           c[rt].re[v] = 16 * rt + 4 * v + lk == col ? (T)1 : (T)0;
           c[rt].im[v] = (T)0;
         }
-      small_fms<T, NE, true>(LM + (1 - leaf) * R * R, lane, R, g, c);
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) small_fms<T, NE, true>(LM + (1 - leaf) * R * R, lane, R, rt, g, c[rt]);
     }
     lds_barrier();
     if (tile && col < R) {
@@ -614,28 +652,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
     lds_barrier();
     group_invert<T>(Ml, R, w, pcol, piv[leaf], bad);
     lds_barrier();
-    {  // W_0' = W_0 (-c (I - G_other G_own)^{-1}), rows 16 w .. + 15
-      c_t<T> *Wp = W0 + (size_t)p * R * HP + 16 * w;
-      c_t<T> a[NE];
-#pragma unroll
-      for (int e = 0; e < NE; ++e) a[e] = cload<T>(Wp + (4 * e + lk < R ? 4 * e + lk : 0) * HP + rowperm<T>(li));
-#pragma unroll
-      for (int ct = 0; ct < NT; ++ct) {
-        const int cc = 16 * ct + li;
-        ctile<T> o;
-        o.zero();
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          const bool in = cc < R && 4 * e + lk < R;
-          const c_t<T> b = hmul<T>(mc, Ml[in ? cc * R + 4 * e + lk : 0]);
-          tile_fma<T>(o, a[e], in ? b.x : (T)0, in ? b.y : (T)0);
-        }
-        if (cc < R) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) Wp[cc * HP + 4 * lk + v] = mk<T>(o.re[v], o.im[v]);
-        }
-      }
-    }
+    scale_rows<T, NE>(W0 + (size_t)p * R * HP + 16 * w, 1, R, Ml, mc, lane);
     __syncthreads();
   }
   if (bad) *flag = 1;
@@ -655,6 +672,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
     if (act) leaf_tile<T>(d, LX, ln, p, lev, col, ok, B);
     if (live) {
       if (act) {
+        zero_tiles<T, NT>(a);
         panel_gram<T, NE>(hier_x(d, 0), ln, leaf ? 0 : HP - 1, leaf ? 1 : -1, R, B, a);
 #pragma unroll
         for (int e = 0; e < NE; ++e) xb[64 * e + ln] = a[e >> 2].re[e & 3];
@@ -675,329 +693,206 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
       if (act) {
 #pragma unroll
         for (int e = 0; e < NE; ++e) z[e >> 2].im[e & 3] = xo[64 * e + ln];
-        small_fms<T, NE, false>(G + (size_t)(1 - leaf) * R * R, ln, R, a, z);
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt) small_fms<T, NE, false>(G + (size_t)(1 - leaf) * R * R, ln, R, rt, a, z[rt]);
         panel_update<T, NE>(W0 + (size_t)p * R * HP, ln, R, z, B);
       }
       lds_barrier();
     }
-    if (act && ok) panel_store<T>(hier_w<T>(d, lev, k) + ((size_t)p * d.hR[lev] + col) * HP + 4 * (ln >> 4), B);
+    if (act && ok) panel_store<T>(hier_w<T>(d, lev, k) + ((size_t)p * d.hR[lev] + col) * HP + mfma_row<T>(ln >> 4, 0), B);
   }
 }
 
 // ------------------------------------------------------------------------------------
-// V^T B over one half of a node for two 16-column tiles: MFMA, the half's 16-row groups divided
-// between two waves (part).  Lane (j, kk) takes rows 4 kk .. + 3 of a group of column j, so its four
-// loads are consecutive.  Bc: the columns' first panel, pst their panel strides.  The partial products go to an LDS slot ([column][row], stride HS).
-template <typename T>
-__device__ __forceinline__ void hier_gram(const double *X, int h, int side, int len,
-                                          const c_t<T> *const *Bc, const int *pst, const bool *ok, int part, bool two,
-                                          c_t<T> *slot) {
-  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  acc_t<T> acc[2][2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b][0] = acc[a][b][1] = acc_t<T>{0, 0, 0, 0};
-  for (int g = part; g < (len >> 4); g += 2) {
-    const int r0 = 16 * g + 4 * lk;
-    c_t<T> b[2][4];
-    T x[2][4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int pi = side ? r0 + v : h - 1 - r0 - v;
-      x[0][v] = (T)X[(size_t)pi * 32 + li];
-      x[1][v] = two ? (T)X[(size_t)pi * 32 + 16 + li] : (T)0;
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        b[n][v] = mk<T>((T)0, (T)0);
-        if (ok[n]) b[n][v] = cload<T>(Bc[n] + (size_t)(g >> 2) * pst[n] + (r0 & 63) + v);
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        acc[0][n][0] = mfma16(x[0][v], b[n][v].x, acc[0][n][0]);
-        acc[0][n][1] = mfma16(x[0][v], b[n][v].y, acc[0][n][1]);
-        if (two) {
-          acc[1][n][0] = mfma16(x[1][v], b[n][v].x, acc[1][n][0]);
-          acc[1][n][1] = mfma16(x[1][v], b[n][v].y, acc[1][n][1]);
-        }
-      }
-  }
-#pragma unroll
-  for (int n = 0; n < 2; ++n)
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        slot[(16 * n + li) * HS + 16 * mt + mfma_row<T>(lk, v)] = mk<T>(acc[mt][n][0][v], acc[mt][n][1][v]);
-}
-
-// In-place inverses of two R x R matrices in LDS ([column][row], stride HS) by Gauss-Jordan with
-// partial pivoting: threads 0..127 the first, 128..255 the second.
-template <typename T>
-__device__ __forceinline__ void hier_invert2(c_t<T> *P1, c_t<T> *P2, int R, int (*piv)[32], bool &bad) {
-  const int sel = threadIdx.x >> 7, r = threadIdx.x & 31, cq = (threadIdx.x >> 5) & 3;
-  c_t<T> *P = sel ? P2 : P1;
-  for (int j = 0; j < R; ++j) {
-    if (cq == 0) {  // half a wavefront: the largest entry of column j at or below the diagonal
-      const c_t<T> v = P[j * HS + r];
-      T best = r >= j && r < R ? v.x * v.x + v.y * v.y : (T)-1;
-      int at = r;
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) {
-        const T ob = __shfl_xor(best, o, 32);
-        const int oa = __shfl_xor(at, o, 32);
-        if (ob > best || (ob == best && oa < at)) {
-          best = ob;
-          at = oa;
-        }
-      }
-      if (r == 0) piv[sel][j] = at;
-      bad = bad || !(best > (T)0) || !isfinite(best);
-    }
-    __syncthreads();
-    const int pr = piv[sel][j];
-    const int src = r == j ? pr : r == pr ? j : r;
-    const c_t<T> pv = P[j * HS + pr];
-    const T iv = (T)1 / (pv.x * pv.x + pv.y * pv.y);
-    const c_t<T> inv = mk<T>(pv.x * iv, -pv.y * iv);
-    const c_t<T> f = P[j * HS + src];
-    const c_t<T> fi = hmul<T>(f, inv);
-    const bool own = r == j;
-    const c_t<T> t = mk<T>(own ? -inv.x : fi.x, own ? -inv.y : fi.y);
-    c_t<T> e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int c = cq + 4 * i;
-      const c_t<T> a = P[c * HS + src], b = P[c * HS + pr];
-      const c_t<T> base = mk<T>(own ? (T)0 : a.x, own ? (T)0 : a.y);
-      e[i] = hfms<T>(t, b, base);
-      if (c == j) e[i] = mk<T>(-t.x, -t.y);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int c = cq + 4 * i;
-      if (c < R && r < R) P[c * HS + r] = e[i];
-    }
-    __syncthreads();
-  }
-  for (int j = R - 1; j >= 0; --j) {  // undo the row exchanges: exchange columns, last first
-    const int pr = piv[sel][j];
-    if (pr != j && cq == 0 && r < R) {
-      const c_t<T> a = P[j * HS + r];
-      P[j * HS + r] = P[pr * HS + r];
-      P[pr * HS + r] = a;
-    }
-  }
-  __syncthreads();
-}
-
-// One node of a level: G_1, G_2, the two R x R inverses, and W -> W' over the node's rows.
-// Item = (instance, block, node).  Waves 0, 1 the left half, 2, 3 the right.
-template <typename T>
-__global__ __launch_bounds__(256) void k_hier_node(const InstDesc *__restrict__ Dd, ItemMap map, int lev, int *flag) {
+// One node of a level from 1 on: G_1, G_2, the two R x R inverses, and W -> W' over the node's rows.
+// Item = (instance, block, node); four wavefronts per half.  For G a wavefront takes a 16-column tile
+// and every other panel, for W' 16 rows of every panel.  The columns are read twice and written once
+// (115 to 150 us a level at 4095 x 256); an inverse's R steps and, at the upper levels, too few nodes to
+// fill the chip make it 245 to 330 us FP64, 1.36 ms for five levels (mixed 0.68), from 1.77 (0.86)
+// with half the wavefronts and a barrier-and-LDS inverse.
+template <typename T, int NE>
+__global__ __launch_bounds__(512) void k_hier_node(const InstDesc *__restrict__ Dd, ItemMap map, int lev, int *flag) {
   extern __shared__ double hier_lds[];
-  c_t<T> *S = (c_t<T> *)hier_lds;  // four slots
   __shared__ int piv[2][32];
+  constexpr int NT = (NE + 3) / 4;
   const int q = item_slot(map, blockIdx.x);
   const InstDesc &d = Dd[map.ids[q]];
   const int local = blockIdx.x - map.pre[q];
   const int nodes = hier_nodes(d.mp, lev), k = local / nodes, node = local % nodes;
-  const int R = d.hR[lev], mp = d.mp, h = HP << lev;
-  const bool two = R > 16;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  const int side = w >> 1, part = w & 1;
-  const int r0 = (2 * node + side) * h, len = min(h, mp - r0);
-  c_t<T> *W = hier_w<T>(d, lev, k) + (size_t)r0 * R;
-  const c_t<T> *Bc[2] = {W + li * HP, W + (16 + li) * HP};
-  const int pst[2] = {R * HP, R * HP};
-  const bool ok[2] = {li < R, 16 + li < R};
-  hier_gram<T>(hier_x(d, lev), h, side, len, Bc, pst, ok, part, two, S + w * HSLOT);
-  __syncthreads();
-  // G_i = -c (V_i^T W_i): slots 0 (left) and 2 (right), and to memory
+  const int R = d.hR[lev], hp = 1 << lev;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int side = wv >> 2, w = wv & 3, ct = w & 1, part = w >> 1, col = 16 * ct + li;
+  const int p0 = (2 * node + side) * hp, np = min(hp, d.npan - p0);
+  // [side][part][column][row] partial sums; G and then I - G G take a side's first one
+  c_t<T> *S = (c_t<T> *)hier_lds, *M = S + side * 2 * R * R, *own = M + part * R * R, *Mo = S + (1 - side) * 2 * R * R;
+  c_t<T> *pcol = S + 4 * R * R + 64 * side;
+  c_t<T> *W = hier_w<T>(d, lev, k) + (size_t)p0 * R * HP;
   const c_t<T> mc = minus_c<T>(d, k);
-  {
-    c_t<T> *G = hier_g<T>(d, lev, k, node);
-    const int sel = threadIdx.x >> 7, r = threadIdx.x & 31, cq = (threadIdx.x >> 5) & 3;
-    c_t<T> *A = S + 2 * sel * HSLOT, *B = A + HSLOT;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int c = cq + 4 * i;
-      const c_t<T> a = A[c * HS + r], b = B[c * HS + r];
-      const c_t<T> g = hmul<T>(mc, mk<T>(a.x + b.x, a.y + b.y));
-      A[c * HS + r] = g;
-      if (c < R && r < R) G[((size_t)sel * R + c) * R + r] = g;
-    }
-    __syncthreads();
-    // slot 1: I - G_1 G_2, slot 3: I - G_2 G_1
-    const c_t<T> *Ga = S + 2 * sel * HSLOT, *Gb = S + 2 * (1 - sel) * HSLOT;
-    c_t<T> acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = mk<T>(cq + 4 * i == r ? (T)1 : (T)0, (T)0);
-    for (int t = 0; t < R; ++t) {
-      const c_t<T> a = Ga[t * HS + r];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = hfms<T>(a, Gb[(cq + 4 * i) * HS + t], acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) B[(cq + 4 * i) * HS + r] = acc[i];
-    __syncthreads();
-  }
+  const double *tab = hier_x(d, lev);
   bool bad = false;
-  hier_invert2<T>(S + HSLOT, S + 3 * HSLOT, R, piv, bad);
-  if (bad) *flag = 1;
-  // W_1' = W_1 (-c (I - G_2 G_1)^{-1}), W_2' = W_2 (-c (I - G_1 G_2)^{-1}): in place, 16 rows at a time
-  const c_t<T> *Q = S + (side == 0 ? 3 : 1) * HSLOT;
-  c_t<T> qb[2][8];
-#pragma unroll
-  for (int n = 0; n < 2; ++n)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qb[n][s] = hmul<T>(mc, Q[(16 * n + li) * HS + 4 * s + lk]);
-  for (int g = part; g < (len >> 4); g += 2) {
-    c_t<T> a[8];
-    auto *Wg = W + (size_t)(g >> 2) * R * HP + 16 * (g & 3);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      a[s] = mk<T>((T)0, (T)0);
-      if (4 * s < R) a[s] = cload<T>(Wg + (4 * s + lk) * HP + rowperm<T>(li));
-    }
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      if (n == 1 && !two) break;
-      acc_t<T> re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if (4 * s < R) {
-          re = mfma16(a[s].x, qb[n][s].x, re);
-          re = mfma16(-a[s].y, qb[n][s].y, re);
-          im = mfma16(a[s].x, qb[n][s].y, im);
-          im = mfma16(a[s].y, qb[n][s].x, im);
-        }
-      }
-      if (16 * n + li < R) {
-        c_t<T> *o = Wg + (16 * n + li) * HP + 4 * lk;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = mk<T>(re[v], im[v]);
-      }
-    }
+  ctile<T> g[NT], c;
+  zero_tiles<T, NT>(g);
+#pragma unroll 1
+  for (int pp = part; pp < np; pp += 2) {
+    ctile<T> B[4];
+    panel_load<T>(W + ((size_t)pp * R + (col < R ? col : 0)) * HP + mfma_row<T>(lk, 0), B);
+    panel_gram<T, NE>(tab, lane, side ? pp * HP : (hp - pp) * HP - 1, side ? 1 : -1, R, B, g);
   }
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+    if (col < R && 4 * e + lk < R) own[col * R + 4 * e + lk] = mk<T>(g[e >> 2].re[e & 3], g[e >> 2].im[e & 3]);
+  lds_barrier();
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const bool in = col < R && 4 * e + lk < R;
+    const int at = in ? col * R + 4 * e + lk : 0;
+    const c_t<T> a = M[at], b = M[R * R + at];
+    const c_t<T> t = hmul<T>(mc, mk<T>(a.x + b.x, a.y + b.y));
+    g[e >> 2].re[e & 3] = in ? t.x : (T)0;
+    g[e >> 2].im[e & 3] = in ? t.y : (T)0;
+  }
+  lds_barrier();
+  if (part == 0) {
+    c_t<T> *G = hier_g<T>(d, lev, k, node) + (size_t)side * R * R;
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+      if (col < R && 4 * e + lk < R)
+        G[col * R + 4 * e + lk] = M[col * R + 4 * e + lk] = mk<T>(g[e >> 2].re[e & 3], g[e >> 2].im[e & 3]);
+  }
+  lds_barrier();
+  // I - G_other G_own, row tile `part`
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    c.re[v] = 16 * part + 4 * v + lk == col ? (T)1 : (T)0;
+    c.im[v] = (T)0;
+  }
+  small_fms<T, NE, true>(Mo, lane, R, part, g, c);
+  lds_barrier();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int r = 16 * part + 4 * v + lk;
+    if (col < R && r < R) M[col * R + r] = mk<T>(c.re[v], c.im[v]);
+  }
+  lds_barrier();
+  group_invert<T>(M, R, w, pcol, piv[side], bad);
+  if (bad) *flag = 1;
+  __syncthreads();
+  // W_1' = W_1 (-c (I - G_2 G_1)^{-1}), W_2' = W_2 (-c (I - G_1 G_2)^{-1})
+  scale_rows<T, NE>(W + 16 * w, np, R, M, mc, lane);
 }
 
-// The columns of the levels above `lev` through that level's elimination: 32 columns B of a node,
+// The columns of the levels above `lev` through that level's elimination,
 //   B_1 -= W_1' (A_2 - G_2 A_1),  B_2 -= W_2' (A_1 - G_1 A_2),  A_i = V_i^T B_i.
-// Item = (instance, block, node, 32-column chunk of those levels' columns).
-template <typename T>
-__global__ __launch_bounds__(256) void k_hier_cols(const InstDesc *__restrict__ Dd, ItemMap map, int lev) {
+// Item = (instance, block, node, 16-column tile of those columns); SW wavefronts per half, a panel's
+// 64 x 16 tile at a time.  Up to PP panels of a wavefront stay in its registers between the two
+// products, so a column is read once and written once (PP = 0, the levels of more than 16 panels a
+// node, reads it twice).  The tiles of a node follow each other eight items apart, on one XCD: its W'
+// and G come from that L2 after the first.  The products and the passes over the columns take about as
+// long as each other (317 us and 370 us at level 1 of 4095 x 256 FP64, of 658); all levels from 1 on
+// 1.99 ms (mixed 0.69), from 2.50 (0.96) with 32 columns a workgroup read twice.
+template <typename T, int NE, int SW, int PP>
+__global__ __launch_bounds__(SW * 128) void k_hier_cols(const InstDesc *__restrict__ Dd, ItemMap map, int lev) {
   extern __shared__ double hier_lds[];
-  c_t<T> *S = (c_t<T> *)hier_lds;
+  constexpr int NT = (NE + 3) / 4;
   const int q = item_slot(map, blockIdx.x);
   const InstDesc &d = Dd[map.ids[q]];
   const int local = blockIdx.x - map.pre[q];
   int ncol = 0;
   for (int l = lev + 1; l < d.nlev; ++l) ncol += d.hR[l];
-  const int chunks = (ncol + 31) / 32, nodes = hier_nodes(d.mp, lev);
-  const int ch = local % chunks, kn = local / chunks, k = kn / nodes, node = kn % nodes;
-  const int R = d.hR[lev], mp = d.mp, h = HP << lev;
-  const bool two = R > 16;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  const int side = w >> 1, part = w & 1;
-  const int r0 = (2 * node + side) * h, len = min(h, mp - r0);
-  c_t<T> *Bc[2];
-  int pst[2];
-  bool ok[2];
+  const int chunks = (ncol + 15) / 16, nodes = hier_nodes(d.mp, lev);
+  const int base = local / (8 * chunks) * 8, cnt = min(8, d.nb * nodes - base), rem = local - base * chunks;
+  const int kn = base + rem % cnt, ch = rem / cnt, k = kn / nodes, node = kn % nodes;
+  const int R = d.hR[lev], hp = 1 << lev;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int side = wv / SW, w = wv % SW;
+  const int p0 = (2 * node + side) * hp, np = min(hp, d.npan - p0);
+  int col = 16 * ch + li, l = lev + 1;
+  const bool ok = col < ncol;
+  if (!ok) col = 0;
+  while (col >= d.hR[l]) col -= d.hR[l++];
+  const size_t pst = (size_t)d.hR[l] * HP;
+  c_t<T> *Bc = hier_w<T>(d, l, k) + (size_t)p0 * pst + col * HP + mfma_row<T>(lk, 0);
+  const c_t<T> *W = hier_w<T>(d, lev, k) + (size_t)p0 * R * HP;
+  const double *tab = hier_x(d, lev);
+  // partial A [side][w][e][lane], later z [side][e][lane]; A [side][e][lane]
+  c_t<T> *S = (c_t<T> *)hier_lds, *A = S + 2 * SW * NE * 64;
+  constexpr int HELD = PP > 0 ? PP : 1;
+  ctile<T> B[HELD][4], a[NT], z[NT];
+  zero_tiles<T, NT>(a);
+  auto gram = [&](int pp, const ctile<T> *b) {
+    panel_gram<T, NE>(tab, lane, side ? pp * HP : (hp - pp) * HP - 1, side ? 1 : -1, R, b, a);
+  };
+  if constexpr (PP > 0) {
 #pragma unroll
-  for (int n = 0; n < 2; ++n) {
-    int col = 32 * ch + 16 * n + li, l = lev + 1;
-    ok[n] = col < ncol;
-    if (!ok[n]) col = 0;
-    while (col >= d.hR[l]) col -= d.hR[l++];
-    pst[n] = d.hR[l] * HP;
-    Bc[n] = hier_w<T>(d, l, k) + (size_t)(r0 >> 6) * pst[n] + col * HP;
-  }
-  const c_t<T> *Br[2] = {Bc[0], Bc[1]};
-  hier_gram<T>(hier_x(d, lev), h, side, len, Br, pst, ok, part, two, S + w * HSLOT);
-  __syncthreads();
-  {  // A_1 into slot 0, A_2 into slot 2
-    const int sel = threadIdx.x >> 7, r = threadIdx.x & 31, cq = (threadIdx.x >> 5) & 3;
-    c_t<T> *A = S + 2 * sel * HSLOT;
+    for (int u = 0; u < PP; ++u)
+      if (w + SW * u < np) panel_load<T>(Bc + (w + SW * u) * pst, B[u]);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int e = (cq + 4 * i) * HS + r;
-      const c_t<T> a = A[e], b = A[HSLOT + e];
-      A[e] = mk<T>(a.x + b.x, a.y + b.y);
+    for (int u = 0; u < PP; ++u)
+      if (w + SW * u < np) gram(w + SW * u, B[u]);
+  } else {
+#pragma unroll 1
+    for (int pp = w; pp < np; pp += SW) {
+      panel_load<T>(Bc + pp * pst, B[0]);
+      gram(pp, B[0]);
     }
   }
-  __syncthreads();
-  {  // slot 1: A_2 - G_2 A_1 (waves 0, 1: one column tile each), slot 3: A_1 - G_1 A_2 (waves 2, 3)
-    const c_t<T> *G = hier_g<T>(d, lev, k, node) + (size_t)(1 - side) * R * R;
-    const c_t<T> *Am = S + 2 * side * HSLOT, *Ao = S + 2 * (1 - side) * HSLOT;
-    c_t<T> *To = S + (1 + 2 * side) * HSLOT;
-    acc_t<T> acc[2][2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) acc[a][0] = acc[a][1] = acc_t<T>{0, 0, 0, 0};
+  for (int e = 0; e < NE; ++e) S[(wv * NE + e) * 64 + lane] = mk<T>(a[e >> 2].re[e & 3], a[e >> 2].im[e & 3]);
+  lds_barrier();
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      if (4 * s < R) {
-        const c_t<T> b = Am[(16 * part + li) * HS + 4 * s + lk];
+  for (int e = w; e < NE; e += SW) {
+    c_t<T> t = S[(side * SW * NE + e) * 64 + lane];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          c_t<T> a = mk<T>((T)0, (T)0);
-          if (16 * mt + li < R) a = cload<T>(G + (size_t)(4 * s + lk) * R + 16 * mt + li);
-          acc[mt][0] = mfma16(a.x, b.x, acc[mt][0]);
-          acc[mt][0] = mfma16(-a.y, b.y, acc[mt][0]);
-          acc[mt][1] = mfma16(a.x, b.y, acc[mt][1]);
-          acc[mt][1] = mfma16(a.y, b.x, acc[mt][1]);
-        }
-      }
+    for (int i = 1; i < SW; ++i) {
+      const c_t<T> v = S[((side * SW + i) * NE + e) * 64 + lane];
+      t.x += v.x;
+      t.y += v.y;
     }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int e = (16 * part + li) * HS + 16 * mt + mfma_row<T>(lk, v);
-        const c_t<T> a = Ao[e];
-        To[e] = mk<T>(a.x - acc[mt][0][v], a.y - acc[mt][1][v]);
-      }
+    A[(side * NE + e) * 64 + lane] = t;
   }
-  __syncthreads();
-  const c_t<T> *Tm = S + (1 + 2 * side) * HSLOT;
-  c_t<T> tb[2][8];
+  lds_barrier();
+  if (w < NT) {  // row tile w of A_other - G_other A_own
+    ctile<T> o[NT];
+    zero_tiles<T, NT>(a);
 #pragma unroll
-  for (int n = 0; n < 2; ++n)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) tb[n][s] = Tm[(16 * n + li) * HS + 4 * s + lk];
-  const c_t<T> *W = hier_w<T>(d, lev, k) + (size_t)r0 * R;
-  for (int g = part; g < (len >> 4); g += 2) {
-    c_t<T> a[8];
-    auto *Wg = W + (size_t)(g >> 2) * R * HP + 16 * (g & 3);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      a[s] = mk<T>((T)0, (T)0);
-      if (4 * s < R) a[s] = cload<T>(Wg + (4 * s + lk) * HP + rowperm<T>(li));
+    for (int e = 0; e < NE; ++e) {
+      const c_t<T> t = A[(side * NE + e) * 64 + lane];
+      a[e >> 2].re[e & 3] = t.x;
+      a[e >> 2].im[e & 3] = t.y;
     }
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      c_t<T> o[4];
-      c_t<T> *po = Bc[n] + (size_t)(g >> 2) * pst[n] + 16 * (g & 3) + 4 * lk;
-      if (ok[n])
+    for (int v = 0; v < 4; ++v) {
+      const int e = min(4 * w + v, NE - 1);
+      const c_t<T> t = A[((1 - side) * NE + e) * 64 + lane];
+      o[0].re[v] = t.x;
+      o[0].im[v] = t.y;
+    }
+    small_fms<T, NE, false>(hier_g<T>(d, lev, k, node) + (size_t)(1 - side) * R * R, lane, R, w, a, o[0]);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = cload<T>(po + v);
-      acc_t<T> re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    for (int v = 0; v < 4; ++v)
+      if (4 * w + v < NE) S[(side * NE + 4 * w + v) * 64 + lane] = mk<T>(o[0].re[v], o[0].im[v]);
+  }
+  lds_barrier();
+  zero_tiles<T, NT>(z);
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if (4 * s < R) {
-          re = mfma16(a[s].x, tb[n][s].x, re);
-          re = mfma16(-a[s].y, tb[n][s].y, re);
-          im = mfma16(a[s].x, tb[n][s].y, im);
-          im = mfma16(a[s].y, tb[n][s].x, im);
-        }
+  for (int e = 0; e < NE; ++e) {
+    const c_t<T> t = S[(side * NE + e) * 64 + lane];
+    z[e >> 2].re[e & 3] = t.x;
+    z[e >> 2].im[e & 3] = t.y;
+  }
+  if constexpr (PP > 0) {
+#pragma unroll
+    for (int u = 0; u < PP; ++u)
+      if (w + SW * u < np) {
+        panel_update<T, NE>(W + (size_t)(w + SW * u) * R * HP, lane, R, z, B[u]);
+        if (ok) panel_store<T>(Bc + (w + SW * u) * pst, B[u]);
       }
-      if (ok[n])
-#pragma unroll
-        for (int v = 0; v < 4; ++v) po[v] = mk<T>(o[v].x - re[v], o[v].y - im[v]);
+  } else {
+#pragma unroll 1
+    for (int pp = w; pp < np; pp += SW) {
+      panel_load<T>(Bc + pp * pst, B[0]);
+      panel_update<T, NE>(W + (size_t)pp * R * HP, lane, R, z, B[0]);
+      if (ok) panel_store<T>(Bc + pp * pst, B[0]);
     }
   }
 }
@@ -1272,23 +1167,47 @@ hipError_t launch_hier_leaf(const InstDesc *D, const ItemMap &map, int items, in
   hipLaunchKernelGGL(k_hier_leaf<T>, dim3(items), dim3(512), lds, st, D, map, flag);
   return hipGetLastError();
 }
-template <typename T>
-hipError_t launch_hier_node(const InstDesc *D, const ItemMap &map, int items, int lev, int *flag, hipStream_t st) {
-  if (items <= 0) return hipSuccess;
-  const size_t lds = 4 * HSLOT * sizeof(c_t<T>);
-  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_node<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+template <typename T, int NE>
+static hipError_t hier_node_ne(const InstDesc *D, const ItemMap &map, int items, int lev, int R, int *flag, hipStream_t st) {
+  const size_t lds = (4 * R * R + 128) * sizeof(c_t<T>);
+  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_node<T, NE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hier_node<T>, dim3(items), dim3(256), lds, st, D, map, lev, flag);
+  hipLaunchKernelGGL((k_hier_node<T, NE>), dim3(items), dim3(512), lds, st, D, map, lev, flag);
   return hipGetLastError();
 }
-template <typename T>
-hipError_t launch_hier_cols(const InstDesc *D, const ItemMap &map, int items, int lev, hipStream_t st) {
-  if (items <= 0) return hipSuccess;
-  const size_t lds = 4 * HSLOT * sizeof(c_t<T>);
-  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_cols<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+template <typename T, int NE, int SW, int PP>
+static hipError_t hier_cols_at(const InstDesc *D, const ItemMap &map, int items, int lev, hipStream_t st) {
+  const size_t lds = (2 * SW + 2) * NE * 64 * sizeof(c_t<T>);
+  const hipError_t e =
+      hipFuncSetAttribute((const void *)k_hier_cols<T, NE, SW, PP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hier_cols<T>, dim3(items), dim3(256), lds, st, D, map, lev);
+  hipLaunchKernelGGL((k_hier_cols<T, NE, SW, PP>), dim3(items), dim3(128 * SW), lds, st, D, map, lev);
   return hipGetLastError();
+}
+// Two wavefronts per half at level 1 (two panels), four above; a wavefront's one or two panels in
+// registers up to level 3.
+template <typename T, int NE>
+static hipError_t hier_cols_ne(const InstDesc *D, const ItemMap &map, int items, int lev, hipStream_t st) {
+  if (lev == 1) return hier_cols_at<T, NE, 2, 1>(D, map, items, lev, st);
+  if (lev == 2) return hier_cols_at<T, NE, 4, 1>(D, map, items, lev, st);
+  if (lev == 3) return hier_cols_at<T, NE, 4, 2>(D, map, items, lev, st);
+  return hier_cols_at<T, NE, 4, 0>(D, map, items, lev, st);
+}
+// R: the level's largest rank in the launch.  Products run over 4 NE rows, so NE follows it in steps of
+// 8 rows.
+template <typename T>
+hipError_t launch_hier_node(const InstDesc *D, const ItemMap &map, int items, int lev, int R, int *flag, hipStream_t st) {
+  if (items <= 0) return hipSuccess;
+  if (R <= 16) return hier_node_ne<T, 4>(D, map, items, lev, R, flag, st);
+  if (R <= 24) return hier_node_ne<T, 6>(D, map, items, lev, R, flag, st);
+  return hier_node_ne<T, 8>(D, map, items, lev, R, flag, st);
+}
+template <typename T>
+hipError_t launch_hier_cols(const InstDesc *D, const ItemMap &map, int items, int lev, int R, hipStream_t st) {
+  if (items <= 0) return hipSuccess;
+  if (R <= 16) return hier_cols_ne<T, 4>(D, map, items, lev, st);
+  if (R <= 24) return hier_cols_ne<T, 6>(D, map, items, lev, st);
+  return hier_cols_ne<T, 8>(D, map, items, lev, st);
 }
 template <typename T>
 hipError_t launch_hier_sub(const InstDesc *D, const ItemMap &map, int items, hipStream_t st) {
@@ -1305,8 +1224,8 @@ hipError_t launch_hier_up(const InstDesc *D, const ItemMap &map, int items, int 
 
 #define HIER_INST(T)                                                                                       \
   template hipError_t launch_hier_leaf<T>(const InstDesc *, const ItemMap &, int, int *, hipStream_t);     \
-  template hipError_t launch_hier_node<T>(const InstDesc *, const ItemMap &, int, int, int *, hipStream_t); \
-  template hipError_t launch_hier_cols<T>(const InstDesc *, const ItemMap &, int, int, hipStream_t);       \
+  template hipError_t launch_hier_node<T>(const InstDesc *, const ItemMap &, int, int, int, int *, hipStream_t); \
+  template hipError_t launch_hier_cols<T>(const InstDesc *, const ItemMap &, int, int, int, hipStream_t);  \
   template hipError_t launch_hier_sub<T>(const InstDesc *, const ItemMap &, int, hipStream_t);        \
   template hipError_t launch_hier_up<T>(const InstDesc *, const ItemMap &, int, int, hipStream_t);
 HIER_INST(double)

@@ -203,14 +203,14 @@ hipError_t launch_qgemm(const InstDesc *D, const ItemMap &map, int items, int tr
 
 // ---- the blocks in hierarchical form (k_hier.hip) ----
 // items: leaf (leaf inverses, W of all levels, level 0) nb ceil(npan / 2) per instance; for the
-// levels from 1 on, node nb nodes(lev) and cols nb nodes(lev) times the 32-column chunks of the
-// higher levels' columns
+// levels from 1 on, node nb nodes(lev) and cols nb nodes(lev) times the 16-column tiles of the
+// higher levels' columns; R the level's largest rank of the instances
 template <typename T>
 hipError_t launch_hier_leaf(const InstDesc *D, const ItemMap &map, int items, int *flag, hipStream_t st);
 template <typename T>
-hipError_t launch_hier_node(const InstDesc *D, const ItemMap &map, int items, int lev, int *flag, hipStream_t st);
+hipError_t launch_hier_node(const InstDesc *D, const ItemMap &map, int items, int lev, int R, int *flag, hipStream_t st);
 template <typename T>
-hipError_t launch_hier_cols(const InstDesc *D, const ItemMap &map, int items, int lev, hipStream_t st);
+hipError_t launch_hier_cols(const InstDesc *D, const ItemMap &map, int items, int lev, int R, hipStream_t st);
 // Vh <- the block solves, in place: `sub` does the leaves and the levels 0 and 1 in chunks of
 // HIER_CHUNK panels, then `up` the levels from 2 on, one each; items nb ceil(npan / HIER_CHUNK)
 template <typename T>

@@ -1835,7 +1835,7 @@ static fde_status hier_factor(Plan *P) {
   for (int l = 1; l < nlev; ++l) {
     hm.push_back(fill([&](const fde_bvm *h) { return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) : 0; }));
     hm.push_back(fill([&](const fde_bvm *h) {
-      return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) * ((higher(h, l) + 31) / 32) : 0;
+      return l < h->nlev ? h->nb * hier_nodes_p(h->npan, l) * ((higher(h, l) + 15) / 16) : 0;
     }));
   }
   std::vector<ItemMap> dm;
@@ -1843,9 +1843,12 @@ static fde_status hier_factor(Plan *P) {
   HIPCHK(run(L, "hier_leaf", wleaf, [&] { return launch_hier_leaf<T>(P->d_desc, dm[0], hm[0].items, P->d_flag, st); }));
   for (int l = 1; l < nlev; ++l) {
     const size_t a = 2 * l - 1, b = a + 1;
-    HIPCHK(run(L, "hier_node", wnode[l], [&] { return launch_hier_node<T>(P->d_desc, dm[a], hm[a].items, l, P->d_flag, st); }));
+    int R = 0;
+    for (const fde_bvm *h : P->hs)
+      if (h->hier && l < h->nlev) R = std::max(R, h->hR[l]);
+    HIPCHK(run(L, "hier_node", wnode[l], [&] { return launch_hier_node<T>(P->d_desc, dm[a], hm[a].items, l, R, P->d_flag, st); }));
     if (hm[b].items > 0)
-      HIPCHK(run(L, "hier_cols", wcols[l], [&] { return launch_hier_cols<T>(P->d_desc, dm[b], hm[b].items, l, st); }));
+      HIPCHK(run(L, "hier_cols", wcols[l], [&] { return launch_hier_cols<T>(P->d_desc, dm[b], hm[b].items, l, R, st); }));
   }
   return FDE_OK;
 }
