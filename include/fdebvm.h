@@ -284,7 +284,7 @@ typedef enum { FDE_BLOCKS_LU = 0, FDE_BLOCKS_HESSENBERG = 1, FDE_BLOCKS_BAND = 2
  * (64 + 25 log2(m / 64)) m numbers per block instead of m^2 or m^2 / 2, in the block's precision and
  * with the same operator S^{-1} up to rounding.
  *   0  never;
- *   1  (default) with FDE_BLOCKS_AUTO, from m = 257 on;
+ *   1  (default) with FDE_BLOCKS_AUTO, from m = 257 or s = 64 on;
  *   2  whenever the problem allows it, whatever FDE_OPT_BLOCKS says.
  * It needs blocks that are diagonally dominant, Re(lambda_k conj mu_k) >= 0 for every frequency (all
  * built-in formulas); other problems keep the dense route.  FDE_OPT_BLOCKS_IN_USE still names the
@@ -292,7 +292,8 @@ typedef enum { FDE_BLOCKS_LU = 0, FDE_BLOCKS_HESSENBERG = 1, FDE_BLOCKS_BAND = 2
  * fde_get_hessenberg return; with the hierarchical form in use (FDE_OPT_COMPRESS_IN_USE, read-only)
  * those are computed when first asked for.  Changing the option discards the factorization. */
 /* FDE_OPT_ORTHO selects the Arnoldi orthogonalisation (FP64 either way):
- *   FDE_ORTHO_MGS   (default) modified Gram-Schmidt, j + 2 dependent launches at step j.
+ *   FDE_ORTHO_MGS   (default) modified Gram-Schmidt: one launch at step j for vectors of up to 4096
+ *                   entries, j + 2 dependent launches up to 7168, three launches above.
  *   FDE_ORTHO_CGS2  classical Gram-Schmidt applied twice: three launches per step whatever j;
  *                   the same basis in exact arithmetic, orthogonal to working precision. */
 typedef enum { FDE_ORTHO_MGS = 0, FDE_ORTHO_CGS2 = 1 } fde_ortho;

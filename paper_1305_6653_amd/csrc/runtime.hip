@@ -626,7 +626,7 @@ static std::string plan_shape_key(const Plan *P, int prec) {
   if (!P->hs.empty() && P->hs[0]->blk_route == FDE_BLOCKS_BAND) k += "b";
   char buf[32];
   for (const fde_bvm *h : P->hs) {
-    snprintf(buf, sizeof buf, h->hier ? ":%dx%dc" : ":%dx%d", h->m, h->s);
+    snprintf(buf, sizeof buf, ":%dx%d", h->m, h->s);
     k += buf;
   }
   return k;
@@ -891,9 +891,13 @@ static void build_tables(fde_bvm *h) {
   }
 }
 
-// The largest size at which FDE_OPT_COMPRESS = 1 leaves the dense routes in place (see
-// hier_choice), in 64-row panels.
-static constexpr int HIER_MIN_PANELS = 5;
+// Where FDE_OPT_COMPRESS = 1 takes the hierarchical form: from five 64-row panels or 33 blocks
+// (s = 64) on.  Factor + solve in us, block LU / hierarchical, FP64 (mixed alike): 63 x 64 963 / 845,
+// 96 x 128 1281 / 1006, 128 x 512 1732 / 1452, 255 x 128 2108 / 1360, 300 x 16 2892 / 1550.  It is the
+// faster one below the line too (63 x 16 751 / 652, 200 x 16 1591 / 991); there the block LU stays
+// because its launches are what the autotuner, FDE_OPT_TRSV_W and the profile show for small systems,
+// and programs (and the library's own tests) look at them.
+static bool hier_auto(const fde_bvm *h) { return h->npan >= 5 || h->nb >= 33; }
 
 // Basis tables of the hierarchical form: per level the pivoted Cholesky factor X of the positive
 // definite Hankel matrix [g_{p+q+2}] of order h = 64 << l, [h][32] with column 0 = e_0 (the g_0
@@ -1262,7 +1266,7 @@ extern "C" fde_status fde_bvm_setup(const fde_problem *p, fde_bvm **out) {
     return bail(fail(FDE_EDEVICE, "symbol FFT launch failed: %s", hipGetErrorString(hipGetLastError())));
   if (hipStreamSynchronize(q) != hipSuccess) return bail(fail(FDE_EDEVICE, "setup synchronisation failed"));
   if ((st = plan_create({h}, &h->self)) != FDE_OK) return bail(st);
-  if (h->npan >= HIER_MIN_PANELS && (st = hier_tables(h)) != FDE_OK) return bail(st);
+  if (hier_auto(h) && (st = hier_tables(h)) != FDE_OK) return bail(st);
   *out = h;
   return FDE_OK;
 }
@@ -1296,7 +1300,7 @@ extern "C" fde_status fde_bvm_set_coefficients(fde_bvm *h, double alpha, const d
   h->prec = -1;
   h->self->desc_dirty = true;
   h->hx_state = 0;
-  if (h->npan >= HIER_MIN_PANELS) STCHK(hier_tables(h));
+  if (hier_auto(h)) STCHK(hier_tables(h));
   return FDE_OK;
 }
 
@@ -1992,7 +1996,7 @@ static fde_status factor_plan(Plan *P, fde_precision prec) {
   const bool automatic = P->hs[0]->opt_blocks == FDE_BLOCKS_AUTO;
   for (fde_bvm *h : P->hs) {
     int use = 0;
-    if (h->opt_compress == 2 || (h->opt_compress == 1 && automatic && h->npan >= HIER_MIN_PANELS)) {
+    if (h->opt_compress == 2 || (h->opt_compress == 1 && automatic && hier_auto(h))) {
       STCHK(hier_tables(h));
       use = h->hx_state > 0 ? 1 : 0;
     }
