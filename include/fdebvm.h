@@ -292,7 +292,7 @@ typedef enum { FDE_BLOCKS_LU = 0, FDE_BLOCKS_HESSENBERG = 1, FDE_BLOCKS_BAND = 2
  * fde_get_hessenberg return; with the hierarchical form in use (FDE_OPT_COMPRESS_IN_USE, read-only)
  * those are computed when first asked for.  Changing the option discards the factorization. */
 /* FDE_OPT_ORTHO selects the Arnoldi orthogonalisation (FP64 either way):
- *   FDE_ORTHO_MGS   (default) modified Gram-Schmidt: one launch at step j for vectors of up to 4096
+ *   FDE_ORTHO_MGS   (default) modified Gram-Schmidt: one launch at step j for vectors of up to 6144
  *                   entries, j + 2 dependent launches up to 7168, three launches above.
  *   FDE_ORTHO_CGS2  classical Gram-Schmidt applied twice: three launches per step whatever j;
  *                   the same basis in exact arithmetic, orthogonal to working precision. */

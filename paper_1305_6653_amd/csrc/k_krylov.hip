@@ -26,10 +26,11 @@ namespace fde {
 
 static constexpr int KR_NT = 256;
 // Vectors of up to KR_ONE_MAX entries form one chunk (one workgroup per reduction), which
-// lets a whole Arnoldi step run in one launch (k_arnoldi1).  Larger vectors keep chunks of
-// 1024 entries: one workgroup streaming a longer vector through a chain launch (a batch that
-// mixes sizes) would become the launch's tail.
-static constexpr size_t KR_ONE_MAX = 4096;
+// lets a whole Arnoldi step run in one launch (k_arnoldi1; 16 or 24 entries of w and of two basis
+// vectors per thread).  At 96 x 64 the steps of a table solve took j + 4 launches of 6.4 us each and
+// take one of 17 us (8 steps: 0.35 to 0.13 ms).  Larger vectors keep chunks of 1024 entries: one workgroup streaming a longer
+// vector through a chain launch (a batch that mixes sizes) would become the launch's tail.
+static constexpr size_t KR_ONE_MAX = 6144;
 
 size_t krylov_one_max() { return KR_ONE_MAX; }
 
@@ -281,8 +282,10 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_step(const InstDesc *__restrict__
 // are kept from earlier steps) are taken in one pass, and w -= V h in a second.  No orthogonality
 // of V is assumed, so the loss of orthogonality is corrected as MGS corrects it.  Launches per
 // step: 3 (with v_{j+1}) instead of j + 4, and every basis vector is read twice instead of w, v_i
-// and v_{i-1} being read and w written per projection: 255 x 128 (19 steps) 1.34 ms of j + 2
-// launches of 6.4 us, and 4095 x 256 1.66 ms.  Below WD_MIN the chain is as fast.
+// and v_{i-1} being read and w written per projection: 255 x 128 (19 steps) 1.34 to 0.45 ms, 96 x 128
+// (20 steps) 1.44 to 0.43, 4095 x 256 (17 steps) 1.66 to 0.82.  Launch latency bounds it up to about
+// 10^5 entries, the passes over V above.  Vectors of 6145 (above k_arnoldi1's) to WD_MIN entries keep
+// the chain, the form whose launches the profile of a small system counts.
 static constexpr size_t WD_MIN = 7 * 1024;
 static constexpr int WD_G = 16;  // basis vectors per pass
 
@@ -588,9 +591,12 @@ hipError_t launch_arnoldi1(const InstDesc *D, const ItemMap &map, int items, siz
                            GmresCtl *ctl, GmresWork *work, int *gates, int count, int R,
                            hipStream_t st) {
   if (items <= 0) return hipSuccess;
-  static_assert(KR_ONE_MAX == (size_t)KR_NT * 16, "one-chunk limit");
+  static_assert(KR_ONE_MAX == (size_t)KR_NT * 24, "one-chunk limit");
   if (max_n > KR_ONE_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_arnoldi1<16>, dim3(items), dim3(KR_NT), 0, st, D, map, j, ctl, work, gates, count, R);
+  if (max_n <= (size_t)KR_NT * 16)
+    hipLaunchKernelGGL(k_arnoldi1<16>, dim3(items), dim3(KR_NT), 0, st, D, map, j, ctl, work, gates, count, R);
+  else
+    hipLaunchKernelGGL(k_arnoldi1<24>, dim3(items), dim3(KR_NT), 0, st, D, map, j, ctl, work, gates, count, R);
   return hipGetLastError();
 }
 
@@ -698,7 +704,10 @@ hipError_t launch_restart1(const InstDesc *D, const ItemMap &map, int items, siz
   ItemMap all = map;
   all.gate = nullptr;
   if (max_n > KR_ONE_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_restart1<16>, dim3(items), dim3(KR_NT), 0, st, D, all, ctl, work, gates, count);
+  if (max_n <= (size_t)KR_NT * 16)
+    hipLaunchKernelGGL(k_restart1<16>, dim3(items), dim3(KR_NT), 0, st, D, all, ctl, work, gates, count);
+  else
+    hipLaunchKernelGGL(k_restart1<24>, dim3(items), dim3(KR_NT), 0, st, D, all, ctl, work, gates, count);
   return hipGetLastError();
 }
 
@@ -708,9 +717,12 @@ hipError_t launch_finish1(const InstDesc *D, const ItemMap &map, int items, size
   if (items <= 0) return hipSuccess;
   ItemMap all = map;
   all.gate = nullptr;
-  static_assert(KR_ONE_MAX == (size_t)FN_NT * 4, "one-chunk limit");
+  static_assert(KR_ONE_MAX == (size_t)FN_NT * 6, "one-chunk limit");
   if (max_n > KR_ONE_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_finish1<4>, dim3(items), dim3(FN_NT), 0, st, D, all, ctl, work, gates, count, basis_sel);
+  if (max_n <= (size_t)FN_NT * 4)
+    hipLaunchKernelGGL(k_finish1<4>, dim3(items), dim3(FN_NT), 0, st, D, all, ctl, work, gates, count, basis_sel);
+  else
+    hipLaunchKernelGGL(k_finish1<6>, dim3(items), dim3(FN_NT), 0, st, D, all, ctl, work, gates, count, basis_sel);
   return hipGetLastError();
 }
 
