@@ -36,122 +36,263 @@ __global__ __launch_bounds__(ST_NT) void k_symbol(const double *__restrict__ cG,
 // mode 3 ((S - M) z): W[n] = (u_S - u) - tau J (v_S - v); nonzero only on the nu + (mu-nu)
 //                boundary rows where the circulant and the BVM matrices differ.
 // J v = scale/L * (d+ Re + d- Im) of IFFT(chat*V + i conj(chat)*V) = L (G v + i G^T v).
-// The combinations u, v above for the KU elements i = tid + NT k (k < KU) of a thread: the
-// loads of one coefficient step are issued together and u, v stay in registers (elements
-// i >= m come out as zeros and are not used).
-template <int KU, int NT>
-__device__ __forceinline__ void band_combo_k(const InstDesc &d, const double *__restrict__ Z, int n, int mode,
-                                             int tid, double (&u)[KU], double (&v)[KU]) {
-  const int m = d.m, s = d.s, mu1 = d.mu1;
+//
+// Shape: one butterfly of eight elements per thread, L / 8 threads per row and 8 NT / L rows per
+// workgroup, so that in a batch the short rows share the workgroups that the longest one needs.  The
+// transforms are fft_lds.hpp's radix-2 stages in the same order (each element sees the same operations
+// and the result does not depend on the grouping), arranged for few passes through LDS:
+//  * thread t combines elements t + r L / 8, r < 4, which with the zeros of the embedding are its
+//    operands of the first three stages, and ends with the same elements of the result;
+//  * the last one to three stages forward, the product with the spectrum and the first stages back
+//    need only eight neighbours, and are one visit to LDS;
+//  * the twiddles of the passes between lie compactly in LDS, and rows are exchanged within 16 by the
+//    next four address bits, so that both kinds of access meet every bank once.
+// For L = 4096 that is 6 barriers instead of 10.  us per product of m x s, with a pass per stage triple
+// and the longest row's LDS for every row / so: 63 x 64 9.0 / 8.3, 701 x 64 16.6 / 11.7, 1023 x 512
+// 23.1 / 15.2, 2047 x 64 25.7 / 15.4, 4095 x 256 45.7 / 33.3, eight instances of 64 to 2047 rows
+// 88 / 28.  Latency bounds it (one or two workgroups per CU), LDS bandwidth for a third of the time.
+__device__ __forceinline__ int fft_sw(int i) { return i ^ ((i >> 4) & 15); }
+
+// three stages with half-spans 4h, 2h, h (forward) on elements j + r h of a group of 8 h; t[k] the
+// twiddle e^{-2 pi i k / (8 h)}
+__device__ __forceinline__ void dif8(double2 (&x)[8], const double2 *t, int j, int h) {
 #pragma unroll
-  for (int k = 0; k < KU; ++k) {
-    u[k] = 0.0;
-    v[k] = 0.0;
+  for (int r = 0; r < 4; ++r) {
+    const double2 a = x[r], c = x[r + 4];
+    x[r] = cadd(a, c);
+    x[r + 4] = cmul(csub(a, c), t[j + r * h]);
   }
-  if (mode == 1) {
 #pragma unroll
-    for (int k = 0; k < KU; ++k) {
-      const int i = tid + NT * k;
-      v[k] = i < m ? Z[(size_t)n * m + i] : 0.0;
-    }
-    return;
+  for (int r = 0; r < 8; r += (r & 1) ? 3 : 1) {
+    const double2 a = x[r], c = x[r + 2];
+    x[r] = cadd(a, c);
+    x[r + 2] = cmul(csub(a, c), t[2 * (j + (r & 1) * h)]);
   }
-  auto step = [&](int col, double a, double b) {
-    double z[KU];
 #pragma unroll
-    for (int k = 0; k < KU; ++k) {
-      const int i = tid + NT * k;
-      z[k] = i < m ? Z[(size_t)col * m + i] : 0.0;
-    }
+  for (int r = 0; r < 8; r += 2) {
+    const double2 a = x[r], c = x[r + 1];
+    x[r] = cadd(a, c);
+    x[r + 1] = cmul(csub(a, c), t[4 * j]);
+  }
+}
+// and back, with half-spans h, 2h, 4h; the upper half of the results is not formed if `low`
+template <bool low>
+__device__ __forceinline__ void dit8(double2 (&x)[8], const double2 *t, int j, int h) {
 #pragma unroll
-    for (int k = 0; k < KU; ++k) {
-      u[k] = fma(a, z[k], u[k]);
-      v[k] = fma(b, z[k], v[k]);
-    }
-  };
-  if (mode != 2) {  // BVM rows (subtracted in mode 3)
-    const int c0 = d.band_c[n] - 1;
-    const double *ra = d.band_a + (size_t)n * mu1;
-    const double *rb = d.band_b + (size_t)n * mu1;
-    for (int t = 0; t < mu1; ++t) {
-      const int col = c0 + t;
-      if (col >= 0 && col < s) step(col, ra[t], rb[t]);
-    }
-    if (mode == 3) {
+  for (int r = 0; r < 8; r += 2) {
+    const double2 a = x[r], c = cmulc(x[r + 1], t[4 * j]);
+    x[r] = cadd(a, c);
+    x[r + 1] = csub(a, c);
+  }
 #pragma unroll
-      for (int k = 0; k < KU; ++k) {
-        u[k] = -u[k];
-        v[k] = -v[k];
-      }
+  for (int r = 0; r < 8; r += (r & 1) ? 3 : 1) {
+    const double2 a = x[r], c = cmulc(x[r + 2], t[2 * (j + (r & 1) * h)]);
+    x[r] = cadd(a, c);
+    x[r + 2] = csub(a, c);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double2 a = x[r], c = cmulc(x[r + 4], t[j + r * h]);
+    x[r] = cadd(a, c);
+    if (!low) x[r + 4] = csub(a, c);
+  }
+}
+// the stages with half-spans below 2^K, K <= 3, on eight neighbours; w1, w2, w3 = the twiddles
+// e^{-2 pi i q / 8}
+template <int K>
+__device__ __forceinline__ void dif_tail(double2 (&x)[8], double2 w1, double2 w2, double2 w3) {
+  if (K == 3) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double2 a = x[r], c = x[r + 4], e = csub(a, c);
+      x[r] = cadd(a, c);
+      x[r + 4] = r == 0 ? e : cmul(e, r == 1 ? w1 : r == 2 ? w2 : w3);
     }
   }
-  if (mode >= 2) {  // circulant rows: main formula (stored in s-form row nu-1) wrapped mod s
-    const double *ra = d.band_a + (size_t)(d.nu - 1) * mu1;
-    const double *rb = d.band_b + (size_t)(d.nu - 1) * mu1;
-    for (int t = 0; t < mu1; ++t) {
-      int col = (n - d.nu + t) % s;
-      if (col < 0) col += s;
-      step(col, ra[t], rb[t]);
+  if (K >= 2) {
+#pragma unroll
+    for (int r = 0; r < 8; r += (r & 1) ? 3 : 1) {
+      const double2 a = x[r], c = x[r + 2], e = csub(a, c);
+      x[r] = cadd(a, c);
+      x[r + 2] = (r & 1) ? cmul(e, w2) : e;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 8; r += 2) {
+    const double2 a = x[r], c = x[r + 1];
+    x[r] = cadd(a, c);
+    x[r + 1] = csub(a, c);
+  }
+}
+template <int K>
+__device__ __forceinline__ void dit_head(double2 (&x)[8], double2 w1, double2 w2, double2 w3) {
+#pragma unroll
+  for (int r = 0; r < 8; r += 2) {
+    const double2 a = x[r], c = x[r + 1];
+    x[r] = cadd(a, c);
+    x[r + 1] = csub(a, c);
+  }
+  if (K >= 2) {
+#pragma unroll
+    for (int r = 0; r < 8; r += (r & 1) ? 3 : 1) {
+      const double2 a = x[r], c = (r & 1) ? cmulc(x[r + 2], w2) : x[r + 2];
+      x[r] = cadd(a, c);
+      x[r + 2] = csub(a, c);
+    }
+  }
+  if (K == 3) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double2 a = x[r], c = r == 0 ? x[4] : cmulc(x[r + 4], r == 1 ? w1 : r == 2 ? w2 : w3);
+      x[r] = cadd(a, c);
+      x[r + 4] = csub(a, c);
     }
   }
 }
 
-// NT threads (1024 for transforms of 4096 points and more, whose LDS allows one workgroup per
-// CU: more wavefronts to hide the LDS passes; 256 below), KU = elements per thread
-// (m <= NT KU).  Rows are numbered contiguously per XCD (xcd_item), so the neighbouring time
-// rows that share band columns read them through one L2; the band combination is formed once
-// (u stays in registers for the output) and d+, d- are loaded before the transforms.  Each
-// element sees the same operations whatever NT, so the result does not depend on it.
-template <int KU, int NT>
-__global__ __launch_bounds__(NT) void k_bvm_matvec(const InstDesc *__restrict__ D, ItemMap map,
-                                                      int src_sel, int src_j, int dst_sel,
-                                                      int dst_j, int mode) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bvm_matvec(const InstDesc *__restrict__ D, ItemMap map, int src_sel, int src_j,
+                                                   int dst_sel, int dst_j, int mode, int nrows) {
   extern __shared__ double2 buf[];
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int q = item_slot(map, item);
   if (item_gated(map, q)) return;
   const InstDesc &d = D[map.ids[q]];
-  const int n = item - map.pre[q];
-  const int m = d.m, L = 1 << d.log2L, tid = threadIdx.x;
+  const int m = d.m, s = d.s, mu1 = d.mu1, lg = d.log2L, L = 1 << lg, T = L >> 3, tid = threadIdx.x;
+  const int tl = tid & (T - 1), row = tid >> (lg - 3), rows = nrows > 0 ? nrows : s;
+  const int n = (item - map.pre[q]) * (NT >> (lg - 3)) + row, nn = min(n, rows - 1);
   const double *Z = vsel(d, src_sel, src_j);
   double *W = vsel(d, dst_sel, dst_j);
-  if (mode == 3 && n >= d.nu && n < d.s - (d.mu1 - 1 - d.nu)) {
-    // interior row: S and M apply the same main formula without wrap-around, so the
-    // difference is exactly zero (uniform per workgroup, before any barrier)
+  // interior rows: S and M apply the same main formula without wrap-around, so the difference is zero
+  const bool zero = mode == 3 && nn >= d.nu && nn < s - (mu1 - 1 - d.nu);
+  if (T == NT && zero) {  // the whole workgroup
     for (int i = tid; i < m; i += NT) W[(size_t)n * m + i] = 0.0;
     return;
   }
-  double u[KU], v[KU], dpv[KU], dmv[KU];
-  band_combo_k<KU, NT>(d, Z, n, mode, tid, u, v);
-#pragma unroll
-  for (int k = 0; k < KU; ++k) {
-    const int i = tid + NT * k;
-    dpv[k] = i < m ? d.dp[i] : 0.0;
-    dmv[k] = i < m ? d.dm[i] : 0.0;
+  // twiddles of pass p >= 1, t_p[k] = tw[k << 3p], one behind the other
+  const int K = lg % 3 == 0 ? 3 : lg % 3, n8 = (lg - K) / 3;
+  double2 *tw = buf + 8 * NT;
+  {
+    int at = 0;
+    for (int p = 1; p < n8; ++p) {
+      const int cnt = L >> (3 * p + 1);
+      for (int k = tid; k < cnt; k += NT) tw[at + k] = gld(d.twL + (k << (3 * p)));
+      at += cnt;
+    }
   }
-  for (int i = tid; i < L; i += NT) buf[i] = make_double2(0.0, 0.0);
+  double u[4], v[4];
+  int ix[4];
 #pragma unroll
-  for (int k = 0; k < KU; ++k) {  // the same thread wrote the zero first
-    const int i = tid + NT * k;
-    if (i < m) buf[i] = make_double2(v[k], 0.0);
+  for (int r = 0; r < 4; ++r) {
+    u[r] = v[r] = 0.0;
+    ix[r] = min(tl + r * T, m - 1);
+  }
+  // u += a_t Z[col_t], v += b_t Z[col_t], t in order; four coefficients' loads in flight
+  auto combine = [&](const double *ra, const double *rb, int c0, bool wrap) {
+    for (int t0 = 0; t0 < mu1; t0 += 4) {
+      double z[4][4], ca[4], cb[4];
+      bool ok[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int t = min(t0 + e, mu1 - 1);
+        int col = c0 + t;
+        if (wrap) col = (col % s + s) % s;
+        const int cc = min(max(col, 0), s - 1);
+        ok[e] = t0 + e < mu1 && cc == col;
+        ca[e] = gld(ra + t);
+        cb[e] = gld(rb + t);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[e][r] = gld(Z + (size_t)cc * m + ix[r]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          u[r] = ok[e] ? fma(ca[e], z[e][r], u[r]) : u[r];
+          v[r] = ok[e] ? fma(cb[e], z[e][r], v[r]) : v[r];
+        }
+    }
+  };
+  if (mode == 1) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = gld(Z + (size_t)nn * m + ix[r]);
+  } else {
+    if (mode != 2) combine(d.band_a + (size_t)nn * mu1, d.band_b + (size_t)nn * mu1, d.band_c[nn] - 1, false);
+    if (mode == 3) {  // BVM rows, subtracted
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        u[r] = -u[r];
+        v[r] = -v[r];
+      }
+    }
+    // circulant rows: the main formula (stored in s-form row nu - 1) wrapped mod s
+    if (mode >= 2) combine(d.band_a + (size_t)(d.nu - 1) * mu1, d.band_b + (size_t)(d.nu - 1) * mu1, nn - d.nu, true);
+  }
+  double2 x[8];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    x[r] = make_double2(tl + r * T < m ? v[r] : 0.0, 0.0);
+    x[r + 4] = make_double2(0.0, 0.0);
+  }
+  double2 *rb = buf + (size_t)row * L;
+  dif8(x, d.twL, tl, T);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) rb[fft_sw(tl + r * T)] = x[r];
+  __syncthreads();
+  int at = 0;
+  for (int p = 1; p < n8; ++p) {
+    const int lh = lg - 3 * (p + 1), h = 1 << lh, j = tl & (h - 1), i0 = ((tl >> lh) << (lh + 3)) + j;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[r] = rb[fft_sw(i0 + r * h)];
+    dif8(x, tw + at, j, h);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) rb[fft_sw(i0 + r * h)] = x[r];
+    __syncthreads();
+    at += L >> (3 * p + 1);
+  }
+  {
+    const double2 w1 = gld(d.twL + (L >> 3)), w2 = gld(d.twL + (L >> 2)), w3 = gld(d.twL + 3 * (L >> 3));
+    double2 ch[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) ch[r] = gld(d.chat + 8 * tl + r);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[r] = rb[fft_sw(8 * tl + r)];
+    if (K == 3) dif_tail<3>(x, w1, w2, w3);
+    else if (K == 2) dif_tail<2>(x, w1, w2, w3);
+    else dif_tail<1>(x, w1, w2, w3);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const double2 P = cmul(ch[r], x[r]);
+      const double2 Qv = cmulc(x[r], ch[r]);
+      x[r] = make_double2(P.x - Qv.y, P.y + Qv.x);
+    }
+    if (K == 3) dit_head<3>(x, w1, w2, w3);
+    else if (K == 2) dit_head<2>(x, w1, w2, w3);
+    else dit_head<1>(x, w1, w2, w3);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) rb[fft_sw(8 * tl + r)] = x[r];
   }
   __syncthreads();
-  fft_dif<NT>(buf, d.log2L, 1, d.twL);
-  for (int k = tid; k < L; k += NT) {
-    const double2 x = buf[k], c = d.chat[k];
-    const double2 P = cmul(c, x);
-    const double2 Qv = cmulc(x, c);
-    buf[k] = make_double2(P.x - Qv.y, P.y + Qv.x);
+  for (int p = n8 - 1; p >= 1; --p) {
+    const int lh = lg - 3 * (p + 1), h = 1 << lh, j = tl & (h - 1), i0 = ((tl >> lh) << (lh + 3)) + j;
+    at -= L >> (3 * p + 1);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[r] = rb[fft_sw(i0 + r * h)];
+    dit8<false>(x, tw + at, j, h);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) rb[fft_sw(i0 + r * h)] = x[r];
+    __syncthreads();
   }
-  __syncthreads();
-  fft_dit_inv<NT>(buf, d.log2L, 1, d.twL);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) x[r] = rb[fft_sw(tl + r * T)];
+  dit8<true>(x, d.twL, tl, T);
   const double coef = (mode == 1 ? 1.0 : -d.tau) * d.scale / (double)L;
 #pragma unroll
-  for (int k = 0; k < KU; ++k) {
-    const int i = tid + NT * k;
-    if (i < m) {
-      const double2 y = buf[i];
-      W[(size_t)n * m + i] = fma(coef, fma(dpv[k], y.x, dmv[k] * y.y), u[k]);
+  for (int r = 0; r < 4; ++r) {
+    const int i = tl + r * T;
+    if (i < m && n < rows) {
+      const double y = fma(coef, fma(d.dp[i], x[r].x, d.dm[i] * x[r].y), u[r]);
+      W[(size_t)n * m + i] = zero ? 0.0 : y;
     }
   }
 }
@@ -342,30 +483,35 @@ hipError_t launch_symbol(const double *cG, double2 *chat_br, int log2L, const do
   return hipGetLastError();
 }
 
-template <int KU, int NT>
-static hipError_t bvm_matvec_ku(const InstDesc *D, const ItemMap &map, int items, size_t lds, int src_sel,
-                                int src_j, int dst_sel, int dst_j, int mode, hipStream_t st) {
-  hipError_t e = set_lds((const void *)k_bvm_matvec<KU, NT>, lds);
+// Threads per workgroup: an eighth of the longest row, at least a wavefront.
+static int matvec_threads(int max_log2L) { return std::max(64, (1 << max_log2L) >> 3); }
+
+int bvm_matvec_items(int rows, int log2L, int max_log2L) {
+  const int per = matvec_threads(max_log2L) >> (log2L - 3);
+  return (rows + per - 1) / per;
+}
+
+template <int NT>
+static hipError_t bvm_matvec_nt(const InstDesc *D, const ItemMap &map, int items, int src_sel, int src_j, int dst_sel,
+                                int dst_j, int mode, int rows, hipStream_t st) {
+  const size_t lds = sizeof(double2) * (8 * NT + NT * 5 / 8);  // rows, and NT (1/2 + 1/16 + ..) twiddles
+  hipError_t e = set_lds((const void *)k_bvm_matvec<NT>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_bvm_matvec<KU, NT>), dim3(items), dim3(NT), lds, st, D, map, src_sel, src_j, dst_sel,
-                     dst_j, mode);
+  hipLaunchKernelGGL(k_bvm_matvec<NT>, dim3(items), dim3(NT), lds, st, D, map, src_sel, src_j, dst_sel, dst_j, mode, rows);
   return hipGetLastError();
 }
 
 hipError_t launch_bvm_matvec(const InstDesc *D, const ItemMap &map, int items, int max_log2L,
-                             int src_sel, int src_j, int dst_sel, int dst_j, int mode,
+                             int src_sel, int src_j, int dst_sel, int dst_j, int mode, int rows,
                              hipStream_t st) {
   if (items <= 0) return hipSuccess;
-  const size_t lds = sizeof(double2) << max_log2L;
-  // every instance has m <= L / 2 <= NT KU
-  switch (max_log2L) {
-    case 13: return bvm_matvec_ku<4, 1024>(D, map, items, lds, src_sel, src_j, dst_sel, dst_j, mode, st);
-    case 12: return bvm_matvec_ku<2, 1024>(D, map, items, lds, src_sel, src_j, dst_sel, dst_j, mode, st);
-    case 11: return bvm_matvec_ku<4, ST_NT>(D, map, items, lds, src_sel, src_j, dst_sel, dst_j, mode, st);
-    case 10: return bvm_matvec_ku<2, ST_NT>(D, map, items, lds, src_sel, src_j, dst_sel, dst_j, mode, st);
-    default:
-      if (max_log2L < 10) return bvm_matvec_ku<1, ST_NT>(D, map, items, lds, src_sel, src_j, dst_sel, dst_j, mode, st);
-      return hipErrorInvalidValue;
+  switch (matvec_threads(max_log2L)) {
+    case 64: return bvm_matvec_nt<64>(D, map, items, src_sel, src_j, dst_sel, dst_j, mode, rows, st);
+    case 128: return bvm_matvec_nt<128>(D, map, items, src_sel, src_j, dst_sel, dst_j, mode, rows, st);
+    case 256: return bvm_matvec_nt<256>(D, map, items, src_sel, src_j, dst_sel, dst_j, mode, rows, st);
+    case 512: return bvm_matvec_nt<512>(D, map, items, src_sel, src_j, dst_sel, dst_j, mode, rows, st);
+    case 1024: return bvm_matvec_nt<1024>(D, map, items, src_sel, src_j, dst_sel, dst_j, mode, rows, st);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -12,10 +12,13 @@ namespace fde {
 hipError_t launch_symbol(const double *cG, double2 *chat_br, int log2L, const double2 *twL,
                          hipStream_t st);
 
-// mode 0: W[n] = sum_q a[n][q] Z[c+q-1] - tau J (sum_q b[n][q] Z[c+q-1]),  items = s per instance
-// mode 1: W[n] = J Z[n],                                                  items = rows per instance
+// mode 0: W[n] = sum_q a[n][q] Z[c+q-1] - tau J (sum_q b[n][q] Z[c+q-1])
+// mode 1: W[n] = J Z[n]
+// rows: rows n per instance (0: s); items = bvm_matvec_items(rows, log2L, max_log2L) per instance.
+// log2L >= 4.
+int bvm_matvec_items(int rows, int log2L, int max_log2L);
 hipError_t launch_bvm_matvec(const InstDesc *D, const ItemMap &map, int items, int max_log2L,
-                             int src_sel, int src_j, int dst_sel, int dst_j, int mode,
+                             int src_sel, int src_j, int dst_sel, int dst_j, int mode, int rows,
                              hipStream_t st);
 // b = tau Bhat f - a0 u0 (+ tau b0 J u0), items = s per instance
 hipError_t launch_rhs(const InstDesc *D, const ItemMap &map, int items, int use_ju0, hipStream_t st);

@@ -1178,7 +1178,7 @@ extern "C" fde_status fde_bvm_setup(const fde_problem *p, fde_bvm **out) {
   h->log2s = log2s;
   h->L = 2;
   h->log2L = 1;
-  while (h->L < 2 * p->m) {
+  while (h->L < 2 * p->m || h->L < 16) {  // 16: the least that k_bvm_matvec takes
     h->L <<= 1;
     h->log2L++;
   }
@@ -2042,6 +2042,7 @@ static fde_status ensure_full_maps(Plan *P) {
     if (it != g_tuned_cols.end()) S.tfft_cols = it->second;
   }
   std::vector<std::vector<int>> hu(HIER_LEVELS + 1, std::vector<int>(count, 0));
+  for (const fde_bvm *h : P->hs) S.max_log2L = std::max(S.max_log2L, h->log2L);
   for (int q = 0; q < count; ++q) {
     fde_bvm *h = P->hs[q];
     slots[q] = q;
@@ -2061,13 +2062,12 @@ static fde_status ensure_full_maps(Plan *P) {
       S.hsub_bytes += (double)h->nb * h->mp * (in * esz + 32.0);
     }
     g[q] = h->hier ? 0 : h->nb;
-    a[q] = h->s;
+    a[q] = bvm_matvec_items(h->s, h->log2L, S.max_log2L);
     b[q] = h->mp / S.tfft_cols;
     c[q] = h->hier ? 0 : h->nb * P->desc[q].W;
     d[q] = h->nblk;
     e[q] = h->s;
     f[q] = h->need_Ju0 ? 1 : 0;
-    S.max_log2L = std::max(S.max_log2L, h->log2L);
     S.max_log2s = std::max(S.max_log2s, h->log2s);
     S.max_mp = std::max(S.max_mp, h->mp);
     qq[q] = h->hier ? 0 : qgemm_items(h->nb, h->mp);
@@ -2169,7 +2169,7 @@ static fde_status ensure_full_maps(Plan *P) {
 static fde_status op_matvec(Plan *P, const SolveMaps &S, int src, int sj, int dst, int dj) {
   fde_bvm *L = P->lead;
   HIPCHK(run(L, "bvm_matvec", 2.0 * S.vec_bytes, [&] {
-    return launch_bvm_matvec(P->d_desc, S.mv, S.n_mv, S.max_log2L, src, sj, dst, dj, 0, L->stream);
+    return launch_bvm_matvec(P->d_desc, S.mv, S.n_mv, S.max_log2L, src, sj, dst, dj, 0, 0, L->stream);
   }));
   return FDE_OK;
 }
@@ -2281,7 +2281,7 @@ static fde_status op_rhs(Plan *P, const SolveMaps &S) {
   fde_bvm *L = P->lead;
   if (S.n_ju0 > 0) {
     HIPCHK(run(L, "toeplitz", 16.0 * S.n_ju0, [&] {
-      return launch_bvm_matvec(P->d_desc, S.ju0, S.n_ju0, S.max_log2L, VS_U0, 0, VS_JU0, 0, 1,
+      return launch_bvm_matvec(P->d_desc, S.ju0, S.n_ju0, S.max_log2L, VS_U0, 0, VS_JU0, 0, 1, 1,
                                L->stream);
     }));
   }
@@ -3008,7 +3008,7 @@ static fde_status self_band_op(fde_bvm *h, const double *z, double *w, int mem_s
   STCHK(self_maps(h, S));
   STCHK(copy_in(h, h->d_sio, z, h->n(), mem_space));
   HIPCHK(run(h, name, 16.0 * h->n(), [&] {
-    return launch_bvm_matvec(h->self->d_desc, S.mv, S.n_mv, S.max_log2L, VS_SIO, 0, VS_TMP, 0, mode,
+    return launch_bvm_matvec(h->self->d_desc, S.mv, S.n_mv, S.max_log2L, VS_SIO, 0, VS_TMP, 0, mode, 0,
                              h->stream);
   }));
   STCHK(copy_out(h, w, h->d_tmp, h->n(), mem_space));
@@ -3175,12 +3175,12 @@ extern "C" fde_status fde_toeplitz_apply(fde_bvm *h, const double *x, double *y,
   SolveMaps S;
   STCHK(self_maps(h, S));
   const size_t cnt = (size_t)count * h->m;
-  std::vector<HostMap> hm = {make_map({0}, {count})};
+  std::vector<HostMap> hm = {make_map({0}, {bvm_matvec_items(count, h->log2L, h->log2L)})};
   std::vector<ItemMap> dm;
   STCHK(upload_maps(h->self, hm, dm));
   STCHK(copy_in(h, h->d_sio, x, cnt, mem_space));
   HIPCHK(run(h, "toeplitz", 16.0 * cnt, [&] {
-    return launch_bvm_matvec(h->self->d_desc, dm[0], count, h->log2L, VS_SIO, 0, VS_TMP, 0, 1, h->stream);
+    return launch_bvm_matvec(h->self->d_desc, dm[0], hm[0].items, h->log2L, VS_SIO, 0, VS_TMP, 0, 1, count, h->stream);
   }));
   STCHK(copy_out(h, y, h->d_tmp, cnt, mem_space));
   return sync_and_flush(h);
