@@ -72,7 +72,8 @@ __host__ __device__ inline int hier_nodes_p(int npan, int lev) {
 __host__ __device__ inline int hier_nodes(int mp, int lev) { return hier_nodes_p(mp >> 6, lev); }
 
 // vector selectors resolved on the device
-enum VSel : int { VS_V = 0, VS_Z, VS_W, VS_X, VS_B, VS_TMP, VS_SIO, VS_U0, VS_JU0 };
+// (VS_VN, the time FFT's only: V_j, formed from w where the two-pass Gram-Schmidt left it unscaled)
+enum VSel : int { VS_V = 0, VS_Z, VS_W, VS_X, VS_B, VS_TMP, VS_SIO, VS_U0, VS_JU0, VS_VN };
 
 __device__ __forceinline__ double *vsel(const InstDesc &d, int sel, int j) {
   const size_t n = (size_t)d.s * d.m;

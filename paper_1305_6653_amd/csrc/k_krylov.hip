@@ -281,7 +281,7 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_step(const InstDesc *__restrict__
 // so the dots with w and the dots of the newest v_j with the older vectors (the other v_i . v_k
 // are kept from earlier steps) are taken in one pass, and w -= V h in a second.  No orthogonality
 // of V is assumed, so the loss of orthogonality is corrected as MGS corrects it.  Launches per
-// step: 3 (with v_{j+1}) instead of j + 4, and every basis vector is read twice instead of w, v_i
+// step: 2, and one for v_{j+1} unless the time FFT scales it (VS_VN), instead of j + 4, and every basis vector is read twice instead of w, v_i
 // and v_{i-1} being read and w written per projection: 255 x 128 (19 steps) 1.34 to 0.45 ms, 96 x 128
 // (20 steps) 1.44 to 0.43, 4095 x 256 (17 steps) 1.66 to 0.82.  Launch latency bounds it up to about
 // 10^5 entries, the passes over V above.  Vectors of 6145 (above k_arnoldi1's) to WD_MIN entries keep

@@ -330,6 +330,10 @@ __global__ __launch_bounds__(ST_NT) void k_rhs(const InstDesc *__restrict__ D, I
 // device-wide counter into epoch_slot[0] (read by the block solve that follows on the stream),
 // so a recorded launch sequence gets a fresh epoch on every replay, and clears the block
 // solve's unit counter epoch_slot[1].
+//
+// Source VS_VN: the basis vector v_j of an instance whose Gram-Schmidt runs in two passes is w / H[j];
+// this kernel, its only reader before the next Gram-Schmidt pass, scales it on the way in and stores
+// it (instead of a launch of its own per step: 255 x 128 1388 to 1363 us).
 template <int TP>
 __global__ __launch_bounds__(ST_NT) void k_time_rfft(const InstDesc *__restrict__ D, ItemMap map,
                                                      int src_sel, int src_j, int max_log2s,
@@ -345,14 +349,21 @@ __global__ __launch_bounds__(ST_NT) void k_time_rfft(const InstDesc *__restrict_
   if (item_gated(map, q)) return;
   const InstDesc &d = D[map.ids[q]];
   const int m = d.m, mp = d.mp, log2s = d.log2s, s = 1 << log2s;
-  const double *V = vsel(d, src_sel, src_j);
+  const bool next = src_sel == VS_VN && d.nwide > 0;
+  const double *V = next ? d.w : vsel(d, src_sel == VS_VN ? (int)VS_V : src_sel, src_j);
+  double *Vn = d.V + (size_t)src_j * s * m;
+  const double nrm = next ? d.H[src_j] : 1.0, inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
   const int col0 = (item - map.pre[q]) * 2 * TP;
   double2 *twl = buf + ((size_t)TP << max_log2s);
   for (int i = threadIdx.x; i < s / 2; i += ST_NT) twl[i] = d.tws[i];
   for (int e = threadIdx.x; e < s * 2 * TP; e += ST_NT) {
     const int n = e / (2 * TP), c = e % (2 * TP);
     const int col = col0 + c;
-    const double v = (col < m) ? V[(size_t)n * m + col] : 0.0;
+    double v = (col < m) ? V[(size_t)n * m + col] : 0.0;
+    if (next) {
+      v *= inv;
+      if (col < m) Vn[(size_t)n * m + col] = v;
+    }
     reinterpret_cast<double *>(&buf[(c >> 1) * s + n])[c & 1] = v;
   }
   __syncthreads();

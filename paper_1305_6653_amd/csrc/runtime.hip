@@ -2521,6 +2521,8 @@ static fde_status gmres_plan(Plan *P, const fde_solve_opts &o, const std::vector
     return FDE_OK;
   };
   // Arnoldi step j: w = M P^{-1} v_j (right; z_j = P^{-1} v_j is kept) or P^{-1} M v_j (left).
+  // v_j of the instances with the two-pass Gram-Schmidt is scaled by the time FFT that reads it first
+  const bool fold = !left && S.pc != FDE_PC_NONE && ortho == FDE_ORTHO_MGS;
   auto steps = [&](int j0, int j1) -> fde_status {
     for (int j = j0; j < j1; ++j) {
       g_step = j;
@@ -2528,7 +2530,7 @@ static fde_status gmres_plan(Plan *P, const fde_solve_opts &o, const std::vector
         STCHK(op_matvec(P, Sact, VS_V, j, VS_TMP, 0));
         STCHK(op_precond(P, Sact, VS_TMP, 0, VS_W, 0));
       } else {
-        STCHK(op_precond(P, Sact, VS_V, j, VS_Z, j));
+        STCHK(op_precond(P, Sact, fold && j > 0 ? VS_VN : VS_V, j, VS_Z, j));
         STCHK(op_matvec(P, Sact, VS_Z, j, VS_W, 0));
       }
       if (ortho == FDE_ORTHO_MGS && S.kry_one_n > 0) {
@@ -2555,8 +2557,9 @@ static fde_status gmres_plan(Plan *P, const fde_solve_opts &o, const std::vector
             return launch_mgs_apply(P->d_desc, Sact.kwide, S.n_kwide, j, P->d_ctl, P->d_work, P->d_gates, count, R,
                                     stream);
           }));
-          HIPCHK(run(L, "normalize", 2.0 * S.wide_bytes,
-                     [&] { return launch_mgs_scale(P->d_desc, Sact.kwide, S.n_kwide, j, stream); }));
+          if (!fold)
+            HIPCHK(run(L, "normalize", 2.0 * S.wide_bytes,
+                       [&] { return launch_mgs_scale(P->d_desc, Sact.kwide, S.n_kwide, j, stream); }));
           if (S.n_kchain == 0) continue;
         }
         for (int i = 0; i <= j + 1; ++i) {
