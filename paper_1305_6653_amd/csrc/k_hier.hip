@@ -1085,9 +1085,13 @@ __global__ __launch_bounds__(256, 2) void k_hier_sub(const InstDesc *__restrict_
 }
 
 // One level above the chunks.  Item = (instance, block, group of 4 panels of one half of a node), a
-// wavefront per panel; everything but the panel sums is loaded before the first barrier.
+// wavefront per panel.  W', G and the panel partials are loaded before the first barrier; V comes from
+// L2 where it is used, because with it in registers too a launch of 129 x 16 workgroups (4095 x 256) is
+// a few more than two (FP32: 126 registers) or four (FP64: 240) full loads of the chip and its last
+// round is nearly empty.  With 96 and 168 registers 27.8 and 57.7 us, before 36.8 and 58.6; 80 and 128
+// registers spill (43 and 105 us).
 template <typename T>
-__global__ __launch_bounds__(256, 2) void k_hier_up(const InstDesc *__restrict__ Dd, ItemMap map, int lev) {
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 3 : 5) void k_hier_up(const InstDesc *__restrict__ Dd, ItemMap map, int lev) {
   __shared__ c_t<T> ps[8][32], sg[8][32], as[64], z[32], y[4][HP];
   const int q = item_slot(map, blockIdx.x);
   if (item_gated(map, q)) return;
@@ -1103,7 +1107,6 @@ __global__ __launch_bounds__(256, 2) void k_hier_up(const InstDesc *__restrict__
   c_t<T> *A = (c_t<T> *)d.ha + (size_t)k * npan * 32;
   double2 *Vh = d.Vh + (size_t)k * mp + (size_t)p * HP + lane;
   c_t<T> wr[32], g[4], v = mk<T>((T)0, (T)0);
-  T x[32];
   if (live) {
     const int hf = gr >> 2, run = hp >> 2, f = (gr & 3) * run;
     ps[gr][r] = sum_run<T>(A + (size_t)(lev & 1) * plane + (size_t)(b0 + hf * hp) * 32 + r, f, f + run,
@@ -1117,7 +1120,6 @@ __global__ __launch_bounds__(256, 2) void k_hier_up(const InstDesc *__restrict__
   }
   if (mine) v = to_t<T>(*Vh);
   if (mine && live) load_w<T>(hier_w<T>(d, lev, k) + (size_t)p * R * HP + lane, R, wr);
-  if (more) load_v<T>(d, lev + 1, p, x);
   if (live) {
     __syncthreads();
     if (threadIdx.x < 64) {
@@ -1150,7 +1152,9 @@ __global__ __launch_bounds__(256, 2) void k_hier_up(const InstDesc *__restrict__
     }
   }
   if (more) {
+    T x[32];
     y[w][lane] = v;
+    load_v<T>(d, lev + 1, p, x);
     wave_fence();
     const c_t<T> a = panel_vty<T>(x, y[w]);
     if (lane < 32) A[(size_t)((lev + 1) & 1) * plane + (size_t)p * 32 + lane] = a;
