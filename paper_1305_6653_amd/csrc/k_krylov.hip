@@ -328,11 +328,17 @@ __device__ __forceinline__ bool wide_last(const InstDesc &d, int *sh) {
 }
 
 // Sum of the nw partials of one value by a row of 16 lanes (fixed order: stride-16 runs, then
-// the row's butterfly); result in every lane of the row.
+// the row's butterfly); result in every lane of the row.  Eight coherent loads are in flight at a time:
+// one by one, each a round trip, 256 partials took longer than the pass over the basis.
 __device__ __forceinline__ double wide_sum16(const double *p, int nw) {
   double t = 0.0;
-#pragma unroll 16
-  for (int b = threadIdx.x & 15; b < nw; b += 16) t += ld_coh1(p + b);
+  for (int b = threadIdx.x & 15; b < nw; b += 128) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = ld_coh1(p + min(b + 16 * q, nw - 1));
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t += b + 16 * q < nw ? v[q] : 0.0;
+  }
   t += dpp_f64<0xB1>(t);
   t += dpp_f64<0x4E>(t);
   t += dpp_f64<0x141>(t);
@@ -350,6 +356,13 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_dots(const InstDesc *__restrict__
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = d.nwide;
   const double2 *w = (const double2 *)d.w, *V = (const double2 *)d.V, *vj = V + (size_t)j * c.n2;
   double *pa = d.wpart, *pl = d.wpart + (size_t)(j + 1) * nw;
+  // the rows of V^T V of earlier steps, for the last chunk's substitution, while the dots run
+  double gp[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = threadIdx.x + q * KR_NT, r = j > 0 ? e / j : 0, k = e - r * j;
+    gp[q] = gld(d.gram + (e < j * j && k < r ? (size_t)r * d.ldgram + k : 0));
+  }
   for (int i0 = 0; i0 <= j; i0 += WD_G) {
     const int ng = min(j + 1 - i0, WD_G);
     double acc[2 * WD_G];  // v_i . w, then v_i . v_j
@@ -393,7 +406,12 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_dots(const InstDesc *__restrict__
     __syncthreads();
   }
   if (!wide_last(d, &sh)) return;
-  for (int e = threadIdx.x; e < j * j; e += KR_NT) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = threadIdx.x + q * KR_NT, r = j > 0 ? e / j : 0, k = e - r * j;
+    if (e < j * j && k < r) gl[r][k] = gp[q];
+  }
+  for (int e = threadIdx.x + 2 * KR_NT; e < j * j; e += KR_NT) {
     const int r = e / j, k = e % j;
     if (k < r) gl[r][k] = d.gram[(size_t)r * d.ldgram + k];
   }
@@ -411,9 +429,13 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_dots(const InstDesc *__restrict__
   __syncthreads();
   if (threadIdx.x < 64) {  // forward substitution, lane i = row i
     double h = lane <= j ? hs[lane] : 0.0;
+    const double *row = lane == j ? ls : gl[min(lane, j)];
+#pragma unroll 4
     for (int k = 0; k < j; ++k) {
-      const double hk = __shfl(h, k, 64);
-      if (lane > k && lane <= j) h = fma(-(lane == j ? ls[k] : gl[lane][k]), hk, h);
+      const double g = row[k];
+      const double hk = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(h), k),
+                                         __builtin_amdgcn_readlane(__double2loint(h), k));
+      if (lane > k && lane <= j) h = fma(-g, hk, h);
     }
     if (lane <= j) d.H[lane] = h;
   }
@@ -429,7 +451,13 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_apply(const InstDesc *__restrict_
   if (!c.d) return;
   const InstDesc &d = *c.d;
   const int nw = d.nwide;
-  if (threadIdx.x <= j) cf[threadIdx.x] = d.H[threadIdx.x];
+  const int inst = map.ids[item_slot(map, blockIdx.x)];
+  if (threadIdx.x <= j) {  // j < GM_RMAX <= the threads; the rotations are for the last chunk
+    cf[threadIdx.x] = d.H[threadIdx.x];
+    csl[threadIdx.x] = work[inst].cs[threadIdx.x];
+    snl[threadIdx.x] = work[inst].sn[threadIdx.x];
+  }
+  const double gj = work[inst].g[j];
   __syncthreads();
   double2 *w = (double2 *)d.w;
   const double2 *V = (const double2 *)d.V;
@@ -454,11 +482,6 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_apply(const InstDesc *__restrict_
   nn = block_sum<KR_NT>(nn, red);
   if (threadIdx.x == 0) st_coh1(d.wpart + c.b, nn);
   if (!wide_last(d, &sh)) return;
-  const int inst = map.ids[item_slot(map, blockIdx.x)];
-  for (int r = threadIdx.x; r < j; r += KR_NT) {
-    csl[r] = work[inst].cs[r];
-    snl[r] = work[inst].sn[r];
-  }
   if (threadIdx.x < 16) {
     const double nrm = sqrt(wide_sum16(d.wpart, nw));
     if (threadIdx.x == 0) cf[j + 1] = nrm;
@@ -466,7 +489,7 @@ __global__ __launch_bounds__(KR_NT) void k_mgs_apply(const InstDesc *__restrict_
   __syncthreads();
   if (threadIdx.x == 0) {
     d.H[j + 1] = cf[j + 1];
-    gm_givens_core(cf, csl, snl, work[inst].g[j], ctl[inst], work[inst], gates, count, inst, j, R);
+    gm_givens_core<false>(cf, csl, snl, gj, ctl[inst], work[inst], gates, count, inst, j, R);
   }
 }
 
@@ -583,7 +606,7 @@ __global__ __launch_bounds__(KR_NT) void k_arnoldi1(const InstDesc *__restrict__
   if (t == 0) {
     d.H[j + 1] = nrm;
     hcol[j + 1] = nrm;
-    gm_givens_core(hcol, csl, snl, gjs, ctl[inst], work[inst], gates, count, inst, j, R);
+    gm_givens_core<false>(hcol, csl, snl, gjs, ctl[inst], work[inst], gates, count, inst, j, R);
   }
 }
 
@@ -832,7 +855,17 @@ __global__ __launch_bounds__(KR_NT) void k_update_x(const InstDesc *__restrict__
   const double *Q = basis_sel == VS_V ? d.V : d.Z;
   for (size_t e = c.begin + threadIdx.x; e < c.end; e += KR_NT) {
     double acc = d.x[e];
-    for (int j = 0; j < k; ++j) acc = fma(d.y[1 + j], Q[(size_t)j * c.n + e], acc);
+    for (int j0 = 0; j0 < k; j0 += 8) {  // eight loads in flight
+      double q[8], y[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int j = min(j0 + t, k - 1);
+        q[t] = gld(Q + (size_t)j * c.n + e);
+        y[t] = d.y[1 + j];
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) acc = j0 + t < k ? fma(y[t], q[t], acc) : acc;
+    }
     d.x[e] = acc;
   }
 }
