@@ -311,7 +311,7 @@ __global__ __launch_bounds__(NT) void k_lu_diag(const InstDesc *__restrict__ Dd,
       a[r][c] = csel<T>(c == r, dgi[r], x[j]);  // U's diagonal by its reciprocal
     }
   }
-  if (bad) atomicOr(flag, 1);
+  if (bad) *flag = 1;
   __syncthreads();  // a[][] complete
   tri_inv_doubling<T, NT, true>(a);
   C *Dl = dinv + ((size_t)(blk * npan + p) * 2 + 0) * PB * PB;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(512) void k_hess_uinv(const InstDesc *__restrict__ 
     const int r = e / PB, c = e % PB;
     Du[e] = csel<T>(r <= c, a[r][c], zero);
   }
-  if (bad) atomicOr(flag, 1);
+  if (bad) *flag = 1;
 }
 
 template <typename T>
@@ -1174,7 +1174,7 @@ __device__ __forceinline__ void band_lu_panel_body(const InstDesc *__restrict__ 
     K[(size_t)(r0 + r) * mp + r0 + c] = a[r][c];
   }
   if (tid < nr) d.hpiv[((size_t)blk * npan + j) * 2 * PB + tid] = perm[tid];
-  if (bad) atomicOr(flag, 1);
+  if (bad) *flag = 1;
   __syncthreads();
   if (tid < PB) {
     bool ok;

@@ -446,7 +446,7 @@ __global__ __launch_bounds__(HL_NT) void k_hess_lu(const InstDesc *__restrict__ 
         }
     }
   }
-  if (bad) atomicOr(flag, 1);
+  if (bad) *flag = 1;
 }
 
 template <typename T>

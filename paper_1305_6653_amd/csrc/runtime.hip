@@ -400,7 +400,8 @@ struct Plan {
   int *d_arena = nullptr;
   size_t arena_ints = 0;
   std::vector<InstDesc> desc;
-  std::vector<int> arena_host;  // kept alive until the next rebuild (async upload source)
+  std::vector<int> arena_host;  // the arena's contents
+  bool arena_ok = false;        // ... and that they are on the device
   std::vector<size_t> part_off;
   std::vector<void *> allocs;
   bool desc_dirty = true;
@@ -412,8 +413,8 @@ struct Plan {
   std::vector<GmresCtl> ctl_host;
   std::vector<int> gates_host;
   // pinned host staging: the control records and the block-solve error flag read back once
-  // per cycle (the factorization's pivot flag in the int after that flag), the control
-  // records and gates uploaded once per solve (pin_* byte offsets)
+  // per cycle (laid out as on the device), the factorization's pivot flag (d_flag: the kernels write it
+  // here), the control records and gates uploaded once per solve (pin_* byte offsets)
   void *pin = nullptr;
   size_t pin_err = 0, pin_ctl_up = 0, pin_gates_up = 0;
   double *pin_parts = nullptr;  // the reduction partials read back for the norms of b
@@ -489,33 +490,39 @@ static HostMap make_map(const std::vector<int> &slots, const std::vector<int> &i
 
 // Upload several maps into the plan's arena; returns device ItemMaps.
 static fde_status upload_maps(Plan *P, const std::vector<HostMap> &maps, std::vector<ItemMap> &out) {
-  size_t need = 0;
-  for (const HostMap &m : maps) need += m.ids.size() + m.pre.size();
-  HIPCHK(hipStreamSynchronize(P->lead->stream));  // previous users of the arena are done
-  if (need > P->arena_ints) {
-    if (P->d_arena) {
-      auto it = std::find(P->allocs.begin(), P->allocs.end(), (void *)P->d_arena);
-      if (it != P->allocs.end()) P->allocs.erase(it);
-      (void)hipFree(P->d_arena);
-      P->d_arena = nullptr;
-    }
-    size_t cap = std::max<size_t>(need, 1024);
-    void *p = nullptr;
-    STCHK(plan_alloc(P, &p, cap * sizeof(int)));
-    P->d_arena = (int *)p;
-    P->arena_ints = cap;
-  }
-  P->arena_host.clear();
-  out.clear();
+  std::vector<int> flat;
   for (const HostMap &m : maps) {
-    const size_t oi = P->arena_host.size();
-    P->arena_host.insert(P->arena_host.end(), m.ids.begin(), m.ids.end());
-    const size_t op = P->arena_host.size();
-    P->arena_host.insert(P->arena_host.end(), m.pre.begin(), m.pre.end());
+    flat.insert(flat.end(), m.ids.begin(), m.ids.end());
+    flat.insert(flat.end(), m.pre.begin(), m.pre.end());
+  }
+  if (!P->arena_ok || flat != P->arena_host) {  // a repeated factorization finds its maps in place
+    HIPCHK(hipStreamSynchronize(P->lead->stream));  // previous users of the arena are done
+    P->arena_ok = false;
+    if (flat.size() > P->arena_ints) {
+      if (P->d_arena) {
+        auto it = std::find(P->allocs.begin(), P->allocs.end(), (void *)P->d_arena);
+        if (it != P->allocs.end()) P->allocs.erase(it);
+        (void)hipFree(P->d_arena);
+        P->d_arena = nullptr;
+        P->arena_ints = 0;
+      }
+      size_t cap = std::max<size_t>(flat.size(), 1024);
+      void *p = nullptr;
+      STCHK(plan_alloc(P, &p, cap * sizeof(int)));
+      P->d_arena = (int *)p;
+      P->arena_ints = cap;
+    }
+    HIPCHK(hipMemcpy(P->d_arena, flat.data(), flat.size() * sizeof(int), hipMemcpyHostToDevice));
+    P->arena_host = std::move(flat);
+    P->arena_ok = true;
+  }
+  out.clear();
+  size_t at = 0;
+  for (const HostMap &m : maps) {
+    const size_t oi = at, op = at + m.ids.size();
+    at = op + m.pre.size();
     out.push_back(ItemMap{P->d_arena + oi, P->d_arena + op, (int)m.ids.size(), nullptr});
   }
-  HIPCHK(hipMemcpy(P->d_arena, P->arena_host.data(), P->arena_host.size() * sizeof(int),
-                   hipMemcpyHostToDevice));
   return FDE_OK;
 }
 
@@ -765,29 +772,20 @@ static fde_status plan_create(const std::vector<fde_bvm *> &hs, Plan **out) {
     return st;
   }
   P->d_desc = (InstDesc *)p;
-  if ((st = plan_alloc(P, &p, 2 * sizeof(int))) != FDE_OK) {
-    plan_free(P);
-    return st;
-  }
-  P->d_err = (int *)p;
-  P->d_flag = P->d_err + 1;
-  if (hipMemset(P->d_err, 0, 2 * sizeof(int)) != hipSuccess) {
-    plan_free(P);
-    return fail(FDE_EDEVICE, "plan flag initialisation failed");
-  }
   const size_t count = hs.size();
   const size_t ctl_bytes = (sizeof(GmresCtl) * count + 255) / 256 * 256;
   const size_t gate_bytes = (sizeof(int) * GATE_COUNT * count + 255) / 256 * 256;
-  if ((st = plan_alloc(P, &p, ctl_bytes + gate_bytes + 256 + sizeof(GmresWork) * count)) != FDE_OK) {
+  if ((st = plan_alloc(P, &p, ctl_bytes + gate_bytes + 512 + sizeof(GmresWork) * count)) != FDE_OK) {
     plan_free(P);
     return st;
   }
   char *base = (char *)p;
-  P->d_ctl = (GmresCtl *)base;
-  P->d_gates = (int *)(base + ctl_bytes);
-  P->d_epoch = (unsigned long long *)(base + ctl_bytes + gate_bytes);
-  P->d_work = (GmresWork *)(base + ctl_bytes + gate_bytes + 256);
-  if (hipMemset(base, 0, ctl_bytes + gate_bytes + 256) != hipSuccess) {
+  P->d_ctl = (GmresCtl *)base;  // the block-solve error flag right behind: one copy reads both back
+  P->d_err = (int *)(base + ctl_bytes);
+  P->d_gates = (int *)(base + ctl_bytes + 256);
+  P->d_epoch = (unsigned long long *)(base + ctl_bytes + 256 + gate_bytes);
+  P->d_work = (GmresWork *)(base + ctl_bytes + 512 + gate_bytes);
+  if (hipMemset(base, 0, ctl_bytes + gate_bytes + 512) != hipSuccess) {
     plan_free(P);
     return fail(FDE_EDEVICE, "plan control initialisation failed");
   }
@@ -801,6 +799,8 @@ static fde_status plan_create(const std::vector<fde_bvm *> &hs, Plan **out) {
     plan_free(P);
     return fail(FDE_EDEVICE, "pinned host buffer allocation failed");
   }
+  P->d_flag = (int *)((char *)P->pin + P->pin_err + 128);
+  *P->d_flag = 0;
   P->desc.resize(hs.size());
   std::memset(P->desc.data(), 0, sizeof(InstDesc) * hs.size());
   *out = P;
@@ -918,7 +918,7 @@ static bool hier_basis(const fde_bvm *h, std::vector<double> &table, int rank[2]
   for (int l = 0; l < nlev; ++l) {
     const int N = 64 << l, rmax = HIER_RMAX - 1;
     double *out = table.data() + (size_t)(N - 64) * HIER_RMAX;
-    X.assign((size_t)N * rmax, 0.0L);  // column by column
+    X.assign((size_t)N * rmax, 0.0L);  // row by row: a row's sum stays in a register
     d.resize(N);
     for (int p = 0; p < N; ++p) d[p] = g[2 * p + 2];
     const long double d0 = d[0];
@@ -931,18 +931,19 @@ static bool hier_basis(const fde_bvm *h, std::vector<double> &table, int rank[2]
         if (d[j] > 2e-17L * d0) return false;
         break;
       }
-      long double *x = &X[(size_t)r * N];
-      const long double *gj = &g[j + 2];
-      for (int p = 0; p < N; ++p) x[p] = gj[p];
-      for (int c = 0; c < r; ++c) {
-        const long double *xc = &X[(size_t)c * N], f = xc[j];
-        for (int p = 0; p < N; ++p) x[p] -= f * xc[p];
-      }
-      const long double s = 1.0L / sqrtl(d[j]);
-      for (int p = 0; p < N; ++p) {
-        x[p] *= s;
-        d[p] -= x[p] * x[p];
-        out[(size_t)p * HIER_RMAX + 1 + r] = (double)x[p];
+      long double f[HIER_RMAX];
+      for (int c = 0; c < r; ++c) f[c] = X[(size_t)j * rmax + c];
+      const long double *gj = &g[j + 2], s = 1.0L / sqrtl(d[j]);
+      for (int p = 0; p < N; p += 4) {  // N is a multiple of 64; four sums hide each other's latency
+        long double *x = &X[(size_t)p * rmax], a[4] = {gj[p], gj[p + 1], gj[p + 2], gj[p + 3]};
+        for (int c = 0; c < r; ++c)
+          for (int q = 0; q < 4; ++q) a[q] -= f[c] * x[q * rmax + c];
+        for (int q = 0; q < 4; ++q) {
+          const long double v = a[q] * s;
+          x[q * rmax + r] = v;
+          d[p + q] -= v * v;
+          out[(size_t)(p + q) * HIER_RMAX + 1 + r] = (double)v;
+        }
       }
       d[j] = 0.0L;
     }
@@ -1898,7 +1899,7 @@ static fde_status factor_blocks(Plan *P, int route, fde_precision prec) {
   // the same shape keeps them, and needs no host round trip here)
   STCHK(plan_prepare(P, std::max(P->R, 1), prec));
   hipEvent_t e0 = get_event(L), e1 = get_event(L);
-  HIPCHK(hipMemsetAsync(P->d_flag, 0, sizeof(int), L->stream));
+  *P->d_flag = 0;  // pinned: the kernels write it, and no factorization is in flight here
   HIPCHK(hipEventRecord(e0, L->stream));
   if (hier) {
     TraceRange tr("blocks: hierarchical form");
@@ -1916,8 +1917,6 @@ static fde_status factor_blocks(Plan *P, int route, fde_precision prec) {
     STCHK(prec == FDE_FP64 ? factor_plan_impl<double>(P) : factor_plan_impl<float>(P));
   }
   HIPCHK(hipEventRecord(e1, L->stream));
-  int *flag_pin = (int *)((char *)P->pin + P->pin_err) + 1;  // pinned: no staging copy
-  HIPCHK(hipMemcpyAsync(flag_pin, P->d_flag, sizeof(int), hipMemcpyDeviceToHost, L->stream));
   std::vector<int> herr(P->hs.size(), 0);
   if (route == FDE_BLOCKS_HESSENBERG)
     for (size_t i = 0; i < P->hs.size(); ++i)
@@ -1937,7 +1936,7 @@ static fde_status factor_blocks(Plan *P, int route, fde_precision prec) {
   HIPCHK(hipEventElapsedTime(&ms, e0, e1));
   L->evpool.push_back(e0);
   L->evpool.push_back(e1);
-  if (*flag_pin) return fail(FDE_ESINGULAR, "zero or non-finite pivot in a preconditioner block");
+  if (*P->d_flag) return fail(FDE_ESINGULAR, "zero or non-finite pivot in a preconditioner block");
   for (fde_bvm *h : P->hs) {
     h->prec = prec;
     h->t_factor_ms = ms;
@@ -2600,8 +2599,7 @@ static fde_status gmres_plan(Plan *P, const fde_solve_opts &o, const std::vector
   int *err_pin = (int *)((char *)P->pin + P->pin_err);
   *err_pin = 0;
   auto read_ctl = [&]() -> fde_status {
-    HIPCHK(hipMemcpyAsync(ctl_pin, P->d_ctl, count * sizeof(GmresCtl), hipMemcpyDeviceToHost, stream));
-    HIPCHK(hipMemcpyAsync(err_pin, P->d_err, sizeof(int), hipMemcpyDeviceToHost, stream));
+    HIPCHK(hipMemcpyAsync(ctl_pin, P->d_ctl, P->pin_err + sizeof(int), hipMemcpyDeviceToHost, stream));
     HIPCHK(hipStreamSynchronize(stream));
     std::memcpy(ctl.data(), ctl_pin, count * sizeof(GmresCtl));
     for (int i = 0; i < count; ++i)
