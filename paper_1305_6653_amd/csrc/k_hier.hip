@@ -287,8 +287,9 @@ __device__ __forceinline__ void group_invert(c_t<T> *M, int R, int w, c_t<T> *co
 // Newton.  X <- X + X (I - K X).  Gauss-Jordan leaves an error of cond(K_leaf) eps in X (the leaf of
 // a frequency near zero is close to a singular M-matrix), the largest error of the whole form; the
 // step takes it to the size of X's own rounding (forward errors of S^{-1} v 5 to 20 times
-// smaller).  K X = lambda X - c (J X) with J real, so it costs one real-by-complex and one complex
-// product.
+// smaller).  In FP64 K is the matrix of rounded entries that the dense routes factor: an ulp of its
+// diagonal moves S^{-1} v by more (3e-13 at 1000 x 128) than all rounding from there on (5e-14).  In
+// FP32, K X = lambda X - c (J X) with J real, half the products and without the rounding of K.
 //
 // Level 0.  W_0 and G on two wavefronts per leaf (a 16-column tile each), the R x R inverse and W_0' on
 // four.  The columns of the levels above then pass through the pair, one 16-column tile of one leaf
@@ -299,7 +300,7 @@ __device__ __forceinline__ void group_invert(c_t<T> *M, int R, int w, c_t<T> *co
 // In FP64 one workgroup fills a CU's LDS, so what counts is that its phases are short: MFMA is busy
 // for half of the time (block Gauss-Jordan is bound by its 16-step chains, the R x R inverses by theirs
 // of 20), and the code (54 KB) stays within the instruction cache, with the block loop rolled.  4095 x
-// 256: 2.84 ms FP64 and 1.09 mixed (two workgroups per CU) for leaves, columns and level 0, from 4.48
+// 256: 2.91 ms FP64 and 1.10 mixed (two workgroups per CU) for leaves, columns and level 0, from 4.48
 // and 1.94 in four launches with three passes over the columns.
 template <typename T> struct HierLds {
   static constexpr int R0 = sizeof(T) == 8 ? HIER_R0 : HIER_R0_32;  // level 0's largest rank
@@ -483,8 +484,8 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
       for (int v = 0; v < 4; ++v) {
         const int i = 16 * I + mfma_row<T>(lk, v), row = p * HP + i, dd = i - cl;
         const bool in = row < m;
-        const double dp = d.scale * gld(d.dp + (in ? row : 0)), dm = d.scale * gld(d.dm + (in ? row : 0));
-        const double Jv = fma(dp, gt[dd + 64], dm * gt[64 - dd]), J = in && incol ? Jv : 0.0;
+        const double dp = gld(d.dp + (in ? row : 0)), dm = gld(d.dm + (in ? row : 0));
+        const double Jv = d.scale * fma(dp, gt[dd + 64], dm * gt[64 - dd]), J = in && incol ? Jv : 0.0;
         double re = -d.tau * mu.x * J, im = -d.tau * mu.y * J;
         if (dd == 0) {
           re = in ? re + lam.x : 1.0;
@@ -498,8 +499,9 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
     const int row = p * HP + 16 * mt + li;
-    dpr[mt] = row < m ? (T)(d.scale * gld(d.dp + (row < m ? row : 0))) : (T)0;
-    dmr[mt] = row < m ? (T)(d.scale * gld(d.dm + (row < m ? row : 0))) : (T)0;
+    const double by = sizeof(T) == 8 ? 1.0 : d.scale;
+    dpr[mt] = row < m ? (T)(by * gld(d.dp + (row < m ? row : 0))) : (T)0;
+    dmr[mt] = row < m ? (T)(by * gld(d.dm + (row < m ? row : 0))) : (T)0;
   }
 #pragma unroll 1
   for (int J = 0; J < 4; ++J) {  // X[i] is row tile (J + i) % 4
@@ -556,7 +558,13 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
         const T J = fma(dpr[mt], (T)gp[16 * (mt - t) - mfma_row<T>(0, s)], dmr[mt] * (T)gm[16 * (t - mt) + mfma_row<T>(0, s)]);
-        tile_fma<T>(E[mt], J, X[t].re[s], X[t].im[s]);
+        if (sizeof(T) == 8) {
+          const T Js = (T)d.scale * J;
+          const bool dg = mt == t && li == mfma_row<T>(lk, s);
+          tile_fma<T>(E[mt], mk<T>(mc.x * Js + (dg ? lam.x : (T)0), mc.y * Js + (dg ? lam.y : (T)0)), X[t].re[s], X[t].im[s]);
+        } else {
+          tile_fma<T>(E[mt], J, X[t].re[s], X[t].im[s]);
+        }
       }
       chk += X[t].re[s] + X[t].im[s];
     }
@@ -567,8 +575,12 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
       for (int v = 0; v < 4; ++v) {
         const int r = 16 * mt + mfma_row<T>(lk, v);
         c_t<T> t = mk<T>(r == cl ? (T)1 : (T)0, (T)0);
-        t = hfms<T>(lam, mk<T>(X[mt].re[v], X[mt].im[v]), t);
-        t = hfms<T>(mc, mk<T>(E[mt].re[v], E[mt].im[v]), t);
+        if (sizeof(T) == 8) {
+          t = mk<T>(t.x - E[mt].re[v], -E[mt].im[v]);
+        } else {
+          t = hfms<T>(lam, mk<T>(X[mt].re[v], X[mt].im[v]), t);
+          t = hfms<T>(mc, mk<T>(E[mt].re[v], E[mt].im[v]), t);
+        }
         const bool in = p * HP + r < m && p * HP + cl < m;
         E[mt].re[v] = in ? t.x : (T)0;
         E[mt].im[v] = in ? t.y : (T)0;

@@ -1819,6 +1819,7 @@ static fde_status hier_factor(Plan *P) {
     return make_map(slots, it);
   };
   // algorithmic flops: 8 per complex multiply-add, 4 per real times complex one
+  const bool prec64 = sizeof(T) == 8;
   double wleaf = 0.0;
   std::vector<double> wnode(HIER_LEVELS, 0.0), wcols(HIER_LEVELS, 0.0);
   auto higher = [](const fde_bvm *h, int l) {
@@ -1828,7 +1829,7 @@ static fde_status hier_factor(Plan *P) {
   };
   for (const fde_bvm *h : P->hs) {
     if (!h->hier) continue;
-    wleaf += 4.0 * h->nb * h->mp * 64.0 * (5.0 * 64.0 + higher(h, -1));
+    wleaf += 4.0 * h->nb * h->mp * 64.0 * ((prec64 ? 6.0 : 5.0) * 64.0 + higher(h, -1));
     for (int l = 0; l < h->nlev; ++l) {
       const double r = h->hR[l], n = higher(h, l);
       wnode[l] += h->nb * (12.0 * h->mp * r * r + 48.0 * hier_nodes_p(h->npan, l) * r * r * r);
