@@ -53,8 +53,8 @@ PMC_KERNEL_GROUP = {
 }
 # Per measured workload: the source hashes of every kernel group when its counters were taken,
 # and the bytes per launch.  Workload keys: the bench workload, plus a route letter for the
-# routes compared beside the headline ("c2h": Hessenberg route at 1023x512, "c3l": block-LU
-# route at 4095x256; "c3" itself is the band route, the default there).
+# routes compared beside the headline ("c2h": Hessenberg route at 1023x512, "c3b" and "c3l": band
+# and block-LU routes at 4095x256; "c3" itself has the hierarchical blocks, the default there).
 PMC_MEASURED = {
     "c2": {"hash": {"factor": "c53d9b1c3810c0bd", "spacetime": "41b6c6d79eb78c42", "krylov": "a336f5b3ef0ee3cb"},
            "bytes": {
@@ -76,27 +76,31 @@ PMC_MEASURED = {
                 ("mixed", "hess_reduce"): 6.8204e+09, ("mixed", "hess_uinv"): 2.1905e+08,
                 ("mixed", "qgemm"): 5.2862e+07, ("mixed", "trsv"): 1.3156e+09}},
     # profiles/hbm_traffic_m4095_s256_gbdf3.txt
-    "c3": {"hash": {"factor": "da95ccf4032e6e85", "spacetime": "7d1eafc888daca2c", "krylov": "5584998f77183f5e",
-                    "hessenberg": "6ab681476fb4a268", "band": "6851e166aa9f8d8b"},
+    "c3": {"hash": {"hier": "1906dca0a9944c31", "spacetime": "0f1619def8dd30b9", "krylov": "50b514dae8dc2928"},
            "bytes": {
-               ("fp64", "trsv"): 1.7687e+10, ("fp64", "band_lu_step"): 9.8122e+08,
-               ("fp64", "band_lu_rows"): 4.2619e+07, ("fp64", "band_lu_panel"): 3.4665e+07,
-               ("fp64", "band_lsolve"): 1.0948e+09, ("fp64", "qgemm"): 2.1053e+08,
-               ("fp64", "band_panel"): 1.4629e+07, ("fp64", "band_init"): 2.6943e+08,
-               ("fp64", "mgs"): 3.1258e+07, ("fp64", "bvm_matvec"): 1.9734e+07,
-               ("fp64", "time_rfft"): 1.7079e+07, ("fp64", "time_irfft"): 1.6881e+07,
-               ("fp64", "normalize"): 1.6917e+07, ("mixed", "trsv"): 9.3656e+09,
-               ("mixed", "band_lu_step"): 6.9877e+08, ("mixed", "band_lu_rows"): 2.1533e+07,
-               ("mixed", "band_lu_panel"): 1.7741e+07, ("mixed", "band_lsolve"): 5.5800e+08,
-               ("mixed", "qgemm"): 2.1053e+08, ("mixed", "band_panel"): 1.4629e+07,
-               ("mixed", "band_init"): 2.6943e+08}},
-    "c3l": {"hash": {"factor": "da95ccf4032e6e85", "spacetime": "7d1eafc888daca2c", "krylov": "5584998f77183f5e"},
+               ("fp64", "hier_leaf"): 2.6758e+09, ("fp64", "hier_node"): 7.5209e+08,
+               ("fp64", "hier_cols"): 1.6609e+09, ("fp64", "hier_sub"): 1.0322e+09,
+               ("fp64", "hier_up"): 3.2743e+08, ("mixed", "hier_leaf"): 1.0703e+09,
+               ("mixed", "hier_node"): 2.3723e+08, ("mixed", "hier_cols"): 5.3949e+08,
+               ("mixed", "hier_sub"): 4.5128e+08, ("mixed", "hier_up"): 1.1706e+08,
+               ("fp64", "mgs"): 9.0766e+07, ("fp64", "bvm_matvec"): 4.4981e+07,
+               ("fp64", "time_rfft"): 2.0748e+07, ("fp64", "time_irfft"): 1.6904e+07}},
+    "c3b": {"hash": {"factor": "d6f84b1eccd5a802", "band": "25254ed24f34b195", "hessenberg": "ed9a807ae6d95f67"},
            "bytes": {
-               ("fp64", "lu_update"): 2.2898e+10, ("fp64", "trsv"): 3.5387e+10,
+               ("fp64", "trsv"): 1.7694e+10, ("fp64", "band_lu_step"): 9.8113e+08,
+               ("fp64", "band_lu_rows"): 4.2620e+07, ("fp64", "band_lsolve"): 1.0948e+09,
+               ("mixed", "trsv"): 9.3536e+09, ("mixed", "band_lu_step"): 6.9834e+08,
+               ("mixed", "band_lu_rows"): 2.1526e+07, ("mixed", "band_lsolve"): 5.5800e+08,
+               ("fp64", "qgemm"): 2.1053e+08, ("mixed", "qgemm"): 2.1053e+08,
+               ("fp64", "band_panel"): 1.4625e+07, ("mixed", "band_panel"): 1.4625e+07,
+               ("fp64", "band_init"): 2.6943e+08}},
+    "c3l": {"hash": {"factor": "d6f84b1eccd5a802"},
+           "bytes": {
+               ("fp64", "lu_update"): 2.2899e+10, ("fp64", "trsv"): 3.5385e+10,
                ("fp64", "lu_panel"): 1.1004e+09, ("fp64", "lu_diag"): 3.4090e+07,
-               ("fp64", "assemble"): 2.1333e+09, ("mixed", "lu_update"): 9.5230e+09,
-               ("mixed", "trsv"): 1.8712e+10, ("mixed", "lu_panel"): 6.3364e+08,
-               ("mixed", "lu_diag"): 1.7037e+07, ("mixed", "assemble"): 1.0673e+09}},
+               ("fp64", "assemble"): 2.1333e+09, ("mixed", "lu_update"): 9.5275e+09,
+               ("mixed", "trsv"): 1.8712e+10, ("mixed", "lu_panel"): 6.3521e+08,
+               ("mixed", "lu_diag"): 1.7036e+07, ("mixed", "assemble"): 1.0670e+09}},
 }
 
 

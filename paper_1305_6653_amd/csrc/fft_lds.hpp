@@ -7,7 +7,8 @@
 //          unnormalised (Cooley-Tukey decimation in time).
 // Pairing the two needs no permutation at all: a spectrum is multiplied pointwise in
 // bit-reversed order (the multiplier is stored bit-reversed), which is how the
-// Toeplitz products through a circulant embedding use them.
+// Toeplitz products through a circulant embedding use them (k_bvm_matvec, with passes of its own
+// in the same order of operations).
 //
 // tw[t] = e^{-2 pi i t/N}, t < N/2, precomputed in FP64 on the host.
 // Every thread of the block must call these (they contain __syncthreads()).
