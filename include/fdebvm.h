@@ -383,7 +383,7 @@ fde_status fde_profile_query(const fde_bvm *h, const char *name, double *total_m
  * spatial positions (channels = the s+1 time levels of f normalised by its RMS, d+, d-,
  * alpha-1.5), three fully connected layers, and a fixed synthesis basis
  * cos(q pi t) sin(p pi x/2) (q < nt, p < nx) that maps the nx*nt coefficients to [s][m].
- * Convolutions are im2col + GEMM; every GEMM runs on bf16 MFMA with FP32 accumulation;
+ * Convolutions are GEMMs over their input windows; every GEMM runs on bf16 MFMA with FP32 accumulation;
  * weights are FP32 masters with bf16 copies; Adam updates the masters.
  * Parameter layout (FP32 vector): per layer l = conv1..3, fc1..3, W_l [kin][kout] row-major
  * then b_l [kout]; conv kin = 5*Cin with element (t, c) at t*Cin + c (tap t reads position
