@@ -421,6 +421,7 @@ struct Plan {
   // solve maps over all instances, in their own allocation (recorded graphs refer to them)
   SolveMaps full;
   bool full_ok = false;
+  std::vector<char> full_hier;  // the instances' form (fde_bvm::hier) that the maps were made for
   bool trsv_solo = false;  // the block solve's launch form (see trsv_solo_choice)
   int *d_fullmaps = nullptr;
   size_t fullmaps_ints = 0;
@@ -2002,7 +2003,6 @@ static fde_status factor_plan(Plan *P, fde_precision prec) {
     }
     if (!use && route == FDE_BLOCKS_HESSENBERG && h->m > hess_reduce_max_m())
       return fail(FDE_EUNSUPPORTED, "the Hessenberg route takes m <= %d (m = %d)", hess_reduce_max_m(), h->m);
-    if (use != h->hier && h->self) h->self->full_ok = false;
     h->hier = use;
   }
   return factor_blocks(P, route, prec);
@@ -2017,15 +2017,21 @@ extern "C" fde_status fde_precond_factor(fde_bvm *h, fde_precision prec) {
 // solve-phase maps and operators over a plan
 // ====================================================================================
 // Maps over every instance of the plan (gates select the instances of a launch), uploaded
-// into the plan's own buffer.  Rebuilt only when the item counts change (block-solve W or
-// precision); recorded graphs refer to this buffer, so a rebuild drops them.
+// into the plan's own buffer.  Rebuilt only when the item counts change (block-solve W,
+// precision, preconditioner, dense route or the form of an instance's blocks); recorded graphs
+// refer to this buffer, so a rebuild drops them.
 static fde_status ensure_full_maps(Plan *P) {
   const int count = (int)P->hs.size();
   const int prec = P->hs[0]->prec;
   int route = P->hs[0]->blk_route;  // of the instances in dense form
   for (int q = count - 1; q >= 0; --q)
     if (!P->hs[q]->hier) route = P->hs[q]->blk_route;
-  if (P->full_ok && P->full.prec == prec && P->full.pc == P->hs[0]->pc && P->full.route == route)
+  // The forms are compared here, not dropped where they change: a factorization with another
+  // preconditioner in between leaves neither maps nor a trace of the form that they are for.
+  std::vector<char> form(count);
+  for (int q = 0; q < count; ++q) form[q] = P->hs[q]->hier ? 1 : 0;
+  if (P->full_ok && P->full.prec == prec && P->full.pc == P->hs[0]->pc && P->full.route == route &&
+      P->full_hier == form)
     return FDE_OK;
   std::vector<int> slots(count), a(count), b(count), c(count), d(count), e(count), f(count), g(count),
       qq(count);
@@ -2162,6 +2168,7 @@ static fde_status ensure_full_maps(Plan *P) {
     if (!h->hier) S.npan_u = S.npan_u < 0 || h->npan == S.npan_u ? h->npan : 0;
   S.npan_u = std::max(S.npan_u, 0);
   P->full = S;
+  P->full_hier = std::move(form);
   P->full_ok = true;
   return FDE_OK;
 }

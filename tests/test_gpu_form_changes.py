@@ -1,0 +1,47 @@
+"""A handle that is factored again with its blocks in another form (hierarchical, or one of the dense
+routes) solves with the new factors, also where a factorization with another preconditioner lies
+between the two and nothing was applied with it: bit for bit as a handle that knows only the last
+factorization."""
+import numpy as np
+import pytest
+
+import workloads as W
+from paper_1305_6653_amd import BvmSolver
+from paper_1305_6653_amd import _native as N
+
+pytestmark = pytest.mark.gpu
+
+# (FDE_OPT_COMPRESS, blocks) of a Strang factorization; 300 x 16 is hierarchical by default
+FORMS = {"hier": (1, "auto"), "auto_dense": (0, "auto"), "lu": (1, "lu"), "hessenberg": (1, "hessenberg"),
+         "band": (1, "band")}
+
+
+def _factor(S, form, prec):
+    compress, blocks = FORMS[form]
+    S.set_option(N.FDE_OPT_COMPRESS, compress)
+    S.factor(prec, "strang", blocks)
+    assert S.get_option(N.FDE_OPT_COMPRESS_IN_USE) == (1 if form == "hier" else 0)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("between", [None, "bccb", "none"])
+@pytest.mark.parametrize("first,then", [("hier", f) for f in FORMS if f != "hier"] + [("lu", "hier"), ("band", "hier")])
+def test_refactored_in_another_form(first, then, between, prec):
+    p, q = W.tiny(300, 16, 1.3, 1, "gbdf3"), W.tiny(300, 16, 1.7, 2, "gbdf3")
+    v = np.random.default_rng(5).standard_normal((q.s, q.m))
+    S, T = BvmSolver(p), BvmSolver(q)
+    for X in (S, T):
+        X.set_option(N.FDE_OPT_AUTOTUNE, 0)
+    _factor(S, first, prec)
+    S.precond(v)
+    S.solve(p.u0, p.f)
+    if between is not None:
+        S.factor(prec, between)
+    S.set_coefficients(q.alpha, q.d_plus, q.d_minus)
+    _factor(S, then, prec)
+    _factor(T, then, prec)
+    assert np.array_equal(S.precond(v), T.precond(v))
+    (u, i), (w, j) = S.solve(q.u0, q.f), T.solve(q.u0, q.f)
+    assert np.array_equal(u, w) and i["iters"] == j["iters"]
+    S.close()
+    T.close()
