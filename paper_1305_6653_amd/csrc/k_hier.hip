@@ -289,7 +289,12 @@ __device__ __forceinline__ void group_invert(c_t<T> *M, int R, int w, c_t<T> *co
 // step takes it to the size of X's own rounding (forward errors of S^{-1} v 5 to 20 times
 // smaller).  In FP64 K is the matrix of rounded entries that the dense routes factor: an ulp of its
 // diagonal moves S^{-1} v by more (3e-13 at 1000 x 128) than all rounding from there on (5e-14).  In
-// FP32, K X = lambda X - c (J X) with J real, half the products and without the rounding of K.
+// FP32, K X = lambda X - c (J X) with J real, half the products, and all of it in FP64: X's own rounding
+// is then what is left of the leaf's error.  In FP32 the weights g are off by the same amount in
+// every row (by nothing where alpha, the diagonal's weight, is an FP32 number), and with constant
+// coefficients so are the entries and the sums; such errors add up over the leaves where others cancel.
+// Error of a single application at 1800 x 8, alpha = 1.3: 3.6e-4 with the residual in FP32, 8e-6 so,
+// 6.2e-5 with dense FP32 factors; the kernel at 4095 x 256: 1.08 and 1.14 ms.
 //
 // Level 0.  W_0 and G on two wavefronts per leaf (a 16-column tile each), the R x R inverse and W_0' on
 // four.  The columns of the levels above then pass through the pair, one 16-column tile of one leaf
@@ -300,7 +305,7 @@ __device__ __forceinline__ void group_invert(c_t<T> *M, int R, int w, c_t<T> *co
 // In FP64 one workgroup fills a CU's LDS, so what counts is that its phases are short: MFMA is busy
 // for half of the time (block Gauss-Jordan is bound by its 16-step chains, the R x R inverses by theirs
 // of 20), and the code (54 KB) stays within the instruction cache, with the block loop rolled.  4095 x
-// 256: 2.91 ms FP64 and 1.10 mixed (two workgroups per CU) for leaves, columns and level 0, from 4.48
+// 256: 2.91 ms FP64 and 1.14 mixed (two workgroups per CU) for leaves, columns and level 0, from 4.48
 // and 1.94 in four launches with three passes over the columns.
 template <typename T> struct HierLds {
   static constexpr int R0 = sizeof(T) == 8 ? HIER_R0 : HIER_R0_32;  // level 0's largest rank
@@ -495,13 +500,14 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
         X[I].im[v] = (T)im;
       }
   }
-  T dpr[4], dmr[4];  // d+- at rows 16 mt + li, for the Newton step
+  double dpr[4], dmr[4];  // FP64: d+- at rows 16 mt + li, for the Newton step
+  if constexpr (sizeof(T) == 8) {
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    const int row = p * HP + 16 * mt + li;
-    const double by = sizeof(T) == 8 ? 1.0 : d.scale;
-    dpr[mt] = row < m ? (T)(by * gld(d.dp + (row < m ? row : 0))) : (T)0;
-    dmr[mt] = row < m ? (T)(by * gld(d.dm + (row < m ? row : 0))) : (T)0;
+    for (int mt = 0; mt < 4; ++mt) {
+      const int row = p * HP + 16 * mt + li;
+      dpr[mt] = row < m ? gld(d.dp + (row < m ? row : 0)) : 0.0;
+      dmr[mt] = row < m ? gld(d.dm + (row < m ? row : 0)) : 0.0;
+    }
   }
 #pragma unroll 1
   for (int J = 0; J < 4; ++J) {  // X[i] is row tile (J + i) % 4
@@ -541,50 +547,68 @@ __global__ __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) void k_hier_leaf(const
   lds_barrier();
   ctile<T> E[4];
   if (mine) {  // E = I - K X; X into LDS
-    const c_t<T> lam = mk<T>((T)d.lam[k].x, (T)d.lam[k].y);
     T chk = (T)0;
-    // g_{i-j+1} and g_{j-i+1} for row i = 16 mt + li, column j = 16 t + mfma_row(lk, s).  Rows j of X
-    // from m on are zero in the columns before m, and E is only taken there.
-    const double *gp = gt + 64 + li - mfma_row<T>(lk, 0), *gm = gt + 64 - li + mfma_row<T>(lk, 0);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) LX[lx(cl, 16 * mt + mfma_row<T>(lk, v))] = mk<T>(X[mt].re[v], X[mt].im[v]);
-      E[mt].zero();
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int t = e >> 2, s = e & 3;
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const T J = fma(dpr[mt], (T)gp[16 * (mt - t) - mfma_row<T>(0, s)], dmr[mt] * (T)gm[16 * (t - mt) + mfma_row<T>(0, s)]);
-        if (sizeof(T) == 8) {
-          const T Js = (T)d.scale * J;
-          const bool dg = mt == t && li == mfma_row<T>(lk, s);
-          tile_fma<T>(E[mt], mk<T>(mc.x * Js + (dg ? lam.x : (T)0), mc.y * Js + (dg ? lam.y : (T)0)), X[t].re[s], X[t].im[s]);
-        } else {
-          tile_fma<T>(E[mt], J, X[t].re[s], X[t].im[s]);
-        }
-      }
-      chk += X[t].re[s] + X[t].im[s];
-    }
-    bad = !isfinite(chk);
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
+        LX[lx(cl, 16 * mt + mfma_row<T>(lk, v))] = mk<T>(X[mt].re[v], X[mt].im[v]);
+        chk += X[mt].re[v] + X[mt].im[v];
+      }
+    bad = !isfinite(chk);
+    // This lane's row of tile mt as a left operand: 16 mt + ri, so that a result's rows are X's.  gp and gm:
+    // g_{i-j+1} and g_{j-i+1} for that row i and column j = 16 t + mfma_row(lk, s).  Rows j of X from m on
+    // are zero in the columns before m, and E is only taken there.
+    const int ri = rowstr<T>(li);
+    const double *gp = gt + 64 + ri - mfma_row<T>(lk, 0), *gm = gt + 64 - ri + mfma_row<T>(lk, 0);
+    if constexpr (sizeof(T) == 8) {
+      const double2 lam = d.lam[k];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) E[mt].zero();
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int t = e >> 2, s = e & 3;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const double J = d.scale * fma(dpr[mt], gp[16 * (mt - t) - mfma_row<T>(0, s)],
+                                         dmr[mt] * gm[16 * (t - mt) + mfma_row<T>(0, s)]);
+          const bool dg = mt == t && li == mfma_row<T>(lk, s);
+          tile_fma<T>(E[mt], mk<T>(mc.x * J + (dg ? lam.x : 0.0), mc.y * J + (dg ? lam.y : 0.0)), X[t].re[s], X[t].im[s]);
+        }
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      v4d jr = {0, 0, 0, 0}, ji = {0, 0, 0, 0};  // FP32: rows of J X
+      if constexpr (sizeof(T) == 4) {
+        const int row = p * HP + 16 * mt + ri;
+        const double sc = row < m ? d.scale : 0.0;
+        const double dp = sc * gld(d.dp + (row < m ? row : 0)), dm = sc * gld(d.dm + (row < m ? row : 0));
+        asm volatile("" ::: "memory");  // the weights are read again for each mt, not held
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int t = e >> 2, s = e & 3;
+          const double J = fma(dp, gp[16 * (mt - t) - mfma_row<T>(0, s)], dm * gm[16 * (t - mt) + mfma_row<T>(0, s)]);
+          jr = mfma16(J, (double)X[t].re[s], jr);
+          ji = mfma16(J, (double)X[t].im[s], ji);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
         const int r = 16 * mt + mfma_row<T>(lk, v);
-        c_t<T> t = mk<T>(r == cl ? (T)1 : (T)0, (T)0);
-        if (sizeof(T) == 8) {
-          t = mk<T>(t.x - E[mt].re[v], -E[mt].im[v]);
+        double2 t = make_double2(r == cl ? 1.0 : 0.0, 0.0);
+        if constexpr (sizeof(T) == 8) {
+          t = make_double2(t.x - E[mt].re[v], -E[mt].im[v]);
         } else {
-          t = hfms<T>(lam, mk<T>(X[mt].re[v], X[mt].im[v]), t);
-          t = hfms<T>(mc, mk<T>(E[mt].re[v], E[mt].im[v]), t);
+          const double2 lam = d.lam[k], mu = d.mu[k];
+          t = hfms<double>(lam, make_double2(X[mt].re[v], X[mt].im[v]), t);
+          t = hfma<double>(make_double2(d.tau * mu.x, d.tau * mu.y), make_double2(jr[v], ji[v]), t);
         }
         const bool in = p * HP + r < m && p * HP + cl < m;
-        E[mt].re[v] = in ? t.x : (T)0;
-        E[mt].im[v] = in ? t.y : (T)0;
+        E[mt].re[v] = in ? (T)t.x : (T)0;
+        E[mt].im[v] = in ? (T)t.y : (T)0;
       }
+    }
   }
   lds_barrier();
   if (mine) {
