@@ -343,14 +343,17 @@ fde_status fde_time_rfft(fde_bvm *h, const double *v, double *vhat, int mem_spac
 /* z = S^{-1} v (time DFT, block solves with the stored factors, inverse DFT), [s][m]. */
 fde_status fde_apply_precond(fde_bvm *h, const double *v, double *z, int mem_space);
 /* z = S^{-1} v like fde_apply_precond, allocating nothing: for callers that cannot allocate
- * device memory (code under stream capture, tight serving loops, harnesses that forbid
+ * device memory (code that captures another stream, tight serving loops, harnesses that forbid
  * hipMalloc).  v and z are DEVICE pointers ([s][m]); the handle must have been factored with
- * the Strang preconditioner and block LU factors (the default).  The working memory of the
+ * the Strang preconditioner and FDE_BLOCKS_LU as FDE_OPT_BLOCKS_IN_USE (with or without the
+ * hierarchical form; the default below FDE_BAND_MIN_M_*).  The call waits for its result, so the
+ * handle's own stream must not be capturing (FDE_EDEVICE).  The working memory of the
  * call (the frequency-domain vector, the block-solve flags and counters, the launch
- * descriptor) is one fixed static device array of FDE_NOALLOC_SCRATCH_BYTES per GPU, held
- * until the process ends; its address is looked up once per device at fde_bvm_setup.  Every
- * call on a GPU shares that array: calls that overlap on one GPU (from other threads or on
- * other streams) race, so a caller serialises them.  The result equals fde_apply_precond's
+ * descriptor) is one fixed static device array of FDE_NOALLOC_SCRATCH_BYTES per GPU, and a second
+ * of nearly that size for the panel sums of the hierarchical form, held until the process ends;
+ * their addresses are looked up once per device at fde_bvm_setup.  The call writes nothing that
+ * belongs to the handle.  Every call on a GPU shares the arrays: calls that overlap on one GPU
+ * (from other threads or on other streams) race, so a caller serialises them.  The result equals fde_apply_precond's
  * bit for bit (same kernels, same launch shapes).  Errors: FDE_EINVAL for NULL arguments or an
  * unfactored handle; FDE_EUNSUPPORTED when (s/2+1) * mp * 16 bytes of frequency vector (mp =
  * m rounded up to 64) plus its flags exceed the array (m = 4095 fits up to s = 256, m = 1023

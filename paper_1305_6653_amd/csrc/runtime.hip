@@ -237,7 +237,10 @@ struct fde_bvm {
 // ====================================================================================
 // device memory helpers
 // ====================================================================================
-static fde_status noalloc_scratch(void **out);
+struct NoallocArrays {  // the arrays of fde_apply_precond_noalloc on one device
+  void *base = nullptr, *sums = nullptr;
+};
+static fde_status noalloc_scratch(NoallocArrays *out);
 
 static fde_status dalloc_raw(void **p, size_t bytes) {
   *p = nullptr;
@@ -1202,7 +1205,7 @@ extern "C" fde_status fde_bvm_setup(const fde_problem *p, fde_bvm **out) {
   }
   h->stream = h->own_stream;
   {
-    void *na = nullptr;  // the allocation-free apply's array: address looked up once per device
+    NoallocArrays na;  // the allocation-free apply's arrays: addresses looked up once per device
     fde_status sst = noalloc_scratch(&na);
     if (sst != FDE_OK) return bail(sst);
   }
@@ -3051,11 +3054,16 @@ extern "C" fde_status fde_apply_precond(fde_bvm *h, const double *v, double *z, 
 // error flag) in the first NA_HEAD bytes, the block-solve flags [nb][npan][2] in the next
 // NA_FLAGS bytes (a region of their own, so no other use of the array ever overwrites them:
 // every apply draws a larger epoch from the array's own counter, and flags only ever hold
-// earlier epochs), then the frequency-domain vector [nb][mp] complex FP64.
+// earlier epochs), then the frequency-domain vector [nb][mp] complex FP64.  A second array holds
+// the panel sums of the hierarchical form, 2 x [nb][npan][32] complex, at most the frequency vector's
+// size (mp = 64 npan): they are not the handle's, whose own applies may be queued between this one's
+// launches by another thread.
 static constexpr size_t NA_BYTES = (size_t)FDE_NOALLOC_SCRATCH_BYTES;
 static constexpr size_t NA_HEAD = 4096;
 static constexpr size_t NA_FLAGS = 512u << 10;
 static __device__ __align__(256) unsigned char scratch[NA_BYTES];
+static __device__ __align__(256) unsigned char scratch_sums[NA_BYTES - NA_HEAD - NA_FLAGS];
+static_assert(HIER_RMAX == 32, "panel sums: one 16-byte entry per row of two planes");
 
 struct NoallocHead {
   InstDesc desc;
@@ -3068,21 +3076,24 @@ struct NoallocHead {
 static_assert(sizeof(NoallocHead) <= NA_HEAD, "launch head exceeds its region");
 
 static std::mutex g_scratch_mu;
-static void *g_scratch_ptr[64] = {};
+static NoallocArrays g_scratch_ptr[64];
 
-// Device address of this GPU's array (the name `scratch` is a host-side stand-in): looked up
-// once per device, with that device current, and kept.
-static fde_status noalloc_scratch(void **out) {
+// Device addresses of this GPU's arrays (the names are host-side stand-ins): looked up once per
+// device, with that device current, and kept.
+static fde_status noalloc_scratch(NoallocArrays *out) {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return fail(FDE_EDEVICE, "device index %d out of range", dev);
   std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch_ptr[dev]) {
-    void *p = nullptr;
+  NoallocArrays &a = g_scratch_ptr[dev];
+  if (!a.base) {
+    void *p = nullptr, *q = nullptr;
     HIPCHK(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    g_scratch_ptr[dev] = p;
+    HIPCHK(hipGetSymbolAddress(&q, HIP_SYMBOL(scratch_sums)));
+    a.sums = q;
+    a.base = p;
   }
-  *out = g_scratch_ptr[dev];
+  *out = a;
   return FDE_OK;
 }
 
@@ -3114,9 +3125,9 @@ extern "C" fde_status fde_apply_precond_noalloc(fde_bvm *h, const double *v, dou
   if (h->prec < 0) return fail(FDE_EINVAL, "fde_precond_factor must succeed first");
   if (h->pc != FDE_PC_STRANG || h->blk_route != FDE_BLOCKS_LU)
     return fail(FDE_EUNSUPPORTED, "the allocation-free apply takes the Strang preconditioner with block LU factors");
-  void *base = nullptr;
-  STCHK(noalloc_scratch(&base));
-  unsigned char *b = (unsigned char *)base;
+  NoallocArrays na;
+  STCHK(noalloc_scratch(&na));
+  unsigned char *b = (unsigned char *)na.base;
   NoallocHead *hd = (NoallocHead *)b;
   // launch shapes as the handle's own apply takes them (same kernels, same bits)
   int dev = 0, cus = 0;
@@ -3132,6 +3143,7 @@ extern "C" fde_status fde_apply_precond_noalloc(fde_bvm *h, const double *v, dou
   d.tsflags = (unsigned long long *)(b + NA_HEAD);
   d.Vh = (double2 *)(b + NA_HEAD + NA_FLAGS);
   d.Vts = d.Vh;
+  d.ha = na.sums;
   hipStream_t st = h->stream;
   const int n_hier = h->nb * ((h->npan + HIER_CHUNK - 1) / HIER_CHUNK);
   hipLaunchKernelGGL(k_noalloc_head, dim3(1), dim3(64), 0, st, hd, d, n_tfft, n_trsv, n_blk, n_hier);
@@ -3141,7 +3153,7 @@ extern "C" fde_status fde_apply_precond_noalloc(fde_bvm *h, const double *v, dou
   const ItemMap trsv{hd->ids, hd->pre_trsv, 1, nullptr};
   const ItemMap blk{hd->ids, hd->pre_blk, 1, nullptr};
   HIPCHK(launch_time_rfft(D, tfft, n_tfft, h->log2s, cols, VS_SIO, 0, st, &hd->ctr, hd->epoch));
-  if (h->hier) {  // its panel partials are the handle's own, everything else as below
+  if (h->hier) {
     const ItemMap hm{hd->ids, hd->pre_hier, 1, nullptr};
     const bool f64 = h->prec == FDE_FP64;
     HIPCHK(f64 ? launch_hier_sub<double>(D, hm, n_hier, st) : launch_hier_sub<float>(D, hm, n_hier, st));
