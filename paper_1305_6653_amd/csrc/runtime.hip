@@ -1950,6 +1950,12 @@ static fde_status factor_blocks(Plan *P, int route, fde_precision prec) {
   return FDE_OK;
 }
 
+static fde_status dense_route_takes(const fde_bvm *h, int route) {
+  if (route == FDE_BLOCKS_HESSENBERG && h->m > hess_reduce_max_m())
+    return fail(FDE_EUNSUPPORTED, "the Hessenberg route takes m <= %d (m = %d)", hess_reduce_max_m(), h->m);
+  return FDE_OK;
+}
+
 static fde_status factor_plan(Plan *P, fde_precision prec) {
   if (prec != FDE_FP64 && prec != FDE_MIXED_C32) return fail(FDE_EINVAL, "unknown precision %d", (int)prec);
   TraceRange tr_factor("fde_precond_factor");
@@ -2004,8 +2010,7 @@ static fde_status factor_plan(Plan *P, fde_precision prec) {
       STCHK(hier_tables(h));
       use = h->hx_state > 0 ? 1 : 0;
     }
-    if (!use && route == FDE_BLOCKS_HESSENBERG && h->m > hess_reduce_max_m())
-      return fail(FDE_EUNSUPPORTED, "the Hessenberg route takes m <= %d (m = %d)", hess_reduce_max_m(), h->m);
+    if (!use) STCHK(dense_route_takes(h, route));
     h->hier = use;
   }
   return factor_blocks(P, route, prec);
@@ -3208,9 +3213,11 @@ extern "C" fde_status fde_toeplitz_apply(fde_bvm *h, const double *x, double *y,
 }
 
 // The dense factors behind a factorization in hierarchical form, made when they are first asked for
-// (the solves keep the hierarchical form).
+// (the solves keep the hierarchical form).  A form that was asked for whatever the dense route
+// (FDE_OPT_COMPRESS = 2) may stand in for one that does not take the size.
 static fde_status ensure_dense(fde_bvm *h) {
   if (!h->hier || h->dense_ok) return FDE_OK;
+  STCHK(dense_route_takes(h, h->blk_route));
   const fde_precision prec = (fde_precision)h->prec;
   const double ms = h->t_factor_ms;
   h->hier = 0;

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from paper_1305_6653_amd import BvmSolver
+from paper_1305_6653_amd import BvmSolver, FdeError
 from paper_1305_6653_amd import _native as N
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +45,21 @@ def test_refactored_in_another_form(first, then, between, prec):
     assert np.array_equal(u, w) and i["iters"] == j["iters"]
     S.close()
     T.close()
+
+
+def test_dense_factors_that_do_not_exist_are_refused():
+    """The hierarchical form may stand in for a dense route that does not take the size (Hessenberg,
+    m > 1024): its factors are then refused as the route is, and the handle goes on."""
+    p = W.tiny(1100, 8, 1.5, 3, "gbdf3")
+    v = np.random.default_rng(6).standard_normal((p.s, p.m))
+    S = BvmSolver(p)
+    S.set_option(N.FDE_OPT_COMPRESS, 2)
+    S.factor("fp64", blocks="hessenberg")
+    assert S.get_option(N.FDE_OPT_COMPRESS_IN_USE) == 1
+    z = S.precond(v)
+    for call in (lambda: S.factor_block(0), S.hessenberg):
+        with pytest.raises(FdeError) as e:
+            call()
+        assert e.value.status == N.FDE_EUNSUPPORTED
+    assert np.array_equal(S.precond(v), z)
+    S.close()
