@@ -198,10 +198,12 @@ struct fde_bvm {
   // LU [nb][npan][128], the reduction's workspace and error flag
   double *d_bAQ = nullptr, *d_bQt = nullptr, *d_bwork = nullptr;
   int *d_bpiv = nullptr, *d_berr = nullptr;
-  // ---- hierarchical form of the blocks (k_hier.hip): its basis tables (they depend on alpha only;
-  // hx_state 1: built, -1: this problem has none), ranks per level for FP64 and FP32 factors, and
-  // the factor storage (allocated when first factored that way).  hier: the current
-  // factorization is in this form; dense_ok: the dense factors of route blk_route are stored
+  // ---- hierarchical form of the blocks (k_hier.hip): its basis tables (they depend on alpha only and
+  // are kept while hx_alpha is the handle's; hx_state 1: built, -1: this problem has none), ranks per
+  // level for FP64 and FP32 factors, and the factor storage (allocated when first factored that
+  // way).  hier: the current factorization is in this form; dense_ok: the dense factors of route
+  // blk_route are stored
+  double hx_alpha = 0.0;
   int hx_state = 0, nlev = 0, hrank[2][HIER_LEVELS] = {};
   int hR[HIER_LEVELS] = {};
   int hier = 0;
@@ -959,11 +961,14 @@ static bool hier_basis(const fde_bvm *h, std::vector<double> &table, int rank[2]
   return true;
 }
 
-// Builds and uploads the tables once per coefficient set; hx_state -1 where the form does not apply:
+// Builds and uploads the tables when a factorization first takes the form, and again for another
+// alpha (new coefficients with the old one keep them); hx_state -1 where the form does not apply:
 // a time formula with Re(lambda_k conj mu_k) < 0 (then the blocks need not be dominant and only
 // the dense routes' arithmetic is known to be safe) or a basis that is too wide.
 static fde_status hier_tables(fde_bvm *h) {
-  if (h->hx_state != 0) return FDE_OK;
+  if (h->hx_state != 0 && h->hx_alpha == h->alpha) return FDE_OK;
+  h->hx_state = 0;
+  h->hx_alpha = h->alpha;
   h->nlev = 0;
   while ((1 << h->nlev) < h->npan) ++h->nlev;
   bool ok = true;
@@ -981,6 +986,7 @@ static fde_status hier_tables(fde_bvm *h) {
   }
   if (!table.empty()) {
     if (!h->d_hx) STCHK(dalloc_t(h, &h->d_hx, table.size()));
+    HIPCHK(hipStreamSynchronize(h->stream));  // the applies that read the old table
     HIPCHK(hipMemcpy(h->d_hx, table.data(), table.size() * sizeof(double), hipMemcpyHostToDevice));
   }
   h->hx_state = 1;
@@ -1271,7 +1277,6 @@ extern "C" fde_status fde_bvm_setup(const fde_problem *p, fde_bvm **out) {
     return bail(fail(FDE_EDEVICE, "symbol FFT launch failed: %s", hipGetErrorString(hipGetLastError())));
   if (hipStreamSynchronize(q) != hipSuccess) return bail(fail(FDE_EDEVICE, "setup synchronisation failed"));
   if ((st = plan_create({h}, &h->self)) != FDE_OK) return bail(st);
-  if (hier_auto(h) && (st = hier_tables(h)) != FDE_OK) return bail(st);
   *out = h;
   return FDE_OK;
 }
@@ -1304,8 +1309,6 @@ extern "C" fde_status fde_bvm_set_coefficients(fde_bvm *h, double alpha, const d
   HIPCHK(hipStreamSynchronize(h->stream));
   h->prec = -1;
   h->self->desc_dirty = true;
-  h->hx_state = 0;
-  if (hier_auto(h)) STCHK(hier_tables(h));
   return FDE_OK;
 }
 
