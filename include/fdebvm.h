@@ -300,7 +300,8 @@ typedef enum { FDE_ORTHO_MGS = 0, FDE_ORTHO_CGS2 = 1 } fde_ortho;
 fde_status fde_bvm_set_option(fde_bvm *h, int option, int value);
 fde_status fde_bvm_get_option(fde_bvm *h, int option, int *value);
 /* Autotuned choices of this process into buf (NUL-terminated), ';'-separated: "shape=W" for
- * the block solve (W = -1: the ordinary one-workgroup-per-block launch) and "shape/tfft=c" for
+ * the block solve (W = -1: the ordinary one-workgroup-per-block launch; a "c" behind the sizes of
+ * an instance in hierarchical form, which takes no part in it) and "shape/tfft=c" for
  * the time FFTs' spatial columns per workgroup (4, 8 or 16); FDE_EINVAL if len is too small. */
 fde_status fde_autotune_report(char *buf, int len);
 /* Measurement aid: the best of `reps` timed passes of a plain streaming-read kernel over a

@@ -633,13 +633,15 @@ static std::mutex g_tune_mu;
 static std::map<std::string, int> g_tuned_w;
 static std::map<std::string, int> g_tuned_cols;  // time-FFT spatial columns per workgroup
 
-static std::string plan_shape_key(const Plan *P, int prec) {
+// The sizes of a plan's instances, its precision and dense route.  For the block solve (forms) also
+// which instances are in hierarchical form: it runs over the others only.
+static std::string plan_shape_key(const Plan *P, int prec, bool forms) {
   std::string k = prec == FDE_FP64 ? "f64" : "c32";
   if (!P->hs.empty() && P->hs[0]->blk_route == FDE_BLOCKS_HESSENBERG) k += "h";
   if (!P->hs.empty() && P->hs[0]->blk_route == FDE_BLOCKS_BAND) k += "b";
   char buf[32];
   for (const fde_bvm *h : P->hs) {
-    snprintf(buf, sizeof buf, ":%dx%d", h->m, h->s);
+    snprintf(buf, sizeof buf, ":%dx%d%s", h->m, h->s, forms && h->hier ? "c" : "");
     k += buf;
   }
   return k;
@@ -678,7 +680,7 @@ static int trsv_wmax(const Plan *P, const fde_bvm *h, int prec) {
 static int trsv_choice(const Plan *P, int prec, int wmax) {
   if (P->lead->opt_trsv_w != 0) return P->lead->opt_trsv_w;
   std::lock_guard<std::mutex> lock(g_tune_mu);
-  auto it = g_tuned_w.find(plan_shape_key(P, prec));
+  auto it = g_tuned_w.find(plan_shape_key(P, prec, true));
   return it != g_tuned_w.end() ? it->second : wmax;
 }
 
@@ -2055,7 +2057,7 @@ static fde_status ensure_full_maps(Plan *P) {
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     S.tfft_cols = time_fft_cols_per_item(total_mp, std::max(cus, 1));
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    auto it = g_tuned_cols.find(plan_shape_key(P, prec));
+    auto it = g_tuned_cols.find(plan_shape_key(P, prec, false));
     if (it != g_tuned_cols.end()) S.tfft_cols = it->second;
   }
   std::vector<std::vector<int>> hu(HIER_LEVELS + 1, std::vector<int>(count, 0));
@@ -2740,7 +2742,7 @@ static fde_status autotune_trsv(Plan *P, int prec) {
   bool dense = false;
   for (const fde_bvm *h : P->hs) dense = dense || !h->hier;
   if (!dense) return FDE_OK;
-  const std::string key = plan_shape_key(P, prec);
+  const std::string key = plan_shape_key(P, prec, true);
   {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     if (g_tuned_w.count(key)) return FDE_OK;
@@ -2808,7 +2810,7 @@ static fde_status autotune_trsv(Plan *P, int prec) {
 static fde_status autotune_tfft(Plan *P, int prec) {
   fde_bvm *L = P->lead;
   if (!L->opt_autotune || L->pc == FDE_PC_NONE) return FDE_OK;
-  const std::string key = plan_shape_key(P, prec);
+  const std::string key = plan_shape_key(P, prec, false);
   {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     if (g_tuned_cols.count(key)) return FDE_OK;

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from paper_1305_6653_amd import BvmSolver, FdeError
+from paper_1305_6653_amd import BvmSolver, FdeError, autotune_report, factor_batch, solve_batch
 from paper_1305_6653_amd import _native as N
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +63,19 @@ def test_dense_factors_that_do_not_exist_are_refused():
         assert e.value.status == N.FDE_EUNSUPPORTED
     assert np.array_equal(S.precond(v), z)
     S.close()
+
+
+def test_block_solve_is_tuned_for_the_instances_that_take_part():
+    """The launch shape tuned for a batch with one dense instance is not taken for the same sizes with
+    every instance dense, and the other way round."""
+    ps = [W.tiny(330, 16, 1.4, 1, "gbdf3"), W.tiny(70, 16, 1.6, 2, "gbdf3")]
+    S = [BvmSolver(p) for p in ps]
+    for compress, key in ((1, "f64:330x16c:70x16="), (0, "f64:330x16:70x16=")):
+        assert key not in autotune_report()
+        for X in S:
+            X.set_option(N.FDE_OPT_COMPRESS, compress)
+        factor_batch(S, "fp64")
+        solve_batch(S, [p.u0 for p in ps], [p.f for p in ps])
+        assert key in autotune_report()
+    for X in S:
+        X.close()
