@@ -189,7 +189,10 @@ fde_status fde_get_dims(const fde_bvm *h, int *dims);
  *                         k > 0: cooperative, at most k workgroups per block (clamped to what
  *                         fits); -1: the ordinary launch, one workgroup per block, no flags.
  *   FDE_OPT_TRSV_W_IN_USE read-only: workgroups per block of the handle's last plan's
- *                         cooperative block solve, 0 for the ordinary launch.
+ *                         cooperative block solve, 0 for the ordinary launch and where the
+ *                         factorization is in hierarchical form.
+ * Instances in hierarchical form (FDE_OPT_COMPRESS, the default at most sizes) have no such block
+ * solve: FDE_OPT_TRSV_W and its tuning have no effect on them, only the time FFTs are tuned.
  *   FDE_OPT_GRAPHS_IN_USE read-only: 1 if the handle's solves replay recorded sequences.
  * Options of the first handle of a batch call apply to the call.  Setting an option
  * synchronises the handle's stream.  Unknown options return FDE_EINVAL. */
@@ -375,7 +378,10 @@ fde_status fde_get_hessenberg(fde_bvm *h, double *H, double *Q);
  * its duration is added to a per-kernel-name total.  Enabling clears the totals. */
 fde_status fde_profile_enable(fde_bvm *h, int enable);
 /* Total milliseconds, launch count and algorithmic work (flops or bytes, per the kernel:
- * FLOP for the LU kernels, bytes for the others) recorded for the kernel named `name`. */
+ * FLOP for the LU kernels, bytes for the others) recorded for the kernel named `name`.  A block
+ * factorization and its solves are lu_*, hess_* or band_* and trsv for dense factors; hier_leaf,
+ * hier_node and hier_cols, and hier_sub and hier_up, in hierarchical form (then none of the others
+ * is counted). */
 fde_status fde_profile_query(const fde_bvm *h, const char *name, double *total_ms, int *count,
                              double *work);
 

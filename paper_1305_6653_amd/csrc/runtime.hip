@@ -1385,7 +1385,7 @@ extern "C" fde_status fde_bvm_get_option(fde_bvm *h, int option, int *value) {
     case FDE_OPT_AUTOTUNE: *value = h->opt_autotune; return FDE_OK;
     case FDE_OPT_TRSV_W: *value = h->opt_trsv_w; return FDE_OK;
     case FDE_OPT_TRSV_W_IN_USE:
-      *value = h->self->desc.empty() || h->self->trsv_solo ? 0 : h->self->desc[0].W;
+      *value = h->self->desc.empty() || h->self->trsv_solo || (h->prec >= 0 && h->hier) ? 0 : h->self->desc[0].W;
       return FDE_OK;
     case FDE_OPT_GRAPHS_IN_USE: *value = graphs_recorded(h->self) ? 1 : 0; return FDE_OK;
     case FDE_OPT_SIDE: *value = h->opt_side; return FDE_OK;

@@ -79,3 +79,18 @@ def test_block_solve_is_tuned_for_the_instances_that_take_part():
         assert key in autotune_report()
     for X in S:
         X.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_block_solve_in_use(prec):
+    """FDE_OPT_TRSV_W_IN_USE names a block solve that runs: none in hierarchical form."""
+    p = W.tiny(300, 16, 1.5, 4, "gbdf3")
+    S = BvmSolver(p)
+    for form, runs in (("lu", True), ("hier", False), ("auto_dense", True)):
+        _factor(S, form, prec)
+        S.profile(True)
+        S.solve(p.u0, p.f)
+        assert (S.get_option(N.FDE_OPT_TRSV_W_IN_USE) > 0) == runs, form
+        assert (S.profile_query("trsv")["count"] > 0) == runs
+        assert (S.profile_query("hier_sub")["count"] > 0) == (not runs)
+    S.close()
