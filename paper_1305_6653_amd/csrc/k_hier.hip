@@ -1209,8 +1209,10 @@ hipError_t launch_hier_leaf(const InstDesc *D, const ItemMap &map, int items, in
 }
 template <typename T, int NE>
 static hipError_t hier_node_ne(const InstDesc *D, const ItemMap &map, int items, int lev, int R, int *flag, hipStream_t st) {
-  const size_t lds = (4 * R * R + 128) * sizeof(c_t<T>);
-  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_node<T, NE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // the limit is the kernel's for the whole process: always that of the largest rank, so that threads
+  // with different ranks do not lower it for each other
+  const size_t lds = (4 * R * R + 128) * sizeof(c_t<T>), most = (4 * 16 * NE * NE + 128) * sizeof(c_t<T>);
+  const hipError_t e = hipFuncSetAttribute((const void *)k_hier_node<T, NE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_hier_node<T, NE>), dim3(items), dim3(512), lds, st, D, map, lev, flag);
   return hipGetLastError();
