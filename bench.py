@@ -76,15 +76,15 @@ PMC_MEASURED = {
                 ("mixed", "hess_reduce"): 6.8204e+09, ("mixed", "hess_uinv"): 2.1905e+08,
                 ("mixed", "qgemm"): 5.2862e+07, ("mixed", "trsv"): 1.3156e+09}},
     # profiles/hbm_traffic_m4095_s256_gbdf3.txt
-    "c3": {"hash": {"hier": "1906dca0a9944c31", "spacetime": "0f1619def8dd30b9", "krylov": "50b514dae8dc2928"},
+    "c3": {"hash": {"hier": "e5e6111377301756", "spacetime": "0f1619def8dd30b9", "krylov": "50b514dae8dc2928"},
            "bytes": {
-               ("fp64", "hier_leaf"): 2.6758e+09, ("fp64", "hier_node"): 7.5209e+08,
-               ("fp64", "hier_cols"): 1.6609e+09, ("fp64", "hier_sub"): 1.0322e+09,
-               ("fp64", "hier_up"): 3.2743e+08, ("mixed", "hier_leaf"): 1.0703e+09,
-               ("mixed", "hier_node"): 2.3723e+08, ("mixed", "hier_cols"): 5.3949e+08,
-               ("mixed", "hier_sub"): 4.5128e+08, ("mixed", "hier_up"): 1.1706e+08,
-               ("fp64", "mgs"): 9.0766e+07, ("fp64", "bvm_matvec"): 4.4981e+07,
-               ("fp64", "time_rfft"): 2.0748e+07, ("fp64", "time_irfft"): 1.6904e+07}},
+               ("fp64", "hier_leaf"): 2.6557e+09, ("fp64", "hier_node"): 7.5213e+08,
+               ("fp64", "hier_cols"): 1.6723e+09, ("fp64", "hier_sub"): 1.0323e+09,
+               ("fp64", "hier_up"): 3.2743e+08, ("mixed", "hier_leaf"): 9.4920e+08,
+               ("mixed", "hier_node"): 2.3721e+08, ("mixed", "hier_cols"): 5.3971e+08,
+               ("mixed", "hier_sub"): 4.5127e+08, ("mixed", "hier_up"): 1.1707e+08,
+               ("fp64", "mgs"): 9.0768e+07, ("fp64", "bvm_matvec"): 4.4981e+07,
+               ("fp64", "time_rfft"): 2.1918e+07, ("fp64", "time_irfft"): 1.6811e+07}},
     "c3b": {"hash": {"factor": "d6f84b1eccd5a802", "band": "25254ed24f34b195", "hessenberg": "ed9a807ae6d95f67"},
            "bytes": {
                ("fp64", "trsv"): 1.7694e+10, ("fp64", "band_lu_step"): 9.8113e+08,
